@@ -32,6 +32,7 @@ struct ChunkInfo {
   uint32_t *h_wpos = nullptr;   // pinned host [ntok]
   uint16_t *h_z = nullptr;      // pinned host [ntok]
   uint32_t *doc_off = nullptr, *d_cap = nullptr, *word_off = nullptr, *region = nullptr;  // device, chunk-local
+  uint32_t *light_batch = nullptr; // device: the chunk's light regions in batches
   uint32_t *heavy_docs = nullptr;  // device: the chunk's documents longer than kHeavyDocTokens (chunk-local ids)
   uint32_t d_slots = 0;         // D-row slots of the chunk's documents
   Params p{};                   // launch parameters of the chunk
@@ -106,6 +107,7 @@ DevState chunk_state(const lda_handle *h, const ChunkInfo &ci, const ChunkSlot &
   d.d_cap = ci.d_cap;
   d.word_off = ci.word_off;
   d.region = ci.region;
+  d.light_batch = ci.light_batch;
   d.heavy_docs = ci.heavy_docs;
   d.dt_word = sl.dt_word;
   d.dt_wpos = sl.dt_wpos;
@@ -283,6 +285,10 @@ lda_status chunked_create(lda_handle *h, const int32_t *word, const int32_t *doc
     ci.p.M = int32_t(ci.ndoc);
     ci.p.n_regions = int64_t(region.size() / 3);
     ci.p.light_begin = light_region_start(region, K, p.big_k != 0);
+    const std::vector<uint32_t> batches = light_batches(region, ci.p.light_begin, int64_t(p.grid_regions) * 2);
+    ci.p.n_light_batches = int32_t(batches.size() - 1);
+    LDA_TRY(dalloc(h, &ci.light_batch, batches.size()));
+    LDA_TRY(upload(h, ci.light_batch, batches));
     ci.p.key_base = ci.tok0;
     ci.p.xcd_doc[0] = 0;
     for (int x = 1; x < kXcds; ++x) {

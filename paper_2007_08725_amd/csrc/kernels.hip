@@ -1383,14 +1383,42 @@ __device__ void draw_batch_small(bool und, uint32_t nnz, const BatchLds &bt, con
   }
 }
 
+// The draws of the lanes with `und` set: lane ln holds the token staged in
+// slot ln of the batch (row offset off, row length nnz); lanes before `first`
+// belong to another word.  Returns the drawn topic per lane (und lanes only);
+// *nnz_read gets the D-row entries this lane's draw reads.
+// Long rows: runs of tokens of one document (same row offset), whose later
+// tokens draw from the sums of the run's first one.  Rows of up to 128 slots
+// (header and entries): 4 lanes per token; up to 256: 8 lanes; up to 512: 16
+// lanes; longer rows: 16 lanes, one chunk of kChunk slots at a time; then the
+// S' walks and Q' searches, one lane per token.
+template <bool Wide>
+__device__ __forceinline__ uint32_t draw_tokens(bool und, uint32_t off, uint32_t nnz, int first, int ln,
+                                                const BatchLds &bt, const WordState &w,
+                                                const uint32_t *__restrict__ d_ent, unsigned long long &after_s,
+                                                uint32_t *nnz_read) {
+  const unsigned long long lmask = __ballot(und && nnz + 1u > 512u);
+  unsigned long long starts = 0ull;
+  bool fol = false;
+  if (lmask) {
+    const uint32_t prev_off = uint32_t(__shfl(int(off), ln - 1));
+    starts = __ballot(ln == first || off != prev_off);
+    const unsigned long long below = ln ? ~0ull >> (64 - ln) : 0ull;
+    const int rs = 63 - __clzll((long long)(starts & (below | (1ull << ln))));  // this lane's run start
+    fol = ((lmask >> ln) & 1ull) && (lmask & below & (~0ull << rs)) != 0ull;
+  }
+  *nnz_read = und ? (fol ? min(nnz, uint32_t(kChunk)) : nnz) : 0u;  // a follower reads one chunk of its row
+  draw_batch_small<Wide>(und, nnz, bt, w, d_ent, ln, after_s);
+  if (lmask) draw_long(lmask, __ballot(fol), starts, bt, w, d_ent, ln / kGroup, ln % kGroup, after_s);
+  return und ? finish_draw(ln, bt, w, d_ent) : 0u;
+}
+
 // The sampler for workgroups of NB threads (NB / 64 waves); every wave works
 // on its own batches, so NB only changes how many waves share a region's W^
 // row in LDS (larger workgroups for large K, where LDS bounds the residency).
-// Light: the workgroup is one wave and takes the light regions (the suffix
-// [p.light_begin, n_regions) of the region table: words with at most
-// kLightTokens tokens, one batch each) from their own counter; otherwise the
-// regions before p.light_begin.
-template <int NB, bool Light>
+// It takes the regions before p.light_begin; the light ones are
+// k_sampler_light's.
+template <int NB>
 __device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, unsigned long long *__restrict__ stats) {
   extern __shared__ double lds[];
   const int K = p.K;
@@ -1433,9 +1461,8 @@ __device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, u
 
   for (;;) {
     if (tid == 0) {
-      const int64_t r = Light ? p.light_begin + int64_t(atomicAdd(&d.counters[CNT_LIGHT], 1u))
-                              : int64_t(atomicAdd(&d.counters[CNT_SAMPLER], 1u));
-      s_reg[3] = r < (Light ? p.n_regions : p.light_begin) ? 1u : 0u;
+      const int64_t r = int64_t(atomicAdd(&d.counters[CNT_SAMPLER], 1u));
+      s_reg[3] = r < p.light_begin ? 1u : 0u;
       if (s_reg[3]) {
         s_reg[0] = d.region[3 * size_t(r)];
         s_reg[1] = d.region[3 * size_t(r) + 1];
@@ -1572,29 +1599,12 @@ __device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, u
         bt.nnz[ln] = nnz;
         bt.u[ln] = uniform_draw(p.seed, t, key);
       }
-      // long rows: runs of tokens of one document (same row offset), whose
-      // later tokens draw from the sums of the run's first one
-      const unsigned long long lmask = __ballot(und && nnz + 1u > 512u);
-      unsigned long long starts = 0ull;
-      bool fol = false;
-      if (lmask) {
-        const uint32_t prev_off = uint32_t(__shfl(int(off), ln - 1));
-        starts = __ballot(ln == 0 || off != prev_off);
-        const unsigned long long below = ln ? ~0ull >> (64 - ln) : 0ull;
-        const int rs = 63 - __clzll((long long)(starts & (below | (1ull << ln))));  // this lane's run start
-        fol = ((lmask >> ln) & 1ull) && (lmask & below & (~0ull << rs)) != 0ull;
-      }
       n_sampled += uint32_t(__popcll(__ballot(und)));
-      nnz_sum += wave_sum_u32(fol ? min(nnz, uint32_t(kChunk)) : nnz);  // a follower reads one chunk of its row
-      // rows of up to 128 slots (header and entries): 4 lanes per token; up
-      // to 256: 8 lanes; up to 512: 16 lanes; longer rows: 16 lanes, one
-      // chunk of kChunk slots at a time
-      draw_batch_small<(NB >= 1024)>(und, nnz, bt, w, d.d_ent, ln, n_after_s);
-      if (lmask) draw_long(lmask, __ballot(fol), starts, bt, w, d.d_ent, ln / kGroup, ln % kGroup, n_after_s);
-      // the S' walks and Q' searches, one lane per token; the batch's topics
-      // (K1 for the tokens the step-3 test decided) leave in one coalesced store
-      uint32_t topic = K1;
-      if (und) topic = finish_draw(ln, bt, w, d.d_ent);
+      uint32_t nnz_read;
+      const uint32_t drawn = draw_tokens<(NB >= 1024)>(und, off, nnz, 0, ln, bt, w, d.d_ent, n_after_s, &nnz_read);
+      nnz_sum += wave_sum_u32(nnz_read);
+      // the batch's topics (K1 for the tokens the step-3 test decided) leave in one coalesced store
+      const uint32_t topic = und ? drawn : K1;
       if (j < be) d.z_w[j] = uint16_t(topic);
     }
     __syncthreads();
@@ -1614,22 +1624,176 @@ __device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, u
 
 __global__ __launch_bounds__(256, 7) void k_sampler(DevState d, Params p, uint32_t t,
                                                  unsigned long long *__restrict__ stats) {
-  sampler_body<256, false>(d, p, t, stats);
+  sampler_body<256>(d, p, t, stats);
 }
 __global__ __launch_bounds__(512, 4) void k_sampler_512(DevState d, Params p, uint32_t t,
                                                      unsigned long long *__restrict__ stats) {
-  sampler_body<512, false>(d, p, t, stats);
+  sampler_body<512>(d, p, t, stats);
 }
 __global__ __launch_bounds__(1024, 4) void k_sampler_1024(DevState d, Params p, uint32_t t,
                                                        unsigned long long *__restrict__ stats) {
-  sampler_body<1024, false>(d, p, t, stats);
+  sampler_body<1024>(d, p, t, stats);
 }
-// The light regions, one wave each (Sec. 5.1: light units to wavefronts): a
-// word of at most kLightTokens tokens stages its W^' row and Q' prefix with
-// one wave and wave-local barriers instead of tying up a whole workgroup.
-__global__ __launch_bounds__(64) void k_sampler_light(DevState d, Params p, uint32_t t,
-                                                      unsigned long long *__restrict__ stats) {
-  sampler_body<64, true>(d, p, t, stats);
+// The light regions (Sec. 5.1: light units to wavefronts): words of at most
+// kLightTokens tokens, the suffix [p.light_begin, n_regions) of the region
+// table.  A wave takes batches of consecutive light words (d.light_batch: at
+// most 64 tokens together), dealt round-robin over the grid.  The tokens of
+// all the batch's words are staged at once, one per lane (records, row header
+// and uniform), then the words are drawn in turn: the W^' row in the wave's
+// LDS with only the previous word's topics restored, the Q' prefix, the
+// rounds over the word's lanes.  The next word's row entries are loaded while
+// a word is drawn.
+//
+// What bounds it is the chain of memory latencies per word, so the wave holds
+// as little LDS as it can (no table of the Q' blocks' partial sums: 16 waves
+// per CU at K = 1,000 instead of 8) and no word waits for a counter: a
+// counter on one address takes about 85 million atomics a second, 7.3 ms for
+// 623,000 light words.
+__global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, uint32_t t,
+                                                         unsigned long long *__restrict__ stats) {
+  extern __shared__ double lds[];
+  const int K = p.K;
+  const int nb = (K + kGroup - 1) / kGroup;
+  const int nbp = q_blocks_padded(nb);
+  const bool by_doc = doc_marks(d, p, t);
+  double *wh = lds;                  // [wh_entries(K)]
+  double *qb = lds + wh_entries(K);  // [nbp + 1]
+  double *s_u = qb + nbp + 1;        // [64]
+  uint32_t *s_off = reinterpret_cast<uint32_t *>(s_u + kWave);
+  uint32_t *s_nnz = s_off + kWave;
+  uint32_t *s_hand = s_nnz + kWave;  // [kWave / kGroup * kMaxRun]
+  uint16_t *s_top = reinterpret_cast<uint16_t *>(s_hand + kWave / kGroup * kMaxRun);
+  uint8_t *s_list = reinterpret_cast<uint8_t *>(s_top + kWave);
+  const BatchLds bt{s_off, s_nnz, s_u, s_top, s_hand, s_list};
+  const int lane = threadIdx.x;
+  if (blockIdx.x == 0 && lane == 0) stats[ST_MARKS] = by_doc ? 2ull : 1ull;
+  for (int q = nb + 1 + lane; q < nbp; q += kWave) qb[q] = __builtin_inf();
+  if (lane == 0) qb[0] = 0.0;
+  for (int k = K + lane; k < wh_entries(K); k += kWave) wh[k] = 0.0;
+  // the sparse word whose row wh holds (nnz 0 and K1 = K after the first
+  // fill; held < 0: a dense row or none, so that all of wh is rewritten)
+  int held = -1;
+  uint32_t held_k = 0, held_k1 = 0;  // lane q: topic of the held row's entry q
+  unsigned long long n_sampled = 0, n_after_s = 0, nnz_sum = 0, n_dreg = 0, row_bytes = 0, n_reg = 0;
+  // a wave's LDS accesses run in order; the fence keeps the compiler's order
+  auto order = [&]() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+
+  for (uint32_t bi = blockIdx.x; bi < uint32_t(p.n_light_batches); bi += gridDim.x) {
+    const uint32_t r0 = __builtin_amdgcn_readfirstlane(d.light_batch[bi]);
+    const int nw = int(__builtin_amdgcn_readfirstlane(d.light_batch[bi + 1]) - r0);  // 1..64
+    // lane i: word i of the batch
+    const size_t rr = 3 * (size_t(p.light_begin) + r0 + uint32_t(min(lane, nw - 1)));
+    const uint32_t v_l = d.region[rr], b_l = d.region[rr + 1], e_l = d.region[rr + 2];
+    const uint32_t b0 = __builtin_amdgcn_readlane(b_l, 0), e0 = __builtin_amdgcn_readlane(e_l, nw - 1);
+    // lane ln: token ln of the batch
+    const int ln = lane_here();
+    const uint32_t j = b0 + uint32_t(ln);
+    uint32_t sk = 0, key = 0, off = 0;
+    if (j < e0) {
+      const uint2 kr = d.wt_kr[j];
+      key = kr.x;
+      off = kr.y;
+      sk = by_doc ? d.skip_doc[key >> 5] >> (key & 31u) : d.skip_bits[j >> 5] >> (j & 31u);
+    }
+    const bool und = j < e0 && !(sk & 1u);
+    const bool dense_l = int32_t(v_l) < p.n_dense;
+    const int s_l = dense_l ? 0 : int(v_l) - p.n_dense;
+    const uint32_t nnz_l = dense_l ? 0u : d.ws_nnz[s_l];
+    const uint32_t cap_l = dense_l ? 0u : d.ws_cap[s_l];
+    const uint32_t k1_l = d.wrec[v_l].k1;
+    uint32_t nnz = 0;
+    if (und) {
+      nnz = d.d_ent[off] & 0xFFFFu;
+      bt.off[ln] = off;
+      bt.nnz[ln] = nnz;
+      bt.u[ln] = uniform_draw(p.seed, t, key);
+    }
+    n_sampled += uint32_t(__popcll(__ballot(und)));
+    n_reg += uint32_t(nw);
+    n_dreg += uint32_t(__popcll(__ballot(lane < nw && dense_l)));
+    if (lane < nw && b_l == d.word_off[v_l]) row_bytes += dense_l ? 4ull * uint64_t(K) : 4ull * nnz_l;
+    // word i's row entry (one per lane: a sparse word of at most 64 tokens)
+    auto entry_of = [&](int i) {
+      const uint32_t n = __builtin_amdgcn_readlane(nnz_l, i), c = __builtin_amdgcn_readlane(cap_l, i);
+      return uint32_t(lane) < n ? d.ws_ent[c + uint32_t(lane)] : 0u;
+    };
+    uint32_t ent_next = entry_of(0);
+    uint32_t topic = 0;
+    for (int i = 0; i < nw; ++i) {
+      const uint32_t v = __builtin_amdgcn_readlane(v_l, i);
+      const uint32_t ent = ent_next;
+      if (i + 1 < nw) ent_next = entry_of(i + 1);
+      const int f = int(__builtin_amdgcn_readlane(b_l, i) - b0), l = int(__builtin_amdgcn_readlane(e_l, i) - b0);
+      const uint32_t K1 = __builtin_amdgcn_readlane(k1_l, i);
+      const bool mine = ln >= f && ln < l;
+      if (__ballot(mine && und) == 0ull) {  // decided by step 3
+        if (mine) topic = K1;
+        continue;
+      }
+      const double a1 = d.wrec[v].a1, qp = d.wrec[v].qp;
+      if (int32_t(v) < p.n_dense) {
+        const int32_t *wrow = d.w_dense + size_t(v) * size_t(K);
+        for (int k = lane; k < K; k += kWave) wh[k] = what(uint32_t(wrow[k]), p.beta, d.den[k]);
+        held = -1;
+      } else {
+        const uint32_t n = __builtin_amdgcn_readlane(nnz_l, i);
+        const uint32_t ek = ent >> 16;
+        const double we = uint32_t(lane) < n ? what(ent & 0xFFFFu, p.beta, d.den[ek]) : 0.0;
+        if (held >= 0) {
+          if (lane < held) wh[held_k] = d.bden[held_k];
+          if (lane == 0 && held_k1 < uint32_t(K)) wh[held_k1] = d.bden[held_k1];  // K1 = K in two-branch mode
+        } else {
+          for (int k = lane; k < K; k += kWave) wh[k] = d.bden[k];
+        }
+        order();
+        if (uint32_t(lane) < n) wh[ek] = we;
+        held = int(n);
+        held_k = ek;
+        held_k1 = K1;
+      }
+      order();
+      if (lane == 0) {
+        wh[K1] = 0.0;  // the max topic is its own branch (Eq. 5)
+        wh[K] = 0.0;   // topic of the padding entries of D rows
+      }
+      order();
+      // the Q' prefix over blocks of kGroup topics, one block per lane and
+      // round, summed from topic lane % 16 on, wrapping, so that the 16 lanes
+      // of a row read 16 different LDS bank pairs
+      uint32_t rot;
+      asm volatile("v_mov_b32 %0, %1" : "=v"(rot) : "v"(uint32_t(ln & (kGroup - 1))));
+      double acc = 0.0;
+      for (int q0 = 0; q0 < nb; q0 += kWave) {
+        const int blk = q0 + ln;
+        double s = 0.0;
+        if (blk < nb) {
+          const double *wb = wh + blk * kGroup;
+#pragma unroll
+          for (uint32_t q = 0; q < uint32_t(kGroup); ++q) s += p.alpha * wb[(q + rot) & uint32_t(kGroup - 1)];
+        }
+        const double incl = acc + wave_incl_scan(s);
+        if (blk < nb) qb[blk + 1] = incl;
+        acc = __shfl(incl, kWave - 1);
+      }
+      order();
+      const WordState w{wh, qb, nb, K, nbp / 2, K1, a1, qp, p.alpha, nullptr, nullptr};
+      uint32_t nnz_read;
+      const uint32_t drawn = draw_tokens<false>(mine && und, off, nnz, f, ln, bt, w, d.d_ent, n_after_s, &nnz_read);
+      nnz_sum += wave_sum_u32(nnz_read);
+      if (mine) topic = und ? drawn : K1;
+      order();  // wh and qb are rewritten for the next word
+    }
+    if (j < e0) d.z_w[j] = uint16_t(topic);
+  }
+  row_bytes = group_sum_u64<kWave>(row_bytes);
+  if (lane == 0) {
+    if (n_sampled) atomicAdd(&stats[ST_SAMPLED], n_sampled);
+    if (n_after_s) atomicAdd(&stats[ST_SKIP_AFTER_S], n_after_s);
+    if (nnz_sum) atomicAdd(&stats[ST_NNZ], nnz_sum);
+    if (n_reg) atomicAdd(&stats[ST_REGIONS], n_reg);
+    if (n_dreg) atomicAdd(&stats[ST_DENSE_REGIONS], n_dreg);
+    if (row_bytes) atomicAdd(&stats[ST_ROW_BYTES], row_bytes);
+  }
 }
 
 // ---------------------------------------------------------- large K ----
@@ -3082,13 +3246,20 @@ hipError_t launch_sampler(const DevState &d, const Params &p, uint32_t t, hipStr
   return hipGetLastError();
 }
 
+// The light sampler's dynamic LDS for K topics (one wave).
+size_t light_lds_bytes(int K) {
+  const size_t nbp = size_t(q_blocks_padded((K + kGroup - 1) / kGroup));
+  return sizeof(double) * (size_t(wh_entries(K)) + nbp + 1 + kWave) +
+         size_t(kWave) * (2 * sizeof(uint32_t) + sizeof(uint16_t) + 1) + sizeof(uint32_t) * (kWave / kGroup * kMaxRun);
+}
+
 hipError_t launch_sampler_light(const DevState &d, const Params &p, uint32_t t, hipStream_t s) {
-  if (p.light_begin >= p.n_regions) return hipSuccess;
-  const size_t lds = sampler_lds_bytes(p.K, kWave, p.q_table != 0);
+  if (p.n_light_batches <= 0) return hipSuccess;
+  const size_t lds = light_lds_bytes(p.K);
   hipError_t err = allow_lds(k_sampler_light, lds);
   if (err != hipSuccess) return err;
-  const int64_t n_light = p.n_regions - p.light_begin;
-  const uint32_t grid = uint32_t(std::min<int64_t>(n_light, int64_t(p.grid_regions) * 2));
+  // at most 16 one-wave workgroups per CU (grid_regions is 8 per CU)
+  const uint32_t grid = uint32_t(std::min<int64_t>(p.n_light_batches, int64_t(p.grid_regions) * 2));
   hipLaunchKernelGGL(k_sampler_light, dim3(grid), dim3(kWave), lds, s, d, p, t, d.stats);
   return hipGetLastError();
 }

@@ -213,4 +213,24 @@ lda_status build_layout(const int32_t *word, const int32_t *doc, int64_t n, int3
   return LDA_OK;
 }
 
+std::vector<uint32_t> light_batches(const std::vector<uint32_t> &region, int64_t light_begin, int64_t waves) {
+  const size_t n = region.size() / 3, r0 = size_t(light_begin);
+  std::vector<uint32_t> out(1, 0u);
+  if (r0 >= n) return out;
+  int64_t tokens = 0;
+  for (size_t r = r0; r < n; ++r) tokens += region[3 * r + 2] - region[3 * r + 1];
+  const uint32_t most = uint32_t(std::min<int64_t>(kLightTokens, std::max<int64_t>(16, tokens / std::max<int64_t>(waves, 1))));
+  uint32_t begin = region[3 * r0 + 1];  // first token of the open batch
+  for (size_t r = r0 + 1; r < n; ++r) {
+    const uint32_t b = region[3 * r + 1], e = region[3 * r + 2];
+    // a batch's tokens are consecutive (a split word between two light ones ends it)
+    if (b != region[3 * r - 1] || e - begin > most) {
+      out.push_back(uint32_t(r - r0));
+      begin = b;
+    }
+  }
+  out.push_back(uint32_t(n - r0));
+  return out;
+}
+
 }  // namespace lda

@@ -196,6 +196,12 @@ lda_status create_device(lda_handle *h, const lda_options *o, const int32_t *wor
     LDA_TRY(dalloc(h, &d.heavy_docs, heavy.size()));
     LDA_TRY(upload(h, d.heavy_docs, heavy));
   }
+  {
+    const std::vector<uint32_t> batches = light_batches(L.region, p.light_begin, int64_t(p.grid_regions) * 2);
+    p.n_light_batches = int32_t(batches.size() - 1);
+    LDA_TRY(dalloc(h, &d.light_batch, batches.size()));
+    LDA_TRY(upload(h, d.light_batch, batches));
+  }
   LDA_TRY(dalloc(h, &d.split, L.split.size()));
   LDA_TRY(dalloc(h, &d.z_w, n));
   LDA_TRY(dalloc(h, &d.skip_bits, skip_words(int64_t(n))));

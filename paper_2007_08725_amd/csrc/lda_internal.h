@@ -144,6 +144,7 @@ struct DevState {
   uint32_t *doc_off, *dt_word, *dt_key, *dt_wpos, *word_off;
   uint2 *wt_kr;       // per word-ordered token: (input index = RNG key, D-row offset of its document)
   uint32_t *region;   // 3 per region
+  uint32_t *light_batch; // light regions per batch of the light sampler: [n_light_batches + 1], from p.light_begin
   uint32_t *heavy_docs;  // documents longer than kHeavyDoc tokens (one workgroup each in the doc kernels)
   uint8_t *split;     // per dense word
   // assignment, word order
@@ -206,7 +207,8 @@ struct Params {
   int32_t always_skip_test;  // steps 2-3 every iteration instead of when they pay (lda_options)
   uint32_t key_base;     // out-of-core chunks: input index of the chunk's first doc-ordered token (else 0)
   int32_t n_heavy;       // entries of heavy_docs
-  int64_t light_begin;   // regions [light_begin, n_regions): light words, one wave each in the sampler
+  int64_t light_begin;   // regions [light_begin, n_regions): light words, drawn by single waves
+  int32_t n_light_batches;  // entries of light_batch, less one
   int32_t doc_marks_ok;  // the document-ordered bitmap is usable: keys are document positions, regular sampler
   int32_t q_table;       // the sampler keeps the Q' blocks' partial sums in LDS (search instead of walk)
   uint32_t xcd_doc[kXcds + 1];  // document ranges with equal token counts, one per XCD (D rebuild)
@@ -215,7 +217,7 @@ struct Params {
 // Scheduler counters: one each for the region kernels and the doc pass,
 // kXcds (one per document range) for the D rebuild.
 enum { CNT_SAMPLER = 0, CNT_DOCPASS = 2, CNT_LOGLIK = 4, CNT_HEAVY_PASS = 5,
-       CNT_HEAVY_REBUILD = 6, CNT_LIGHT = 7, CNT_REBUILD_D = 16 };
+       CNT_HEAVY_REBUILD = 6, CNT_REBUILD_D = 16 };
 constexpr int kCounters = 32;
 enum { ST_SKIP3 = 0, ST_SKIP_AFTER_S = 1, ST_SAMPLED = 2, ST_NNZ = 3, ST_REGIONS = 4, ST_DENSE_REGIONS = 5, ST_ERRORS = 6,
        ST_ROW_BYTES = 7, ST_MARKS = 8, ST_TEST_RAN = 9 };
@@ -232,7 +234,7 @@ hipError_t launch_clear_skips(const DevState &d, const Params &p, uint32_t t, hi
 hipError_t launch_reset_counters(uint32_t *counters, hipStream_t s);
 hipError_t launch_doc_pass(const DevState &d, const Params &p, uint32_t t, hipStream_t s);
 // The sampler of the regions before p.light_begin (or every region with the
-// tiled sampler), and that of the light regions, one wave each (nothing when
+// tiled sampler), and that of the light regions, by single waves (nothing when
 // there are none); the two touch disjoint topic slots and may run at once.
 hipError_t launch_sampler(const DevState &d, const Params &p, uint32_t t, hipStream_t s);
 hipError_t launch_sampler_light(const DevState &d, const Params &p, uint32_t t, hipStream_t s);
@@ -240,17 +242,23 @@ int sampler_block(int K, int want, bool *q_table);
 // The sampler's dynamic LDS for K topics and workgroups of nb threads.
 size_t sampler_lds_bytes(int K, int nb, bool q_table);
 // Regions of at most this many tokens (one batch of the sampler) are light:
-// a wave takes each of them, when the per-wave W^' row is small (K up to
-// about 2,000).  They form a suffix of the region table, which lists the
-// unsplit words by descending token count after the split ones.
+// single waves take them, several words at a time, when the per-wave W^' row
+// is small (K up to about 2,200: 8 waves per CU, against as many workgroups of
+// the regular sampler).  They form a suffix of the region table, which lists
+// the unsplit words by descending token count after the split ones.
 constexpr uint32_t kLightTokens = 64;
 constexpr size_t kLightLdsMax = 20 * 1024;
+size_t light_lds_bytes(int K);
 inline int64_t light_region_start(const std::vector<uint32_t> &region, int K, bool big_k) {
   int64_t r = int64_t(region.size() / 3);
-  if (big_k || sampler_lds_bytes(K, 64, true) > kLightLdsMax) return r;
+  if (big_k || light_lds_bytes(K) > kLightLdsMax) return r;
   while (r > 0 && region[3 * size_t(r - 1) + 2] - region[3 * size_t(r - 1) + 1] <= kLightTokens) --r;
   return r;
 }
+// The light regions cut into batches of consecutive word-ordered tokens, as
+// offsets from light_begin: at most 64 tokens each, fewer (down to 16) when
+// that would leave the light sampler's waves without a batch.
+std::vector<uint32_t> light_batches(const std::vector<uint32_t> &region, int64_t light_begin, int64_t waves);
 // Large K: topics per tile and the tiled sampler's dynamic LDS.
 int tiled_topics(int K);
 size_t tiled_lds_bytes(int K, int kt);
