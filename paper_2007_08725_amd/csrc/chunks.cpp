@@ -283,6 +283,7 @@ lda_status chunked_create(lda_handle *h, const int32_t *word, const int32_t *doc
     ci.p.n_heavy = int32_t(heavy.size());
     ci.p.n = ci.ntok;
     ci.p.M = int32_t(ci.ndoc);
+    set_doc_batches(ci.p);
     ci.p.n_regions = int64_t(region.size() / 3);
     ci.p.light_begin = light_region_start(region, K, p.big_k != 0);
     const std::vector<uint32_t> batches = light_batches(region, ci.p.light_begin, int64_t(p.grid_regions) * 2);

@@ -232,7 +232,7 @@ __global__ void k_clear_skips(uint32_t *__restrict__ bits, uint32_t *__restrict_
 }
 
 __global__ void k_reset_counters(uint32_t *__restrict__ counters) {
-  if (threadIdx.x < kCounters) counters[threadIdx.x] = 0u;
+  for (int i = int(threadIdx.x); i < kCounters; i += int(blockDim.x)) counters[i] = 0u;
 }
 
 // Whether iteration t carries its skip decisions in the document-ordered
@@ -270,8 +270,8 @@ __global__ void k_begin(const uint32_t *__restrict__ T, double *__restrict__ den
     den[k] = dk;
     bden[k] = what(0u, beta, dk);  // W^[v][k] of every topic that word v does not hold
   }
-  if (blockIdx.x == 0 && threadIdx.x < kCounters) {
-    counters[threadIdx.x] = 0u;
+  if (blockIdx.x == 0) {
+    for (int i = int(threadIdx.x); i < kCounters; i += int(blockDim.x)) counters[i] = 0u;
     if (stats && threadIdx.x < kStatsPerIter) stats[threadIdx.x] = 0ull;
   }
 }
@@ -485,11 +485,6 @@ __global__ __launch_bounds__(kBlock) void k_word_pre_wave(DevState d, Params p) 
 // out in batches through an atomic counter.  The document's D row is spread
 // into a per-wave topic -> count table in LDS, so each token's C1 and C2 are
 // two LDS reads; the table is cleared again from the row afterwards.
-constexpr uint32_t kDocBatch = 32;
-// Documents per batch of the D rebuild: a smaller window of documents in
-// flight keeps more of its topic gathers in the caches (at 16 and below the
-// counters' atomics start to bound the kernel).
-constexpr uint32_t kRebuildBatch = 24;
 
 // Next batch [d0, d1) of documents for a wave of the D rebuild.  The
 // documents are split into kXcds ranges of equal token counts; workgroups are
@@ -503,13 +498,19 @@ __device__ __forceinline__ bool next_docs(uint32_t *__restrict__ cnt, const Para
   const int x = int(blockIdx.x % kXcds);
   while (part < kXcds) {
     const int r = (x + part) % kXcds;
+    const uint32_t b0 = p.xcd_doc[r], e = p.xcd_doc[r + 1];
+    uint32_t *c = cnt + r * kLine;
     uint32_t o = 0;
-    if (lane == 0) o = atomicAdd(&cnt[r], kRebuildBatch);
+    // another XCD's range is looked at before it is counted down (the counter
+    // only grows, so an old value costs at most a wasted atomic)
+    if (lane == 0 && (part == 0 || __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < e - b0))
+      o = atomicAdd(c, p.rebuild_batch);
+    else if (lane == 0)
+      o = e - b0;
     o = __shfl(o, 0);
-    const uint32_t b = p.xcd_doc[r] + o, e = p.xcd_doc[r + 1];
-    if (o < e - p.xcd_doc[r]) {
-      d0 = b;
-      d1 = min(b + kRebuildBatch, e);
+    if (o < e - b0) {
+      d0 = b0 + o;
+      d1 = min(d0 + p.rebuild_batch, e);
       return true;
     }
     ++part;
@@ -610,11 +611,15 @@ __global__ __launch_bounds__(kBlock) void k_doc_pass(DevState d, Params p, uint3
     return skip_test<KeyId>(d, p, t, cmap, pp, len, h, v);
   };
   for (;;) {
-    uint32_t d0 = 0;
-    if (lane == 0) d0 = atomicAdd(&d.counters[CNT_DOCPASS], kDocBatch);
-    d0 = __builtin_amdgcn_readfirstlane(__shfl(d0, 0));
-    if (d0 >= M) break;
-    const int nd = int(min(M, d0 + kDocBatch) - d0);
+    // batches i, i + kDocStripes, ... from the workgroup's stripe's counter
+    const uint32_t stripe = blockIdx.x % uint32_t(kDocStripes);
+    uint32_t o = 0;
+    if (lane == 0) o = atomicAdd(&d.counters[CNT_DOCPASS + stripe * uint32_t(kLine)], 1u);
+    o = __builtin_amdgcn_readfirstlane(__shfl(o, 0));
+    const uint64_t first = (uint64_t(o) * uint32_t(kDocStripes) + stripe) * p.doc_batch;
+    if (first >= M) break;
+    const uint32_t d0 = uint32_t(first);
+    const int nd = int(min(M, d0 + p.doc_batch) - d0);
     // the batch's document offsets and row offsets, one per lane
     const uint32_t offv = lane <= nd ? d.doc_off[d0 + uint32_t(lane)] : 0u;
     const uint32_t capv = lane < nd ? d.d_cap[d0 + uint32_t(lane)] : 0u;
@@ -3116,7 +3121,7 @@ hipError_t launch_clear_skips(const DevState &d, const Params &p, uint32_t t, hi
 }
 
 hipError_t launch_reset_counters(uint32_t *counters, hipStream_t s) {
-  hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(kWave), 0, s, counters);
+  hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(kBlock), 0, s, counters);
   return hipGetLastError();
 }
 
@@ -3151,7 +3156,7 @@ hipError_t launch_doc_pass(const DevState &d, const Params &p, uint32_t t, hipSt
   const auto kernel = p.key_identity ? k_doc_pass<true> : k_doc_pass<false>;
   hipError_t err = allow_lds(kernel, lds);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(kernel, dim3(uint32_t(p.grid_docs)), dim3(kWave * p.doc_waves), lds, s, d, p, t, d.stats);
+  hipLaunchKernelGGL(kernel, dim3(doc_pass_grid(p)), dim3(kWave * p.doc_waves), lds, s, d, p, t, d.stats);
   return hipGetLastError();
 }
 
@@ -3324,7 +3329,7 @@ hipError_t launch_rebuild_d(const DevState &d, const Params &p, hipStream_t s) {
   // half the document grid (4 workgroups per CU): fewer waves in flight keep
   // a narrower window of documents, whose topic gathers then hit the caches
   // more often
-  const uint32_t dgrid = uint32_t(std::max(1, p.grid_docs / 2));
+  const uint32_t dgrid = rebuild_grid(p);
   if (!p.big_k) {
     hipLaunchKernelGGL(k_rebuild_d, dim3(dgrid), dim3(kWave * p.doc_waves), dlds, s, d, p, 1);
     return hipGetLastError();

@@ -88,6 +88,7 @@ lda_status setup_device(lda_handle *h, const lda_options *o) {
     p.doc_waves = best;
   }
   p.grid_docs = std::max(1, cus * 8);
+  set_doc_batches(p);
   return LDA_OK;
 }
 

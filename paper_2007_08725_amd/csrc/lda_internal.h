@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -162,7 +163,7 @@ struct DevState {
   WordRec *wrec;
   SkipRec *wskip;
   // scheduler counters and statistics
-  uint32_t *counters;           // [8]
+  uint32_t *counters;           // [kCounters]
   unsigned long long *stats;    // [8]
   double *ll_part;              // [n_regions]
   double *ll_out;               // [1]
@@ -201,6 +202,7 @@ struct Params {
   int32_t tile_topics;   // topics per tile of the tiled sampler (a multiple of 16)
   int32_t max_region;    // tokens of the largest region
   int32_t doc_waves;     // waves per workgroup of the doc pass and the D rebuild (LDS tables of K entries per wave)
+  uint32_t doc_batch, rebuild_batch;  // documents a wave takes per counter atomic (doc pass, D rebuild)
   int32_t sparse_pre;    // per-word precompute of sparse words from their row and a topic list (large K)
   int32_t top_list;      // length of that topic list
   int32_t skip_marks;    // 0 auto, 1 word-ordered bitmap, 2 document-ordered bitmap (lda_options)
@@ -214,11 +216,36 @@ struct Params {
   uint32_t xcd_doc[kXcds + 1];  // document ranges with equal token counts, one per XCD (D rebuild)
 };
 
-// Scheduler counters: one each for the region kernels and the doc pass,
-// kXcds (one per document range) for the D rebuild.
-enum { CNT_SAMPLER = 0, CNT_DOCPASS = 2, CNT_LOGLIK = 4, CNT_HEAVY_PASS = 5,
-       CNT_HEAVY_REBUILD = 6, CNT_REBUILD_D = 16 };
-constexpr int kCounters = 32;
+// Workgroups of the D rebuild by tables of K counts (k_rebuild_d) and of the
+// doc pass: no more waves than documents (a wave without a document still
+// asks every counter), rounded to whole sets of one workgroup per range.
+inline uint32_t doc_grid(int32_t most, int32_t M, int32_t waves) {
+  const int64_t wg = (int64_t(M) + waves - 1) / waves;
+  return uint32_t(std::max<int64_t>(kXcds, std::min<int64_t>(most, (wg + kXcds - 1) / kXcds * kXcds)));
+}
+inline uint32_t rebuild_grid(const Params &p) { return doc_grid(std::max(1, p.grid_docs / 2), p.M, p.doc_waves); }
+inline uint32_t doc_pass_grid(const Params &p) { return doc_grid(p.grid_docs, p.M, p.doc_waves); }
+// Documents per counter atomic.  Large corpora: 32 in the doc pass and 24 in
+// the D rebuild (a smaller window of documents in flight keeps more of its
+// topic gathers in the caches).  Small corpora: few enough that every wave of
+// the grid gets two batches, down to single documents.
+constexpr uint32_t kDocBatch = 32, kRebuildBatch = 24;
+inline void set_doc_batches(Params &p) {
+  const int64_t w_doc = int64_t(doc_pass_grid(p)) * p.doc_waves, w_reb = int64_t(rebuild_grid(p)) * p.doc_waves;
+  p.doc_batch = uint32_t(std::min<int64_t>(kDocBatch, std::max<int64_t>(1, p.M / (2 * w_doc))));
+  p.rebuild_batch = uint32_t(std::min<int64_t>(kRebuildBatch, std::max<int64_t>(1, p.M / (2 * w_reb))));
+}
+
+// Scheduler counters.  One cache line of the device takes about 88 million
+// atomics a second however many addresses in it they go to (8 counters in one
+// line 88M/s, in 8 lines 536M/s), so the document kernels' counters, one per
+// document range or stripe, sit on lines of their own (kLine words apart);
+// the two kernels use different words of them.
+constexpr int kLine = 32;  // u32 words per 128-byte line
+enum { CNT_SAMPLER = 0, CNT_LOGLIK = 4, CNT_HEAVY_PASS = 5, CNT_HEAVY_REBUILD = 6,
+       CNT_DOCPASS = kLine, CNT_REBUILD_D = kLine + 1 };
+constexpr int kCounters = kLine * (1 + kXcds);
+constexpr int kDocStripes = kXcds;  // counters of the doc pass
 enum { ST_SKIP3 = 0, ST_SKIP_AFTER_S = 1, ST_SAMPLED = 2, ST_NNZ = 3, ST_REGIONS = 4, ST_DENSE_REGIONS = 5, ST_ERRORS = 6,
        ST_ROW_BYTES = 7, ST_MARKS = 8, ST_TEST_RAN = 9 };
 constexpr int kStatsPerIter = 16;
@@ -286,11 +313,12 @@ hipError_t launch_sum_f64(const double *part, int64_t n, double *out, hipStream_
 // kNoAllocChunkSums, per-region partials from kNoAllocHead), its
 // device address on the current device (looked up once per device), and the
 // LLPT launches on it.  hipErrorInvalidValue past LDA_NOALLOC_MAX_REGIONS.
-constexpr size_t kNoAllocResult = 256;
-constexpr size_t kNoAllocChunkSums = 512;
+constexpr size_t kNoAllocResult = 1536;
+constexpr size_t kNoAllocChunkSums = 2048;
 constexpr size_t kNoAllocHead = 4096;
 static_assert(kNoAllocChunkSums + sizeof(double) * LDA_MAX_CHUNKS <= kNoAllocHead, "chunk sums overlap the partials");
-static_assert(sizeof(uint32_t) * kCounters <= kNoAllocResult, "counters overlap the result");
+static_assert(sizeof(uint32_t) * kCounters + sizeof(unsigned long long) * kStatsPerIter <= kNoAllocResult,
+              "counters and statistics overlap the result");
 hipError_t noalloc_scratch_address(void **out);
 hipError_t launch_loglik_noalloc(DevState d, const Params &p, void *scratch_dev, hipStream_t s);
 hipError_t launch_sum_nnz(const DevState &d, const Params &p, unsigned long long *out, hipStream_t s);
