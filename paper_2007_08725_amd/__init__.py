@@ -260,9 +260,8 @@ class LDA:
 
     def counts(self, z: bool = True, D: bool = True, W: bool = True) -> dict:
         """Assignment (input order) and count tables in the caller's ids (CSR, topics ascending)."""
-        sz = self.sizes()
+        sz = self.sizes() if D or W else None  # the tables' arrays need their sizes first
         c = Counts()
-        out = dict(iteration=sz["iteration"], M=sz["M"])
         arrays = {}
         if z:
             arrays["z"] = np.empty(self.N, np.int32)
@@ -278,6 +277,7 @@ class LDA:
         for name, arr in arrays.items():
             setattr(c, name, arr.ctypes.data)
         _check(self._lib, self._h, self._lib.lda_get_counts(self._h, ctypes.byref(c)))
+        out = dict(iteration=c.iteration, M=c.M)
         if D:
             arrays["D_topic"] = arrays["D_topic"][:sz["nnz_D"]]
             arrays["D_count"] = arrays["D_count"][:sz["nnz_D"]]

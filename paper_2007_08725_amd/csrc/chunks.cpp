@@ -23,6 +23,7 @@
 #include <cstring>
 
 #include "handle.h"
+#include "readback.h"
 
 namespace lda {
 
@@ -428,85 +429,51 @@ lda_status chunked_counts(lda_handle *h, lda_counts *out) {
     return fail(h, LDA_E_ARG, "D arrays must be given together");
   if ((out->W_off || out->W_topic || out->W_count) && (!out->W_off || !out->W_topic || !out->W_count))
     return fail(h, LDA_E_ARG, "W arrays must be given together");
-  std::vector<int32_t> wd(size_t(p.n_dense) * size_t(K));
-  if (!wd.empty()) HIP_TRY(h, hipMemcpy(wd.data(), h->d.w_dense, wd.size() * 4, hipMemcpyDeviceToHost));
-  int64_t nnz_W = 0;
-  for (int32_t x : wd) nnz_W += x != 0;
-  // D: each chunk's rows rebuilt from its topics on the device, then read back
   const bool size_query = !out->z && !out->T && !want_d && !out->W_off && !out->W_topic && !out->W_count;
-  int64_t nnz_D = 0, o = 0;
-  ChunkSlot &s0 = cm.slot[0];
-  unsigned long long *nnz_dev = reinterpret_cast<unsigned long long *>(cm.slot[1].d_ent);
-  std::vector<uint32_t> ent;
+  HIP_TRY(h, hipMemsetAsync(h->nnz, 0, 2 * sizeof(unsigned long long), h->stream));
+  HIP_TRY(h, launch_sum_nnz(h->d, p, false, true, h->nnz, h->stream));
+  Crew crew(size_query ? 1 : read_threads(size_t(L.n) * 2));
+  // D: each chunk's rows rebuilt from its topics on the device; input order is
+  // document order, so a chunk's topics land in their place of z
+  ChunkSlot &s0 = cm.slot[0], &s1 = cm.slot[1];
   size_t next_doc = 0;
+  int64_t o = 0;
   for (const ChunkInfo &ci : cm.c) {
     DevState dc = chunk_state(h, ci, s0);
     dc.stats = h->stats_base;
     LDA_TRY(load_chunk_now(h, ci, dc));
-    if (!want_d) {
-      HIP_TRY(h, hipMemsetAsync(nnz_dev, 0, sizeof(unsigned long long), h->stream));
-      HIP_TRY(h, launch_sum_nnz(dc, ci.p, nnz_dev, h->stream));
-      unsigned long long c_nnz = 0;
-      HIP_TRY(h, hipMemcpyAsync(&c_nnz, nnz_dev, sizeof(c_nnz), hipMemcpyDeviceToHost, h->stream));
-      HIP_TRY(h, hipStreamSynchronize(h->stream));
-      nnz_D += int64_t(c_nnz);
-      continue;
+    HIP_TRY(h, launch_sum_nnz(dc, ci.p, true, false, h->nnz, h->stream));
+    if (want_d) {
+      for (; next_doc < ci.doc0; ++next_doc) out->D_off[next_doc] = o;  // empty documents between chunks
+      int64_t entries = 0;
+      LDA_TRY(export_d(h, crew, dc, int32_t(ci.ndoc), o, out->D_off + ci.doc0, out->D_topic, out->D_count, &entries));
+      o += entries;
+      next_doc += ci.ndoc;
     }
-    ent.resize(ci.d_slots);
-    HIP_TRY(h, hipMemcpyAsync(ent.data(), s0.d_ent, ent.size() * 4, hipMemcpyDeviceToHost, h->stream));
-    std::vector<uint32_t> dcap(size_t(ci.ndoc) + 1);
-    HIP_TRY(h, hipMemcpyAsync(dcap.data(), ci.d_cap, dcap.size() * 4, hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
-    for (; next_doc < ci.doc0; ++next_doc) out->D_off[next_doc] = o;  // empty documents between chunks
-    for (uint32_t q = 0; q < ci.ndoc; ++q, ++next_doc) {
-      out->D_off[next_doc] = o;
-      const uint32_t hdr = ent[dcap[q]];
-      for (uint32_t e = 0; e < (hdr & 0xFFFFu); ++e) {
-        const uint32_t v = ent[size_t(dcap[q]) + 1 + e];
-        out->D_topic[o] = int32_t(v >> 16);
-        out->D_count[o] = int32_t(v & 0xFFFFu);
-        ++o;
-      }
+    if (out->z) {
+      HIP_TRY(h, launch_gather_z16(dc.dt_wpos, nullptr, dc.z_w, ci.ntok, s1.z_w, h->stream));
+      LDA_TRY(read_z(h, crew, s1.z_w, ci.ntok, out->z + ci.tok0));
     }
   }
-  if (want_d) {
+  if (want_d)
     for (; next_doc <= size_t(L.M); ++next_doc) out->D_off[next_doc] = o;
-    nnz_D = o;
-  }
+  unsigned long long nnz[2] = {0, 0};
+  HIP_TRY(h, hipMemcpyAsync(nnz, h->nnz, sizeof(nnz), hipMemcpyDeviceToHost, h->stream));
+  HIP_TRY(h, hipStreamSynchronize(h->stream));
   out->iteration = h->iteration;
   out->M = L.M;
   out->V = L.V;
   out->K = K;
   out->n_tokens = L.n;
-  out->nnz_D = nnz_D;
-  out->nnz_W = nnz_W;
+  out->nnz_D = int64_t(nnz[0]);
+  out->nnz_W = int64_t(nnz[1]);
   if (size_query) return LDA_OK;
-  if (out->z) {
-    // input order is document order: the topic of position p sits at its word-order slot
-    for (const ChunkInfo &ci : cm.c)
-      for (uint32_t q = 0; q < ci.ntok; ++q) out->z[size_t(ci.tok0) + q] = int32_t(ci.h_z[ci.h_wpos[q]]);
-  }
   if (out->T) {
     std::vector<uint32_t> tk(static_cast<size_t>(K));
     HIP_TRY(h, hipMemcpy(tk.data(), h->d.T, size_t(K) * 4, hipMemcpyDeviceToHost));
     for (int32_t k = 0; k < K; ++k) out->T[k] = tk[size_t(k)];
   }
-  if (out->W_off) {
-    int64_t w = 0;
-    for (int32_t v = 0; v < L.V; ++v) {
-      out->W_off[v] = w;
-      const int32_t r = L.relabel[size_t(v)];
-      if (r >= L.n_present) continue;
-      const int32_t *row = &wd[size_t(r) * size_t(K)];
-      for (int32_t k = 0; k < K; ++k)
-        if (row[k]) {
-          out->W_topic[w] = k;
-          out->W_count[w] = row[k];
-          ++w;
-        }
-    }
-    out->W_off[L.V] = w;
-  }
+  if (out->W_off) LDA_TRY(export_w(h, crew, h->d, p, out->W_off, out->W_topic, out->W_count));
   return LDA_OK;
 }
 

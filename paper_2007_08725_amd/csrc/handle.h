@@ -45,6 +45,11 @@ struct lda_handle {
   // out-of-core mode (lda_options.chunks > 1): the chunks, their host arrays
   // and the device slots they stream through; null when everything is resident
   std::unique_ptr<lda::ChunkMode, lda::ChunkModeDeleter> chunks;
+  // pinned buffers that results are read back through (readback.h), made by
+  // the first large read and given back with the handle
+  void *stage[2] = {nullptr, nullptr};
+  hipEvent_t stage_ev[2] = {nullptr, nullptr};
+  unsigned long long *nnz = nullptr;  // device [2]: entries of D and of W (lda_get_counts)
   int32_t chunks_wanted = 0;  // lda_options.chunks
   int64_t iteration = 0;
   bool poisoned = false;
@@ -52,6 +57,8 @@ struct lda_handle {
 };
 
 namespace lda {
+
+constexpr size_t kStageBytes = size_t(4) << 20;  // of one pinned buffer
 
 inline lda_status fail(lda_handle *h, lda_status st, const std::string &msg) {
   if (h) {

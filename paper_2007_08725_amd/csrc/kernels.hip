@@ -3084,16 +3084,6 @@ __global__ __launch_bounds__(kBlock) void k_loglik_reduce(const double *__restri
   if (threadIdx.x == 0) out[0] = s;
 }
 
-// Total entries of D (for the size query of lda_get_counts).
-__global__ void k_sum_nnz(const uint32_t *__restrict__ d_ent, const uint32_t *__restrict__ d_cap, int32_t M,
-                          unsigned long long *__restrict__ out) {
-  unsigned long long s = 0;
-  for (int64_t dd = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; dd < M; dd += int64_t(gridDim.x) * blockDim.x)
-    s += d_ent[d_cap[dd]] & 0xFFFFu;
-  s = group_sum_u64<kWave>(s);
-  if ((threadIdx.x & (kWave - 1)) == 0 && s) atomicAdd(out, s);
-}
-
 }  // namespace
 
 // ---------------------------------------------------------- launchers ----
@@ -3341,13 +3331,6 @@ hipError_t launch_rebuild_d(const DevState &d, const Params &p, hipStream_t s) {
   }
   const size_t slds = sizeof(uint16_t) * size_t(kHeavyDoc) * (kBlock / kWave);
   hipLaunchKernelGGL(k_rebuild_d_sort, dim3(uint32_t(p.grid_docs)), dim3(kBlock), slds, s, d, p);
-  return hipGetLastError();
-}
-
-hipError_t launch_sum_nnz(const DevState &d, const Params &p, unsigned long long *out, hipStream_t s) {
-  const int64_t blocks = std::min<int64_t>((int64_t(p.M) + kBlock - 1) / kBlock, 4096);
-  hipLaunchKernelGGL(k_sum_nnz, dim3(uint32_t(std::max<int64_t>(blocks, 1))), dim3(kBlock), 0, s, d.d_ent, d.d_cap,
-                     p.M, out);
   return hipGetLastError();
 }
 

@@ -59,12 +59,6 @@ __global__ void k_word_order(const uint32_t *__restrict__ wkey, const uint32_t *
   }
 }
 
-__global__ void k_scatter_z(const uint16_t *__restrict__ z_w, const uint2 *__restrict__ wt_kr, int64_t n,
-                            int32_t *__restrict__ z_in) {
-  for (int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; j < n; j += int64_t(gridDim.x) * blockDim.x)
-    z_in[wt_kr[j].x] = int32_t(z_w[j]);
-}
-
 __global__ void k_gather_z(const int32_t *__restrict__ z_in, const uint2 *__restrict__ wt_kr, int64_t n,
                            int32_t K, uint16_t *__restrict__ z_w, unsigned long long *__restrict__ bad) {
   unsigned long long nbad = 0;
@@ -120,14 +114,8 @@ __global__ void k_inflate(const uint32_t *__restrict__ doc_off, const uint32_t *
   }
 }
 
-// Topics in doc order (int32) from topics in word order, and back with a
-// range check (bad counts topics outside [0, K), which are stored as 0).
-__global__ void k_doc_gather_z(const uint32_t *__restrict__ dt_wpos, const uint16_t *__restrict__ z_w, int64_t n,
-                               int32_t *__restrict__ z_doc) {
-  for (int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n; p += int64_t(gridDim.x) * blockDim.x)
-    z_doc[p] = int32_t(z_w[dt_wpos[p]]);
-}
-
+// Topics in word order from topics in doc order (int32), with a range check
+// (bad counts topics outside [0, K), which are stored as 0).
 __global__ void k_doc_scatter_z(const int32_t *__restrict__ z_doc, const uint32_t *__restrict__ dt_wpos, int64_t n,
                                 int32_t K, uint16_t *__restrict__ z_w, unsigned long long *__restrict__ bad) {
   unsigned long long nbad = 0;
@@ -138,6 +126,112 @@ __global__ void k_doc_scatter_z(const int32_t *__restrict__ z_doc, const uint32_
     nbad += ok ? 0ull : 1ull;
   }
   if (nbad) atomicAdd(bad, nbad);
+}
+
+// ----------------------------------------------------------------- exports --
+// The kernels of lda_get_counts.  All are bound by memory (each table is read
+// once); what they replace is the tables' way over PCIe: the dense rows of W
+// were copied to the host to count their entries (564 MB, 158 ms a call, for
+// 141,000 out-of-core words at K = 1,000), and rows were walked by one host
+// thread.
+
+__global__ void k_gather_z16(const uint32_t *__restrict__ dt_wpos, const uint32_t *__restrict__ dt_key,
+                             const uint16_t *__restrict__ z_w, int64_t n, uint16_t *__restrict__ z_out) {
+  for (int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n; p += int64_t(gridDim.x) * blockDim.x)
+    z_out[dt_key ? dt_key[p] : uint32_t(p)] = z_w[dt_wpos[p]];
+}
+
+__device__ __forceinline__ unsigned long long wave_total(unsigned long long v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+__global__ __launch_bounds__(kThreads) void k_sum_nnz(DevState d, Params p, int D, int W,
+                                                      unsigned long long *__restrict__ out) {
+  const int64_t i0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x, step = int64_t(gridDim.x) * blockDim.x;
+  unsigned long long nd = 0, nw = 0;
+  if (D)
+    for (int64_t q = i0; q < p.M; q += step) nd += d.d_ent[d.d_cap[q]] & 0xFFFFu;
+  if (W) {
+    // the dense table by 16 bytes (its base is 256-byte aligned), then its last values
+    const int64_t total = int64_t(p.n_dense) * p.K, quads = total / 4;
+    const int4 *w4 = reinterpret_cast<const int4 *>(d.w_dense);
+    for (int64_t q = i0; q < quads; q += step) {
+      const int4 v = w4[q];
+      nw += uint32_t(v.x != 0) + uint32_t(v.y != 0) + uint32_t(v.z != 0) + uint32_t(v.w != 0);
+    }
+    if (quads * 4 + i0 < total) nw += d.w_dense[quads * 4 + i0] != 0;
+    for (int64_t q = i0; q < p.n_present - p.n_dense; q += step) nw += d.ws_nnz[q];
+  }
+  nd = wave_total(nd);
+  nw = wave_total(nw);
+  if ((threadIdx.x & 63) == 0) {
+    if (nd) atomicAdd(&out[0], nd);
+    if (nw) atomicAdd(&out[1], nw);
+  }
+}
+
+__global__ void k_doc_nnz(DevState d, int64_t doc0, int64_t n, uint32_t *__restrict__ num) {
+  for (int64_t q = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; q < n; q += int64_t(gridDim.x) * blockDim.x)
+    num[q] = d.d_ent[d.d_cap[doc0 + q]] & 0xFFFFu;
+}
+
+// One wave per word.
+__global__ __launch_bounds__(kThreads) void k_word_nnz(DevState d, Params p, uint32_t *__restrict__ num) {
+  const int lane = threadIdx.x & 63;
+  for (int64_t r = int64_t(blockIdx.x) * (kThreads / 64) + threadIdx.x / 64; r < p.n_present;
+       r += int64_t(gridDim.x) * (kThreads / 64)) {
+    if (r >= p.n_dense) {
+      if (lane == 0) num[r] = d.ws_nnz[r - p.n_dense];
+      continue;
+    }
+    const int32_t *row = d.w_dense + size_t(r) * size_t(p.K);
+    uint32_t c = 0;
+    for (int k = lane; k < p.K; k += 64) c += row[k] != 0;
+    c = uint32_t(wave_total(c));
+    if (lane == 0) num[r] = c;
+  }
+}
+
+// 16 lanes per document.
+__global__ void k_export_d(DevState d, int64_t doc0, int64_t n, const uint32_t *__restrict__ off,
+                           uint32_t *__restrict__ out) {
+  const int li = threadIdx.x & 15;
+  for (int64_t q = int64_t(blockIdx.x) * (kThreads / 16) + threadIdx.x / 16; q < n;
+       q += int64_t(gridDim.x) * (kThreads / 16)) {
+    const uint32_t *row = d.d_ent + d.d_cap[doc0 + q];
+    const uint32_t m = row[0] & 0xFFFFu, o = off[q];
+    for (uint32_t i = uint32_t(li); i < m; i += 16u) out[o + i] = row[1u + i];
+  }
+}
+
+// One wave per word: a dense row's nonzero counts compacted by ballot, a
+// sparse row's entries unpacked.
+__global__ __launch_bounds__(kThreads) void k_export_w(DevState d, Params p, const uint32_t *__restrict__ row,
+                                                       const uint32_t *__restrict__ off, int64_t n,
+                                                       uint2 *__restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  for (int64_t i = int64_t(blockIdx.x) * (kThreads / 64) + threadIdx.x / 64; i < n;
+       i += int64_t(gridDim.x) * (kThreads / 64)) {
+    const uint32_t r = row[i];
+    uint32_t o = off[i];
+    if (r < uint32_t(p.n_dense)) {
+      const int32_t *w = d.w_dense + size_t(r) * size_t(p.K);
+      for (int k0 = 0; k0 < p.K; k0 += 64) {
+        const int k = k0 + lane;
+        const int32_t c = k < p.K ? w[k] : 0;
+        const unsigned long long m = __ballot(c != 0);
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
+        if (c != 0) out[o + rank] = make_uint2(uint32_t(k), uint32_t(c));
+        o += uint32_t(__popcll(m));
+      }
+    } else {
+      const uint32_t s = r - uint32_t(p.n_dense), m = d.ws_nnz[s];
+      const uint32_t *e = d.ws_ent + d.ws_cap[s];
+      for (uint32_t q = uint32_t(lane); q < m; q += 64u) out[o + q] = make_uint2(e[q] >> 16, e[q] & 0xFFFFu);
+    }
+  }
 }
 
 }  // namespace
@@ -160,8 +254,38 @@ hipError_t launch_inflate(const uint32_t *region, int64_t n_regions, const uint3
   return hipGetLastError();
 }
 
-hipError_t launch_doc_gather_z(const uint32_t *dt_wpos, const uint16_t *z_w, int64_t n, int32_t *z_doc, hipStream_t s) {
-  hipLaunchKernelGGL(k_doc_gather_z, dim3(grid_for(n)), dim3(kThreads), 0, s, dt_wpos, z_w, n, z_doc);
+hipError_t launch_sum_nnz(const DevState &d, const Params &p, bool D, bool W, unsigned long long *out, hipStream_t s) {
+  const int64_t work = std::max<int64_t>(D ? p.M : 0, W ? std::max<int64_t>(int64_t(p.n_dense) * p.K / 16, p.n_present) : 0);
+  const uint32_t grid = std::min(grid_for(work), 2048u);
+  hipLaunchKernelGGL(k_sum_nnz, dim3(grid), dim3(kThreads), 0, s, d, p, D ? 1 : 0, W ? 1 : 0, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather_z16(const uint32_t *dt_wpos, const uint32_t *dt_key, const uint16_t *z_w, int64_t n,
+                             uint16_t *z_out, hipStream_t s) {
+  hipLaunchKernelGGL(k_gather_z16, dim3(grid_for(n)), dim3(kThreads), 0, s, dt_wpos, dt_key, z_w, n, z_out);
+  return hipGetLastError();
+}
+
+hipError_t launch_doc_nnz(const DevState &d, int64_t doc0, int64_t n, uint32_t *num, hipStream_t s) {
+  hipLaunchKernelGGL(k_doc_nnz, dim3(grid_for(n)), dim3(kThreads), 0, s, d, doc0, n, num);
+  return hipGetLastError();
+}
+
+hipError_t launch_word_nnz(const DevState &d, const Params &p, uint32_t *num, hipStream_t s) {
+  hipLaunchKernelGGL(k_word_nnz, dim3(grid_for(int64_t(p.n_present) * 64)), dim3(kThreads), 0, s, d, p, num);
+  return hipGetLastError();
+}
+
+hipError_t launch_export_d(const DevState &d, int64_t doc0, int64_t n, const uint32_t *off, uint32_t *out,
+                           hipStream_t s) {
+  hipLaunchKernelGGL(k_export_d, dim3(grid_for(n * 16)), dim3(kThreads), 0, s, d, doc0, n, off, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_export_w(const DevState &d, const Params &p, const uint32_t *row, const uint32_t *off, int64_t n,
+                           uint2 *out, hipStream_t s) {
+  hipLaunchKernelGGL(k_export_w, dim3(grid_for(n * 64)), dim3(kThreads), 0, s, d, p, row, off, n, out);
   return hipGetLastError();
 }
 
@@ -202,11 +326,6 @@ hipError_t launch_word_order(const uint32_t *wkey, const uint32_t *wpos, int64_t
                              const uint32_t *d_cap, uint2 *wt_kr, hipStream_t s) {
   hipLaunchKernelGGL(k_word_order, dim3(grid_for(n)), dim3(kThreads), 0, s, wkey, wpos, n, relabel, woff_orig,
                      woff_new, doc_sorted, doc_in, dt_key, dt_word, dt_wpos, d_cap, wt_kr);
-  return hipGetLastError();
-}
-
-hipError_t launch_scatter_z(const uint16_t *z_w, const uint2 *wt_kr, int64_t n, int32_t *z_in, hipStream_t s) {
-  hipLaunchKernelGGL(k_scatter_z, dim3(grid_for(n)), dim3(kThreads), 0, s, z_w, wt_kr, n, z_in);
   return hipGetLastError();
 }
 

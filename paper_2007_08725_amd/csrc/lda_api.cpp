@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "handle.h"
+#include "readback.h"
 
 using namespace lda;
 
@@ -47,6 +48,7 @@ lda_status setup_device(lda_handle *h, const lda_options *o) {
   HIP_TRY(h, hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking));
   HIP_TRY(h, hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming));
   HIP_TRY(h, hipEventCreateWithFlags(&h->join_ev, hipEventDisableTiming));
+  LDA_TRY(dalloc(h, &h->nnz, 2));
   // the fixed scratch of the allocation-free LLPT, looked up once per device
   HIP_TRY(h, noalloc_scratch_address(&h->noalloc_scratch));
   Params &p = h->p;
@@ -283,12 +285,61 @@ void release(lda_handle *h) {
   if (h->side) (void)hipStreamDestroy(h->side);
   for (hipEvent_t ev : h->events)
     if (ev) (void)hipEventDestroy(ev);
+  for (hipEvent_t ev : h->stage_ev)
+    if (ev) (void)hipEventDestroy(ev);
+  for (void *st : h->stage)
+    if (st) (void)hipHostFree(st);
   for (void *ptr : h->allocations) {
     if (h->dev_alloc) h->dev_free(ptr, h->alloc_ctx);
     else (void)hipFree(ptr);
   }
   if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
   delete h;
+}
+
+lda_status resident_counts(lda_handle *h, lda_counts *out) {
+  const Layout &L = h->L;
+  const size_t n = size_t(L.n);
+  const int32_t K = L.K;
+  unsigned long long nnz[2] = {0, 0};
+  HIP_TRY(h, hipMemsetAsync(h->nnz, 0, sizeof(nnz), h->stream));
+  HIP_TRY(h, launch_sum_nnz(h->d, h->p, true, true, h->nnz, h->stream));
+  HIP_TRY(h, hipMemcpyAsync(nnz, h->nnz, sizeof(nnz), hipMemcpyDeviceToHost, h->stream));
+  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  out->iteration = h->iteration;
+  out->M = L.M;
+  out->V = L.V;
+  out->K = K;
+  out->n_tokens = L.n;
+  out->nnz_D = int64_t(nnz[0]);
+  out->nnz_W = int64_t(nnz[1]);
+  if (!out->z && !out->T && !out->D_off && !out->D_topic && !out->D_count && !out->W_off && !out->W_topic &&
+      !out->W_count)
+    return LDA_OK;  // size query
+  Crew crew(read_threads(std::max({out->z ? 2 * n : 0, out->D_topic ? size_t(nnz[0]) * 4 : 0,
+                                   out->W_topic ? size_t(nnz[1]) * 8 : 0})));
+  if (out->z) {
+    uint16_t *zin = nullptr;
+    LDA_TRY(dalloc(h, &zin, n));
+    HIP_TRY(h, launch_gather_z16(h->d.dt_wpos, h->d.dt_key, h->d.z_w, L.n, zin, h->stream));
+    LDA_TRY(read_z(h, crew, zin, n, out->z));
+    dfree(h, zin);
+  }
+  if (out->T) {
+    std::vector<uint32_t> tk(static_cast<size_t>(K));
+    HIP_TRY(h, hipMemcpy(tk.data(), h->d.T, size_t(K) * 4, hipMemcpyDeviceToHost));
+    for (int32_t k = 0; k < K; ++k) out->T[k] = tk[size_t(k)];
+  }
+  if (out->D_off || out->D_topic || out->D_count) {
+    if (!out->D_off || !out->D_topic || !out->D_count) return fail(h, LDA_E_ARG, "D arrays must be given together");
+    int64_t entries = 0;
+    LDA_TRY(export_d(h, crew, h->d, L.M, 0, out->D_off, out->D_topic, out->D_count, &entries));
+  }
+  if (out->W_off || out->W_topic || out->W_count) {
+    if (!out->W_off || !out->W_topic || !out->W_count) return fail(h, LDA_E_ARG, "W arrays must be given together");
+    LDA_TRY(export_w(h, crew, h->d, h->p, out->W_off, out->W_topic, out->W_count));
+  }
+  return LDA_OK;
 }
 
 }  // namespace
@@ -454,97 +505,11 @@ lda_status lda_iterate(lda_handle *h, int32_t n_iters, lda_iter_stats *stats) {
 lda_status lda_get_counts(lda_handle *h, lda_counts *out) {
   LDA_TRY(check_handle(h));
   if (!out) return fail(h, LDA_E_ARG, "out is NULL");
-  if (h->chunks) return chunked_counts(h, out);
-  const Layout &L = h->L;
-  const size_t n = size_t(L.n);
-  const int32_t K = L.K;
-  std::vector<uint32_t> ws_nnz(L.ws_cap.size() - 1);
-  unsigned long long *nnz_dev = nullptr;
-  LDA_TRY(dalloc(h, &nnz_dev, 1));
-  HIP_TRY(h, hipMemsetAsync(nnz_dev, 0, sizeof(unsigned long long), h->stream));
-  HIP_TRY(h, launch_sum_nnz(h->d, h->p, nnz_dev, h->stream));
-  unsigned long long nnz_D_dev = 0;
-  HIP_TRY(h, hipMemcpyAsync(&nnz_D_dev, nnz_dev, sizeof(nnz_D_dev), hipMemcpyDeviceToHost, h->stream));
-  if (!ws_nnz.empty())
-    HIP_TRY(h, hipMemcpyAsync(ws_nnz.data(), h->d.ws_nnz, ws_nnz.size() * 4, hipMemcpyDeviceToHost, h->stream));
-  std::vector<int32_t> wd(static_cast<size_t>(L.n_dense) * static_cast<size_t>(K));
-  if (!wd.empty())
-    HIP_TRY(h, hipMemcpyAsync(wd.data(), h->d.w_dense, wd.size() * 4, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
-  dfree(h, nnz_dev);
-  int64_t nnz_D = int64_t(nnz_D_dev), nnz_W = 0;
-  for (uint32_t x : ws_nnz) nnz_W += x;
-  for (int32_t x : wd) nnz_W += x != 0;
-  out->iteration = h->iteration;
-  out->M = L.M;
-  out->V = L.V;
-  out->K = K;
-  out->n_tokens = L.n;
-  out->nnz_D = nnz_D;
-  out->nnz_W = nnz_W;
-  if (!out->z && !out->T && !out->D_off && !out->D_topic && !out->D_count && !out->W_off && !out->W_topic &&
-      !out->W_count)
-    return LDA_OK;  // size query
-  if (out->z) {
-    int32_t *zin = nullptr;
-    LDA_TRY(dalloc(h, &zin, n));
-    HIP_TRY(h, launch_scatter_z(h->d.z_w, h->d.wt_kr, L.n, zin, h->stream));
-    HIP_TRY(h, hipMemcpyAsync(out->z, zin, n * 4, hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
-    dfree(h, zin);
+  try {
+    return h->chunks ? chunked_counts(h, out) : resident_counts(h, out);
+  } catch (const std::bad_alloc &) {
+    return fail(h, LDA_E_NOMEM, "host allocation failed");
   }
-  if (out->T) {
-    std::vector<uint32_t> tk(static_cast<size_t>(K));
-    HIP_TRY(h, hipMemcpy(tk.data(), h->d.T, size_t(K) * 4, hipMemcpyDeviceToHost));
-    for (int32_t k = 0; k < K; ++k) out->T[k] = tk[size_t(k)];
-  }
-  if (out->D_off || out->D_topic || out->D_count) {
-    if (!out->D_off || !out->D_topic || !out->D_count) return fail(h, LDA_E_ARG, "D arrays must be given together");
-    std::vector<uint32_t> ent(static_cast<size_t>(L.d_cap.back()));
-    if (!ent.empty()) HIP_TRY(h, hipMemcpy(ent.data(), h->d.d_ent, ent.size() * 4, hipMemcpyDeviceToHost));
-    int64_t o = 0;
-    for (int32_t dd = 0; dd < L.M; ++dd) {
-      out->D_off[dd] = o;
-      const uint32_t hdr = ent[size_t(L.d_cap[size_t(dd)])];
-      for (uint32_t q = 0; q < (hdr & 0xFFFFu); ++q) {
-        const uint32_t e = ent[size_t(L.d_cap[size_t(dd)]) + 1 + q];
-        out->D_topic[o] = int32_t(e >> 16);
-        out->D_count[o] = int32_t(e & 0xFFFFu);
-        ++o;
-      }
-    }
-    out->D_off[L.M] = o;
-  }
-  if (out->W_off || out->W_topic || out->W_count) {
-    if (!out->W_off || !out->W_topic || !out->W_count) return fail(h, LDA_E_ARG, "W arrays must be given together");
-    std::vector<uint32_t> went(static_cast<size_t>(L.ws_cap.back()));
-    if (!went.empty()) HIP_TRY(h, hipMemcpy(went.data(), h->d.ws_ent, went.size() * 4, hipMemcpyDeviceToHost));
-    int64_t o = 0;
-    for (int32_t v = 0; v < L.V; ++v) {
-      out->W_off[v] = o;
-      const int32_t r = L.relabel[size_t(v)];
-      if (r >= L.n_present) continue;
-      if (r < L.n_dense) {
-        const int32_t *row = &wd[size_t(r) * size_t(K)];
-        for (int32_t k = 0; k < K; ++k)
-          if (row[k]) {
-            out->W_topic[o] = k;
-            out->W_count[o] = row[k];
-            ++o;
-          }
-      } else {
-        const size_t s = size_t(r - L.n_dense);
-        for (uint32_t q = 0; q < ws_nnz[s]; ++q) {
-          const uint32_t e = went[size_t(L.ws_cap[s]) + q];
-          out->W_topic[o] = int32_t(e >> 16);
-          out->W_count[o] = int32_t(e & 0xFFFFu);
-          ++o;
-        }
-      }
-    }
-    out->W_off[L.V] = o;
-  }
-  return LDA_OK;
 }
 
 lda_status lda_loglik(lda_handle *h, double *llpt) {

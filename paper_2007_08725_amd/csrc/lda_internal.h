@@ -99,18 +99,16 @@ hipError_t launch_word_order(const uint32_t *wkey, const uint32_t *wpos, int64_t
                              const uint32_t *woff_orig, const uint32_t *woff_new, const uint32_t *doc_sorted,
                              const int32_t *doc_in, const uint32_t *dt_key, uint32_t *dt_word, uint32_t *dt_wpos,
                              const uint32_t *d_cap, uint2 *wt_kr, hipStream_t s);
-hipError_t launch_scatter_z(const uint16_t *z_w, const uint2 *wt_kr, int64_t n, int32_t *z_in, hipStream_t s);
 hipError_t launch_gather_z(const int32_t *z_in, const uint2 *wt_kr, int64_t n, int32_t K, uint16_t *z_w,
                            unsigned long long *bad, hipStream_t s);
 // Out-of-core chunks: the word-order slot of each doc-order position from the
 // positions listed in word order; the per-token arrays derived from dt_wpos
-// and the chunk's regions and document tables; topics between doc order
-// (int32) and word order.
+// and the chunk's regions and document tables; topics from doc order
+// (int32) to word order.
 hipError_t launch_invert(const uint32_t *wpos, int64_t n, uint32_t *dt_wpos, hipStream_t s);
 hipError_t launch_inflate(const uint32_t *region, int64_t n_regions, const uint32_t *doc_off, const uint32_t *d_cap,
                           int32_t M, const uint32_t *dt_wpos, uint32_t key_base, uint32_t *dt_word, uint2 *wt_kr,
                           hipStream_t s);
-hipError_t launch_doc_gather_z(const uint32_t *dt_wpos, const uint16_t *z_w, int64_t n, int32_t *z_doc, hipStream_t s);
 hipError_t launch_doc_scatter_z(const int32_t *z_doc, const uint32_t *dt_wpos, int64_t n, int32_t K, uint16_t *z_w,
                                 unsigned long long *bad, hipStream_t s);
 
@@ -321,6 +319,19 @@ static_assert(sizeof(uint32_t) * kCounters + sizeof(unsigned long long) * kStats
               "counters and statistics overlap the result");
 hipError_t noalloc_scratch_address(void **out);
 hipError_t launch_loglik_noalloc(DevState d, const Params &p, void *scratch_dev, hipStream_t s);
-hipError_t launch_sum_nnz(const DevState &d, const Params &p, unsigned long long *out, hipStream_t s);
+// Exports of lda_get_counts.  out[0] += entries of the D rows, out[1] +=
+// entries of W (either may be left out); the topics in doc order or, with
+// dt_key (input not sorted by document), in input order; entries per document
+// and per relabelled word; D entries and W (topic, count) pairs of a slab of
+// rows compacted at off[] (relative to the slab).
+hipError_t launch_sum_nnz(const DevState &d, const Params &p, bool D, bool W, unsigned long long *out, hipStream_t s);
+hipError_t launch_gather_z16(const uint32_t *dt_wpos, const uint32_t *dt_key, const uint16_t *z_w, int64_t n,
+                             uint16_t *z_out, hipStream_t s);
+hipError_t launch_doc_nnz(const DevState &d, int64_t doc0, int64_t n, uint32_t *num, hipStream_t s);
+hipError_t launch_word_nnz(const DevState &d, const Params &p, uint32_t *num, hipStream_t s);
+hipError_t launch_export_d(const DevState &d, int64_t doc0, int64_t n, const uint32_t *off, uint32_t *out,
+                           hipStream_t s);
+hipError_t launch_export_w(const DevState &d, const Params &p, const uint32_t *row, const uint32_t *off, int64_t n,
+                           uint2 *out, hipStream_t s);
 
 }  // namespace lda
