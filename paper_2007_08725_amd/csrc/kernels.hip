@@ -921,6 +921,8 @@ __device__ __forceinline__ uint32_t pick_segment(uint32_t k, double term, double
 // the first one also draws them from the sums it holds, reading at most the
 // one chunk that holds each x.  Every draw is the one the token would get on
 // its own, bit for bit.
+// Sum: no draw; bt.u of every token gets the sum of its row's terms.
+template <bool Sum>
 __device__ void draw_long(unsigned long long mask, unsigned long long foll, unsigned long long starts,
                           const BatchLds &bt, const WordState &w, const uint32_t *__restrict__ d_ent, int grp, int li,
                           unsigned long long &after_s) {
@@ -948,13 +950,22 @@ __device__ void draw_long(unsigned long long mask, unsigned long long foll, unsi
     for (uint32_t ch = 0; ch < nch; ++ch) {
       load_run<R>(row + ch * kChunk, li, r);
       if (ch == 0u && li == 0) r[0] = pad;
-      c1 = run_count_of<R>(r, w.K1, c1);
+      if (!Sum) c1 = run_count_of<R>(r, w.K1, c1);
       s = run_sum<R>(r, w.wh);
       incl = row_incl_scan(s);
       const double tch = __shfl(incl, kGroup - 1, kGroup);
       S += tch;
       tot = uint32_t(li) == ch ? tch : tot;
     }
+    // the run's later tokens: lanes after src up to the next run start
+    const unsigned long long after = ~((2ull << src) - 1ull);  // the lanes above src
+    const unsigned long long nxt = starts & after;
+    unsigned long long fl = foll & after & (nxt ? (nxt & (0ull - nxt)) - 1ull : ~0ull);
+    if constexpr (Sum) {
+      if (li == 0) bt.u[src] = S;
+      for (; fl; fl &= fl - 1ull)
+        if (li == 0) bt.u[__ffsll((long long)fl) - 1] = S;
+    } else {
     // max-topic branch, Eq. 7: M = W^[v][K1] * (D[d][K1] + alpha)
     const double Mm = w.a1 * (double(row_sum_u32(c1 <= 0xFFFFu ? c1 : 0u)) + w.alpha);
     // with the totals kept in the lanes: lane c's chunk base
@@ -1039,10 +1050,6 @@ __device__ void draw_long(unsigned long long mask, unsigned long long foll, unsi
     };
     const uint32_t topic = draw_x(bt.u[src] * ((Mm + S) + w.qp));
     if (li == 0) bt.top[src] = uint16_t(topic);
-    // the run's later tokens: lanes after src up to the next run start
-    const unsigned long long after = ~((2ull << src) - 1ull);  // the lanes above src
-    const unsigned long long nxt = starts & after;
-    unsigned long long fl = foll & after & (nxt ? (nxt & (0ull - nxt)) - 1ull : ~0ull);
     while (fl) {
       const int f = __ffsll((long long)fl) - 1;
       fl &= fl - 1ull;
@@ -1050,8 +1057,9 @@ __device__ void draw_long(unsigned long long mask, unsigned long long foll, unsi
       if (li == 0) bt.top[f] = uint16_t(tf);
     }
     }
+    }
     // outside the divergent part, so the count stays wave-uniform
-    after_s += wave_sum_u32(li == 0 ? n_m : 0u);
+    if (!Sum) after_s += wave_sum_u32(li == 0 ? n_m : 0u);
   }
 }
 
@@ -1238,7 +1246,8 @@ __device__ __forceinline__ uint32_t finish_draw(int q, const BatchLds &bt, const
 // entries, lane l holding entries [l*kRun, l*kRun + kRun) of each chunk (the
 // group's loads of a chunk share cache lines); NC is the largest chunk count
 // in the round, and a group whose row has fewer chunks skips the rest.
-template <int G, int NC>
+// Sum: no draw; bt.u of the token gets the sum of its row's terms.
+template <int G, int NC, bool Sum>
 __device__ void draw_small(const BatchLds &bt, int slot, int n, const WordState &w,
                            const uint32_t *__restrict__ d_ent, int li, unsigned long long &after_s) {
   constexpr uint32_t kSpan = uint32_t(G) * kRun;  // entries per chunk
@@ -1265,7 +1274,7 @@ __device__ void draw_small(const BatchLds &bt, int slot, int n, const WordState 
     for (int c = 0; c < NC; ++c) {
       s[c] = 0.0;
       if (uint32_t(c) < nc) {
-        c1 = run_count_of<kRun>(r[c], w.K1, c1);
+        if (!Sum) c1 = run_count_of<kRun>(r[c], w.K1, c1);
         s[c] = run_sum<kRun>(r[c], w.wh);
       }
     }
@@ -1275,6 +1284,10 @@ __device__ void draw_small(const BatchLds &bt, int slot, int n, const WordState 
     for (int c = 0; c < NC; ++c) {
       S += gsum<G>(s[c]);
       T[c] = S;
+    }
+    if constexpr (Sum) {
+      if (li == 0) bt.u[src] = S;
+      return;
     }
     c1 = gmin_u32<G>(c1);
     // max-topic branch, Eq. 7: M = W^[v][K1] * (D[d][K1] + alpha)
@@ -1312,7 +1325,7 @@ __device__ void draw_small(const BatchLds &bt, int slot, int n, const WordState 
     if (in_m && li == 0) bt.top[src] = uint16_t(w.K1);
   }
   // outside the divergent part, so the count stays wave-uniform
-  after_s += uint32_t(__popcll(__ballot(in_m && li == 0)));
+  if (!Sum) after_s += uint32_t(__popcll(__ballot(in_m && li == 0)));
 }
 
 // Row-length buckets of a batch (slots, header included): upper bounds.
@@ -1322,7 +1335,7 @@ __device__ constexpr uint32_t kBucketEnd[8] = {32, 64, 96, 128, 192, 256, 384, 5
 // The small-group rounds over list places [from, to) (rows in ascending
 // bucket order), G lanes per token and 64/G tokens a round.  A round reads
 // as many chunks of G*kRun slots as its last (longest) row needs.
-template <int G, int MaxNC>
+template <int G, int MaxNC, bool Sum>
 __device__ void draw_rounds(int from, int to, const int (&ends)[8], const BatchLds &bt, const WordState &w,
                             const uint32_t *__restrict__ d_ent, unsigned long long &after_s) {
   constexpr uint32_t kSpan = uint32_t(G) * kRun;
@@ -1335,17 +1348,17 @@ __device__ void draw_rounds(int from, int to, const int (&ends)[8], const BatchL
     const uint32_t nc = (upper + kSpan - 1) / kSpan;
     const int slot = base + g;
     if (nc <= 1) {
-      draw_small<G, 1>(bt, slot, to, w, d_ent, li, after_s);
+      draw_small<G, 1, Sum>(bt, slot, to, w, d_ent, li, after_s);
     } else if (nc == 2) {
-      draw_small<G, 2>(bt, slot, to, w, d_ent, li, after_s);
+      draw_small<G, 2, Sum>(bt, slot, to, w, d_ent, li, after_s);
     } else if (nc == 3) {
-      draw_small<G, 3>(bt, slot, to, w, d_ent, li, after_s);
+      draw_small<G, 3, Sum>(bt, slot, to, w, d_ent, li, after_s);
     } else if (MaxNC <= 4 || nc == 4) {
-      draw_small<G, 4>(bt, slot, to, w, d_ent, li, after_s);
+      draw_small<G, 4, Sum>(bt, slot, to, w, d_ent, li, after_s);
     } else {
       if constexpr (MaxNC > 4) {
-        if (nc <= 6) draw_small<G, 6>(bt, slot, to, w, d_ent, li, after_s);
-        else draw_small<G, MaxNC>(bt, slot, to, w, d_ent, li, after_s);
+        if (nc <= 6) draw_small<G, 6, Sum>(bt, slot, to, w, d_ent, li, after_s);
+        else draw_small<G, MaxNC, Sum>(bt, slot, to, w, d_ent, li, after_s);
       }
     }
   }
@@ -1362,7 +1375,7 @@ __device__ void draw_rounds(int from, int to, const int (&ends)[8], const BatchL
 // rows of up to 512 slots by 8 lanes as well, 8 tokens a round, so that a
 // round's per-token work (sums, scans, the split of x) serves twice the
 // tokens.
-template <bool Wide>
+template <bool Wide, bool Sum = false>
 __device__ void draw_batch_small(bool und, uint32_t nnz, const BatchLds &bt, const WordState &w,
                                  const uint32_t *__restrict__ d_ent, int lane, unsigned long long &after_s) {
   int n = 0, ends[8];
@@ -1379,12 +1392,12 @@ __device__ void draw_batch_small(bool und, uint32_t nnz, const BatchLds &bt, con
   }
   const int left = ends[3] % 16;
   const int a = left > 0 && left <= 8 && ends[3] - ends[2] >= left ? ends[3] - left : ends[3];
-  draw_rounds<4, 4>(0, a, ends, bt, w, d_ent, after_s);
+  draw_rounds<4, 4, Sum>(0, a, ends, bt, w, d_ent, after_s);
   if (Wide) {
-    draw_rounds<8, 8>(a, ends[7], ends, bt, w, d_ent, after_s);
+    draw_rounds<8, 8, Sum>(a, ends[7], ends, bt, w, d_ent, after_s);
   } else {
-    draw_rounds<8, 4>(a, ends[5], ends, bt, w, d_ent, after_s);
-    draw_rounds<16, 4>(ends[5], ends[7], ends, bt, w, d_ent, after_s);
+    draw_rounds<8, 4, Sum>(a, ends[5], ends, bt, w, d_ent, after_s);
+    draw_rounds<16, 4, Sum>(ends[5], ends[7], ends, bt, w, d_ent, after_s);
   }
 }
 
@@ -1397,7 +1410,9 @@ __device__ void draw_batch_small(bool und, uint32_t nnz, const BatchLds &bt, con
 // (header and entries): 4 lanes per token; up to 256: 8 lanes; up to 512: 16
 // lanes; longer rows: 16 lanes, one chunk of kChunk slots at a time; then the
 // S' walks and Q' searches, one lane per token.
-template <bool Wide>
+// Sum: no draws; bt.u of every such lane gets the sum of its row's terms
+// D[d][k] * W^[v][k] instead (w.wh with all of W^[v]).
+template <bool Wide, bool Sum = false>
 __device__ __forceinline__ uint32_t draw_tokens(bool und, uint32_t off, uint32_t nnz, int first, int ln,
                                                 const BatchLds &bt, const WordState &w,
                                                 const uint32_t *__restrict__ d_ent, unsigned long long &after_s,
@@ -1413,8 +1428,9 @@ __device__ __forceinline__ uint32_t draw_tokens(bool und, uint32_t off, uint32_t
     fol = ((lmask >> ln) & 1ull) && (lmask & below & (~0ull << rs)) != 0ull;
   }
   *nnz_read = und ? (fol ? min(nnz, uint32_t(kChunk)) : nnz) : 0u;  // a follower reads one chunk of its row
-  draw_batch_small<Wide>(und, nnz, bt, w, d_ent, ln, after_s);
-  if (lmask) draw_long(lmask, __ballot(fol), starts, bt, w, d_ent, ln / kGroup, ln % kGroup, after_s);
+  draw_batch_small<Wide, Sum>(und, nnz, bt, w, d_ent, ln, after_s);
+  if (lmask) draw_long<Sum>(lmask, __ballot(fol), starts, bt, w, d_ent, ln / kGroup, ln % kGroup, after_s);
+  if (Sum) return 0u;
   return und ? finish_draw(ln, bt, w, d_ent) : 0u;
 }
 
@@ -3000,86 +3016,309 @@ __global__ __launch_bounds__(kBlock) void k_rebuild_d_sort(DevState d, Params p)
   if (bad) atomicAdd(&d.stats[ST_ERRORS], (unsigned long long)bad);
 }
 
-// LLPT terms per region (Sec. 2.2): for every token,
+// LLPT terms (Sec. 2.2): for every token,
 //   log2( (sum_{k in nz(D[d])} D[d][k] W^[v][k] + alpha * sum_k W^[v][k]) / (len(d) + K alpha) ),
-// summed in a fixed order so that the result does not depend on the schedule.
-__global__ __launch_bounds__(kBlock) void k_loglik(DevState d, Params p) {
+// summed per region (per batch of light regions) in an order that the layout
+// fixes, so that the result does not depend on the schedule.
+//
+// The work is the sampler's S' pass without the draws, and it is organised the
+// same way: batches of 64 tokens per wave, rows in registers by groups of 4, 8
+// or 16 lanes, then one lane per token for the logarithm.  A 16-lane loop per
+// token, 4 waves per CU from K = 10,000 on and the rows in global memory at
+// K = 32,768 took 18.6 ms for 144M tokens at K = 1,000, 25.6 ms for 33M at
+// 10,000 and 74.3 ms for 20M at 32,768; these take 5.9, 6.7 and 10.5 ms.
+__device__ __forceinline__ double llpt_term(double s, double asw, uint32_t len, double Kalpha) {
+  return log2((s + asw) / (double(len) + Kalpha));
+}
+
+template <int NB>
+__device__ __forceinline__ void loglik_body(DevState d, Params p) {
   extern __shared__ double lds[];
   const int K = p.K;
-  // large K: the row lives in the workgroup's slice of global scratch
-  double *wh = p.big_k ? d.wscratch + size_t(blockIdx.x) * size_t(K) : lds;
-  __shared__ uint32_t s_reg[3];
-  __shared__ int s_valid;
-  __shared__ uint32_t s_r;
-  __shared__ double s_part[kBlock / kGroup];
+  double *wh = lds;                     // [wh_entries(K)]: W^ of the region's word, zeros past K
+  double *s_u = lds + wh_entries(K);    // [NB]
+  double *s_part = s_u + NB;            // [NB / kWave]
+  uint32_t *s_off = reinterpret_cast<uint32_t *>(s_part + NB / kWave);
+  uint32_t *s_nnz = s_off + NB;
+  uint32_t *s_reg = s_nnz + NB;         // [4]: the region's index (or past the end), word, begin, end
+  uint8_t *s_list = reinterpret_cast<uint8_t *>(s_reg + 4);
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
-  const int gid = tid / kGroup, li = lane % kGroup;  // 16 groups per block
-  uint32_t cur = 0xFFFFFFFFu;
-  double sumw = 0.0;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const BatchLds bt{s_off + wave * kWave, s_nnz + wave * kWave, s_u + wave * kWave, nullptr, nullptr,
+                    s_list + wave * kWave};
   const double Kalpha = double(K) * p.alpha;
+  for (int k = K + tid; k < wh_entries(K); k += NB) wh[k] = 0.0;
+  uint32_t cur = 0xFFFFFFFFu;
+  double asw = 0.0;
+  const uint32_t *held = nullptr;  // as in the sampler: the sparse word whose row wh holds
+  uint32_t held_nnz = 0;
   for (;;) {
     if (tid == 0) {
       const uint32_t r = atomicAdd(&d.counters[CNT_LOGLIK], 1u);
-      s_r = r;
-      s_valid = int64_t(r) < p.n_regions;
-      if (s_valid) {
-        s_reg[0] = d.region[3 * size_t(r)];
-        s_reg[1] = d.region[3 * size_t(r) + 1];
-        s_reg[2] = d.region[3 * size_t(r) + 2];
+      s_reg[0] = r;
+      if (int64_t(r) < p.light_begin) {
+        s_reg[1] = d.region[3 * size_t(r)];
+        s_reg[2] = d.region[3 * size_t(r) + 1];
+        s_reg[3] = d.region[3 * size_t(r) + 2];
       }
     }
     __syncthreads();
-    if (!s_valid) break;
-    const uint32_t v = s_reg[0], b = s_reg[1], e = s_reg[2], r = s_r;
+    const uint32_t r = __builtin_amdgcn_readfirstlane(s_reg[0]);
+    if (int64_t(r) >= p.light_begin) break;
+    const uint32_t v = __builtin_amdgcn_readfirstlane(s_reg[1]);
+    const uint32_t b = __builtin_amdgcn_readfirstlane(s_reg[2]), e = __builtin_amdgcn_readfirstlane(s_reg[3]);
     if (v != cur) {
       cur = v;
-      sumw = d.wrec[v].sumw;
+      asw = p.alpha * d.wrec[v].sumw;
       if (int32_t(v) < p.n_dense) {
         const int32_t *wrow = d.w_dense + size_t(v) * size_t(K);
-        for (int k = tid; k < K; k += kBlock) wh[k] = what(uint32_t(wrow[k]), p.beta, d.den[k]);
+        for (int k = tid; k < K; k += NB) wh[k] = what(uint32_t(wrow[k]), p.beta, d.den[k]);
+        held = nullptr;
       } else {
         const int s = int(v) - p.n_dense;
         const uint32_t *ents = d.ws_ent + d.ws_cap[s];
         const uint32_t nnz = d.ws_nnz[s];
-        for (int k = tid; k < K; k += kBlock) wh[k] = d.bden[k];
+        if (held) {
+          for (uint32_t q = tid; q < held_nnz; q += NB) {
+            const uint32_t k = held[q] >> 16;
+            wh[k] = d.bden[k];
+          }
+        } else {
+          for (int k = tid; k < K; k += NB) wh[k] = d.bden[k];
+        }
         __syncthreads();
-        for (uint32_t q = tid; q < nnz; q += kBlock) {
+        for (uint32_t q = tid; q < nnz; q += NB) {
           const uint32_t ent = ents[q];
           wh[ent >> 16] = what(ent & 0xFFFFu, p.beta, d.den[ent >> 16]);
+        }
+        held = ents;
+        held_nnz = nnz;
+      }
+      __syncthreads();
+    }
+    const WordState w{wh, nullptr, 0, K, 0, 0u, 0.0, 0.0, p.alpha, nullptr, nullptr};
+    const uint32_t bsz = min(uint32_t(kWave), max(16u, ((e - b + uint32_t(NB / kWave) - 1u) / uint32_t(NB / kWave) + 15u) & ~15u));
+    double part = 0.0;  // this lane's tokens of the region
+    for (uint32_t base = b + uint32_t(wave) * bsz; base < e; base += uint32_t(NB / kWave) * bsz) {
+      const int ln = lane_here();
+      const uint32_t j = base + uint32_t(ln);
+      const bool in = j < min(e, base + bsz);
+      uint32_t off = 0, hdr = 0;
+      if (in) {
+        off = d.wt_kr[j].y;
+        hdr = d.d_ent[off];
+        bt.off[ln] = off;
+        bt.nnz[ln] = hdr & 0xFFFFu;
+      }
+      unsigned long long none = 0;
+      uint32_t nnz_read;
+      draw_tokens<(NB >= 1024), true>(in, off, hdr & 0xFFFFu, 0, ln, bt, w, d.d_ent, none, &nnz_read);
+      if (in) part += llpt_term(bt.u[ln], asw, hdr >> 16, Kalpha);
+    }
+    part = group_sum<kWave>(part);
+    if (lane == 0) s_part[wave] = part;
+    __syncthreads();
+    if (tid == 0) {
+      double s = 0.0;
+      for (int q = 0; q < NB / kWave; ++q) s += s_part[q];
+      d.ll_part[r] = s;
+    }
+    // s_reg and s_part are next written behind the barrier that follows the fetch, by then read
+    __syncthreads();
+  }
+}
+__global__ __launch_bounds__(256, 7) void k_loglik(DevState d, Params p) { loglik_body<256>(d, p); }
+__global__ __launch_bounds__(512, 4) void k_loglik_512(DevState d, Params p) { loglik_body<512>(d, p); }
+__global__ __launch_bounds__(1024, 4) void k_loglik_1024(DevState d, Params p) { loglik_body<1024>(d, p); }
+
+// The light regions, in the light sampler's batches, one wave each: partial
+// p.light_begin + i is batch i's.
+__global__ __launch_bounds__(64, 4) void k_loglik_light(DevState d, Params p) {
+  extern __shared__ double lds[];
+  const int K = p.K;
+  double *wh = lds;
+  double *s_u = lds + wh_entries(K);
+  uint32_t *s_off = reinterpret_cast<uint32_t *>(s_u + kWave);
+  uint32_t *s_nnz = s_off + kWave;
+  uint8_t *s_list = reinterpret_cast<uint8_t *>(s_nnz + kWave);
+  const BatchLds bt{s_off, s_nnz, s_u, nullptr, nullptr, s_list};
+  const int lane = threadIdx.x;
+  const double Kalpha = double(K) * p.alpha;
+  for (int k = K + lane; k < wh_entries(K); k += kWave) wh[k] = 0.0;
+  int held = -1;
+  uint32_t held_k = 0;
+  auto order = [&]() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+  for (uint32_t bi = blockIdx.x; bi < uint32_t(p.n_light_batches); bi += gridDim.x) {
+    const uint32_t r0 = __builtin_amdgcn_readfirstlane(d.light_batch[bi]);
+    const int nw = int(__builtin_amdgcn_readfirstlane(d.light_batch[bi + 1]) - r0);  // 1..64
+    const size_t rr = 3 * (size_t(p.light_begin) + r0 + uint32_t(min(lane, nw - 1)));
+    const uint32_t v_l = d.region[rr], b_l = d.region[rr + 1], e_l = d.region[rr + 2];
+    const uint32_t b0 = __builtin_amdgcn_readlane(b_l, 0), e0 = __builtin_amdgcn_readlane(e_l, nw - 1);
+    const int ln = lane_here();
+    const uint32_t j = b0 + uint32_t(ln);
+    const bool in = j < e0;
+    uint32_t off = 0, hdr = 0;
+    if (in) off = d.wt_kr[j].y;
+    const bool dense_l = int32_t(v_l) < p.n_dense;
+    const int s_l = dense_l ? 0 : int(v_l) - p.n_dense;
+    const uint32_t nnz_l = dense_l ? 0u : d.ws_nnz[s_l];
+    const uint32_t cap_l = dense_l ? 0u : d.ws_cap[s_l];
+    if (in) {
+      hdr = d.d_ent[off];
+      bt.off[ln] = off;
+      bt.nnz[ln] = hdr & 0xFFFFu;
+    }
+    auto entry_of = [&](int i) {
+      const uint32_t n = __builtin_amdgcn_readlane(nnz_l, i), c = __builtin_amdgcn_readlane(cap_l, i);
+      return uint32_t(lane) < n ? d.ws_ent[c + uint32_t(lane)] : 0u;
+    };
+    uint32_t ent_next = entry_of(0);
+    double part = 0.0;
+    for (int i = 0; i < nw; ++i) {
+      const uint32_t v = __builtin_amdgcn_readlane(v_l, i);
+      const uint32_t ent = ent_next;
+      if (i + 1 < nw) ent_next = entry_of(i + 1);
+      const int f = int(__builtin_amdgcn_readlane(b_l, i) - b0), l = int(__builtin_amdgcn_readlane(e_l, i) - b0);
+      const bool mine = ln >= f && ln < l;
+      const double asw = p.alpha * d.wrec[v].sumw;
+      if (int32_t(v) < p.n_dense) {
+        const int32_t *wrow = d.w_dense + size_t(v) * size_t(K);
+        for (int k = lane; k < K; k += kWave) wh[k] = what(uint32_t(wrow[k]), p.beta, d.den[k]);
+        held = -1;
+      } else {
+        const uint32_t n = __builtin_amdgcn_readlane(nnz_l, i);
+        const uint32_t ek = ent >> 16;
+        const double we = uint32_t(lane) < n ? what(ent & 0xFFFFu, p.beta, d.den[ek]) : 0.0;
+        if (held >= 0) {
+          if (lane < held) wh[held_k] = d.bden[held_k];
+        } else {
+          for (int k = lane; k < K; k += kWave) wh[k] = d.bden[k];
+        }
+        order();
+        if (uint32_t(lane) < n) wh[ek] = we;
+        held = int(n);
+        held_k = ek;
+      }
+      order();
+      const WordState w{wh, nullptr, 0, K, 0, 0u, 0.0, 0.0, p.alpha, nullptr, nullptr};
+      unsigned long long none = 0;
+      uint32_t nnz_read;
+      draw_tokens<false, true>(mine, off, hdr & 0xFFFFu, f, ln, bt, w, d.d_ent, none, &nnz_read);
+      if (mine) part = llpt_term(bt.u[ln], asw, hdr >> 16, Kalpha);
+      order();
+    }
+    part = group_sum<kWave>(part);
+    if (lane == 0) d.ll_part[p.light_begin + int64_t(bi)] = part;
+  }
+}
+
+// Large K: the row in two tiles, as in k_sampler_tiled.  Pass 0 keeps each
+// token's sum over the topics below KT and the chunk where its row reaches KT
+// (the per-workgroup scratch of the sampler), pass 1 adds the topics from KT
+// on, reading the row from that chunk.
+__global__ __launch_bounds__(kTiledBlock) void k_loglik_tiled(DevState d, Params p) {
+  extern __shared__ double lds[];
+  const int K = p.K;
+  const uint32_t kt = uint32_t(p.tile_topics);
+  double *wt = lds;                                                    // [kt + kGroup]
+  double *s_part = lds + kt + kGroup;                                  // [waves]
+  uint32_t *s_reg = reinterpret_cast<uint32_t *>(s_part + kTiledBlock / kWave);  // [4]
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = tid / kWave, grp = lane / kGroup, li = lane % kGroup;
+  const uint32_t pad = uint32_t(K) << 16;
+  double *sc_s = d.ts_s + size_t(blockIdx.x) * size_t(p.max_region);
+  uint32_t *sc_c = d.ts_code + size_t(blockIdx.x) * size_t(p.max_region);
+  const double Kalpha = double(K) * p.alpha;
+  const int waves = kTiledBlock / kWave;
+  for (;;) {
+    if (tid == 0) {
+      const uint32_t r = atomicAdd(&d.counters[CNT_LOGLIK], 1u);
+      s_reg[0] = r;
+      if (int64_t(r) < p.n_regions) {
+        s_reg[1] = d.region[3 * size_t(r)];
+        s_reg[2] = d.region[3 * size_t(r) + 1];
+        s_reg[3] = d.region[3 * size_t(r) + 2];
+      }
+    }
+    __syncthreads();
+    const uint32_t r = __builtin_amdgcn_readfirstlane(s_reg[0]);
+    if (int64_t(r) >= p.n_regions) break;
+    const uint32_t v = __builtin_amdgcn_readfirstlane(s_reg[1]);
+    const uint32_t b = __builtin_amdgcn_readfirstlane(s_reg[2]), e = __builtin_amdgcn_readfirstlane(s_reg[3]);
+    const double asw = p.alpha * d.wrec[v].sumw;
+    double part = 0.0;
+    for (int pass = 0; pass < 2; ++pass) {
+      const uint32_t tbase = pass == 1 ? kt : 0u;
+      const uint32_t tlen = pass == 1 ? uint32_t(K) + 1u - kt : kt;
+      fill_tile(d, p, v, 0xFFFFFFFFu, tbase, tlen, kt, wt, tid, kTiledBlock);  // no topic left out
+      const TileState ts{wt, tbase, kt, 0u - tbase * 8u};
+      const uint32_t stride = uint32_t(waves) * 4u;
+      uint32_t off_n = d.wt_kr[min(b + uint32_t(wave) * 4u + uint32_t(grp), e - 1u)].y;
+      for (uint32_t j0 = b + uint32_t(wave) * 4u; j0 < e; j0 += stride) {
+        const uint32_t j = j0 + uint32_t(grp), q = j - b;
+        const uint32_t off = off_n;
+        if (j0 + stride < e) off_n = d.wt_kr[min(j + stride, e - 1u)].y;  // one step ahead
+        if (j >= e) continue;
+        const uint32_t *row = d.d_ent + off;
+        const uint32_t hdr = row[0], slots = d_row_slots(hdr & 0xFFFFu), nch = (slots + kChunk - 1) / kChunk;
+        double s = 0.0;
+        const uint32_t c_from = pass == 0 ? 0u : sc_c[q];
+        uint32_t sc = c_from;
+        bool open = true;
+        for (uint32_t c0 = c_from; open; c0 += kTiledAhead) {
+          uint32_t rr[kTiledAhead][kMaxRun];
+#pragma unroll
+          for (int c = 0; c < kTiledAhead; ++c) load_run_masked(row, c0 + uint32_t(c), slots, li, pad, rr[c]);
+#pragma unroll
+          for (int c = 0; c < kTiledAhead; ++c) {
+            if (open) {
+              sc = c0 + uint32_t(c);
+              open = sc + 1u < nch;
+              if (pass == 0) open = open && (uint32_t(__shfl(int(rr[c][kMaxRun - 1]), kGroup - 1, kGroup)) >> 16) < kt;
+              s += run_sum_tile(rr[c], ts);
+            }
+          }
+        }
+        s = gsum<kGroup>(s);
+        if (li == 0) {
+          if (pass == 0) {
+            sc_s[q] = s;
+            sc_c[q] = sc;
+          } else {
+            part += llpt_term(sc_s[q] + s, asw, hdr >> 16, Kalpha);
+          }
         }
       }
       __syncthreads();
     }
-    double part = 0.0;
-    for (uint32_t j = b + uint32_t(gid); j < e; j += kBlock / kGroup) {
-      const uint32_t *row = d.d_ent + d.wt_kr[j].y + 1;
-      const uint32_t hdr = row[-1];
-      const uint32_t nnz = hdr & 0xFFFFu;
-      double acc = 0.0;
-      for (uint32_t q = li; q < nnz; q += kGroup) {
-        const uint32_t ent = row[q];
-        acc += double(ent & 0xFFFFu) * wh[ent >> 16];
-      }
-      const double num = group_sum<kGroup>(acc) + p.alpha * sumw;
-      const double len = double(hdr >> 16);
-      part += log2(num / (len + Kalpha));
-    }
-    if (li == 0) s_part[gid] = part;
+    part = group_sum<kWave>(part);
+    if (lane == 0) s_part[wave] = part;
     __syncthreads();
     if (tid == 0) {
       double s = 0.0;
-      for (int q = 0; q < kBlock / kGroup; ++q) s += s_part[q];
+      for (int q = 0; q < waves; ++q) s += s_part[q];
       d.ll_part[r] = s;
     }
     __syncthreads();
   }
 }
 
+// out[0] = sum of part[0..n), one workgroup in a fixed order: 256 strands of
+// every 256th value each, kSumAhead of them loaded together.
+constexpr int kSumAhead = 16;
 __global__ __launch_bounds__(kBlock) void k_loglik_reduce(const double *__restrict__ part, int64_t n,
                                                           double *__restrict__ out) {
   __shared__ double red[kBlock / kWave];
   double s = 0.0;
-  for (int64_t q = threadIdx.x; q < n; q += kBlock) s += part[q];
+  int64_t q = threadIdx.x;
+  for (; q + int64_t(kSumAhead - 1) * kBlock < n; q += int64_t(kSumAhead) * kBlock) {
+    double v[kSumAhead];
+#pragma unroll
+    for (int u = 0; u < kSumAhead; ++u) v[u] = part[q + int64_t(u) * kBlock];
+#pragma unroll
+    for (int u = 0; u < kSumAhead; ++u) s += v[u];
+  }
+  for (; q < n; q += kBlock) s += part[q];
   s = block_sum(s, red);
   if (threadIdx.x == 0) out[0] = s;
 }
@@ -3134,8 +3373,9 @@ hipError_t launch_word_pre(const DevState &d, const Params &p, hipStream_t s) {
     err = launch_beta_sum(d, p, s);
     if (err != hipSuccess) return err;
   }
-  // below K = 4,096 a table of K 16-bit counts per wave (at most 32 KB)
-  const size_t lds = p.sparse_pre ? 0 : sizeof(uint16_t) * size_t((p.K + 1) & ~1) * (kBlock / kWave);
+  // below K = 4,096 a table of K 16-bit counts per wave (at most 32 KB), for
+  // sparse rows only (out of core every word is dense, at every K)
+  const size_t lds = p.sparse_pre || p.n_dense >= p.n_present ? 0 : sizeof(uint16_t) * size_t((p.K + 1) & ~1) * (kBlock / kWave);
   const uint32_t grid = uint32_t((p.n_present + kBlock / kWave - 1) / (kBlock / kWave));
   hipLaunchKernelGGL(k_word_pre_wave, dim3(grid), dim3(kBlock), lds, s, d, p);
   return hipGetLastError();
@@ -3197,6 +3437,13 @@ int sampler_block(int K, int want, bool *q_table) {
   return best;
 }
 
+// hipSuccess if the kernel has no static LDS (its dynamic LDS starts at address 0).
+static hipError_t no_static_lds(const void *kernel) {
+  hipFuncAttributes a;
+  const hipError_t e = hipFuncGetAttributes(&a, kernel);
+  return e != hipSuccess ? e : a.sharedSizeBytes == 0 ? hipSuccess : hipErrorInvalidConfiguration;
+}
+
 int tiled_topics(int K) { return ((K + 2) / 2 + kGroup - 1) / kGroup * kGroup; }
 size_t tiled_lds_bytes(int K, int kt) {
   const size_t nb = size_t((K + kGroup - 1) / kGroup);
@@ -3206,11 +3453,7 @@ size_t tiled_lds_bytes(int K, int kt) {
 hipError_t launch_sampler(const DevState &d, const Params &p, uint32_t t, hipStream_t s) {
   if (p.big_k) {
     // the tile must start at LDS address 0 (wt_of): no static LDS
-    static const hipError_t lds_at_0 = [] {
-      hipFuncAttributes a;
-      const hipError_t e = hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_sampler_tiled));
-      return e != hipSuccess ? e : a.sharedSizeBytes == 0 ? hipSuccess : hipErrorInvalidConfiguration;
-    }();
+    static const hipError_t lds_at_0 = no_static_lds(reinterpret_cast<const void *>(k_sampler_tiled));
     if (lds_at_0 != hipSuccess) return lds_at_0;
     // a tile's Q' blocks: at most two per thread
     if (p.tile_topics / kGroup + 1 > 2 * kTiledBlock) return hipErrorInvalidValue;
@@ -3290,11 +3533,10 @@ hipError_t launch_rebuild_w(const DevState &d, const Params &p, hipStream_t s) {
       hipLaunchKernelGGL(k_rebuild_w_bits<false>, dim3(uint32_t(p.grid_regions)), dim3(kBlock), wlds, s, d, p);
     }
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    // T: per-workgroup histograms in the LLPT kernel's scratch (idle here:
-    // loglik_grid_big_k rows of K doubles hold as many rows of K counts)
-    if (!d.wscratch) return hipErrorInvalidValue;  // allocated before any rebuild
-    const int G = loglik_grid_big_k(p);
-    uint32_t *rows = reinterpret_cast<uint32_t *>(d.wscratch);
+    // T: per-workgroup histograms
+    if (!d.hist_rows) return hipErrorInvalidValue;  // allocated before any rebuild
+    const int G = topic_hist_grid(p);
+    uint32_t *rows = d.hist_rows;
     err = allow_lds(k_topic_hist, sizeof(uint32_t) * size_t(p.K));
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(k_topic_hist, dim3(uint32_t(G)), dim3(kHistBlock), sizeof(uint32_t) * size_t(p.K), s, d, p,
@@ -3383,16 +3625,53 @@ hipError_t launch_sum_f64(const double *part, int64_t n, double *out, hipStream_
   return hipGetLastError();
 }
 
+// The LLPT kernels' dynamic LDS: the W^ row and the batch slices of nb threads.
+static size_t loglik_lds_bytes(int K, int nb) {
+  return sizeof(double) * (size_t(wh_entries(K)) + size_t(nb) + size_t(nb) / kWave) +
+         size_t(nb) * (2 * sizeof(uint32_t) + 1) + 4 * sizeof(uint32_t);
+}
+
 hipError_t launch_loglik(const DevState &d, const Params &p, hipStream_t s) {
-  const size_t lds = p.big_k ? 0 : sizeof(double) * size_t(p.K);
-  hipError_t err0 = allow_lds(k_loglik, lds);
-  if (err0 != hipSuccess) return err0;
-  // large K: one workgroup per slice of the W^' scratch
-  const uint32_t grid = uint32_t(p.big_k ? loglik_grid_big_k(p) : p.grid_regions);
-  hipLaunchKernelGGL(k_loglik, dim3(grid), dim3(kBlock), lds, s, d, p);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_loglik_reduce, dim3(1), dim3(kBlock), 0, s, d.ll_part, p.n_regions, d.ll_out);
+  hipError_t err;
+  if (p.big_k) {
+    // the tile must start at LDS address 0 (wt_of): no static LDS
+    static const hipError_t lds_at_0 = no_static_lds(reinterpret_cast<const void *>(k_loglik_tiled));
+    if (lds_at_0 != hipSuccess) return lds_at_0;
+    const size_t lds = sizeof(double) * (size_t(p.tile_topics) + kGroup + kTiledBlock / kWave) + 4 * sizeof(uint32_t);
+    err = allow_lds(k_loglik_tiled, lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(k_loglik_tiled, dim3(uint32_t(tiled_grid(p))), dim3(kTiledBlock), lds, s, d, p);
+  } else if (p.light_begin > 0) {
+    // the sampler's workgroup size: both hold one W^ row per workgroup
+    const int nb = p.sampler_block;
+    const size_t lds = loglik_lds_bytes(p.K, nb);
+    const uint32_t grid = uint32_t(std::min<int64_t>(p.light_begin, std::max<int64_t>(1, int64_t(p.grid_regions) * kBlock / nb)));
+    if (nb == 1024) {
+      err = allow_lds(k_loglik_1024, lds);
+      if (err != hipSuccess) return err;
+      hipLaunchKernelGGL(k_loglik_1024, dim3(grid), dim3(1024), lds, s, d, p);
+    } else if (nb == 512) {
+      err = allow_lds(k_loglik_512, lds);
+      if (err != hipSuccess) return err;
+      hipLaunchKernelGGL(k_loglik_512, dim3(grid), dim3(512), lds, s, d, p);
+    } else {
+      err = allow_lds(k_loglik, lds);
+      if (err != hipSuccess) return err;
+      hipLaunchKernelGGL(k_loglik, dim3(grid), dim3(256), lds, s, d, p);
+    }
+  }
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+  if (p.n_light_batches > 0) {
+    const size_t lds = loglik_lds_bytes(p.K, kWave);
+    err = allow_lds(k_loglik_light, lds);
+    if (err != hipSuccess) return err;
+    const uint32_t grid = uint32_t(std::min<int64_t>(p.n_light_batches, int64_t(p.grid_regions) * 2));
+    hipLaunchKernelGGL(k_loglik_light, dim3(grid), dim3(kWave), lds, s, d, p);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+  }
+  // one partial per region, and per batch of light regions
+  hipLaunchKernelGGL(k_loglik_reduce, dim3(1), dim3(kBlock), 0, s, d.ll_part, p.light_begin + p.n_light_batches,
+                     d.ll_out);
   return hipGetLastError();
 }
 

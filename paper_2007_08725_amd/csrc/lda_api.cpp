@@ -258,7 +258,7 @@ lda_status create_device(lda_handle *h, const lda_options *o, const int32_t *wor
     LDA_TRY(dalloc(h, &d.ts_code, slots));
     LDA_TRY(dalloc(h, &d.ts_list, slots));
   }
-  if (w_bits(p)) LDA_TRY(dalloc(h, &d.wscratch, size_t(loglik_grid_big_k(p)) * size_t(L.K)));
+  if (w_bits(p)) LDA_TRY(dalloc(h, &d.hist_rows, size_t(topic_hist_grid(p)) * size_t(L.K)));
   LDA_TRY(dalloc(h, &d.ll_out, 1));
   d.stats = h->stats_base;
   LDA_TRY(upload(h, d.region, L.region));

@@ -167,12 +167,11 @@ struct DevState {
   double *ll_out;               // [1]
   // large K only (the tiled sampler): per-workgroup slices of max_region
   // entries carrying a token's S' part, C1 and split chunk between passes,
-  // the records of the region's tokens whose draw finishes in the last pass,
-  // and the LLPT kernel's W^' rows
+  // the records of the region's tokens whose draw finishes in the last pass
   double *ts_s;
   uint32_t *ts_c1, *ts_code;
   TiledRec *ts_list;
-  double *wscratch;
+  uint32_t *hist_rows;  // large K: the rows of k_topic_hist
   // large K (p.sparse_pre): topics by ascending T (descending beta/den[k]),
   // their sort buffers, and the sum of beta/den[k] over all topics
   uint32_t *topic_order, *topic_keys, *topic_iota;
@@ -288,10 +287,10 @@ std::vector<uint32_t> light_batches(const std::vector<uint32_t> &region, int64_t
 int tiled_topics(int K);
 size_t tiled_lds_bytes(int K, int kt);
 constexpr int kTiledThreads = 1024;
-// Workgroups of the tiled sampler (one per CU: its LDS fills a CU) and of the
-// large-K LLPT kernel; the scratch slices are sized for these grids.
+// Workgroups of the tiled sampler and LLPT kernel (one per CU: their LDS fills
+// a CU) and of k_topic_hist; the scratch slices are sized for these grids.
 inline int tiled_grid(const Params &p) { return p.grid_regions / 8 > 0 ? p.grid_regions / 8 : 1; }
-inline int loglik_grid_big_k(const Params &p) { return tiled_grid(p); }
+inline int topic_hist_grid(const Params &p) { return tiled_grid(p); }
 // The W rebuild by bitmap, with T from a histogram of the topics (and its
 // scratch rows), from this many topics on: below it a workgroup's tables of K
 // counts are small enough to keep several workgroups on a CU.
