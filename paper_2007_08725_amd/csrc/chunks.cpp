@@ -33,6 +33,7 @@ struct ChunkInfo {
   uint32_t *h_wpos = nullptr;   // pinned host [ntok]
   uint16_t *h_z = nullptr;      // pinned host [ntok]
   uint32_t *doc_off = nullptr, *d_cap = nullptr, *word_off = nullptr, *region = nullptr;  // device, chunk-local
+  uint32_t *unit = nullptr;        // device: the chunk's units of the sampler
   uint32_t *light_batch = nullptr; // device: the chunk's light regions in batches
   uint32_t *heavy_docs = nullptr;  // device: the chunk's documents longer than kHeavyDocTokens (chunk-local ids)
   uint32_t d_slots = 0;         // D-row slots of the chunk's documents
@@ -61,7 +62,7 @@ struct ChunkMode {
   uint32_t *t_next = nullptr;
   double *ll_chunk = nullptr;
   uint32_t max_tok = 0, max_slots = 0;
-  int64_t max_regions = 0;
+  int64_t max_regions = 0, max_partials = 0;
 };
 
 void release_chunks(ChunkMode *cm) {
@@ -108,6 +109,7 @@ DevState chunk_state(const lda_handle *h, const ChunkInfo &ci, const ChunkSlot &
   d.d_cap = ci.d_cap;
   d.word_off = ci.word_off;
   d.region = ci.region;
+  d.unit = ci.unit;
   d.light_batch = ci.light_batch;
   d.heavy_docs = ci.heavy_docs;
   d.dt_word = sl.dt_word;
@@ -287,10 +289,9 @@ lda_status chunked_create(lda_handle *h, const int32_t *word, const int32_t *doc
     set_doc_batches(ci.p);
     ci.p.n_regions = int64_t(region.size() / 3);
     ci.p.light_begin = light_region_start(region, K, p.big_k != 0);
-    const std::vector<uint32_t> batches = light_batches(region, ci.p.light_begin, int64_t(p.grid_regions) * 2);
-    ci.p.n_light_batches = int32_t(batches.size() - 1);
-    LDA_TRY(dalloc(h, &ci.light_batch, batches.size()));
-    LDA_TRY(upload(h, ci.light_batch, batches));
+    int64_t partials = 0;
+    LDA_TRY(make_units(h, region, ci.region, ci.p, &ci.unit, &ci.light_batch, &partials));
+    cm.max_partials = std::max(cm.max_partials, partials);
     ci.p.key_base = ci.tok0;
     ci.p.xcd_doc[0] = 0;
     for (int x = 1; x < kXcds; ++x) {
@@ -315,7 +316,7 @@ lda_status chunked_create(lda_handle *h, const int32_t *word, const int32_t *doc
   p.n_regions = total_regions;
   p.max_region = int32_t(max_region);
   for (ChunkInfo &ci : cm.c) ci.p.max_region = p.max_region;
-  LDA_TRY(dalloc(h, &d.ll_part, size_t(std::max<int64_t>(cm.max_regions, 1))));
+  LDA_TRY(dalloc(h, &d.ll_part, size_t(std::max<int64_t>(cm.max_partials, 1))));
   if (p.big_k) {
     const size_t sl = size_t(tiled_grid(p)) * size_t(max_region);
     LDA_TRY(dalloc(h, &d.ts_s, sl));
@@ -366,6 +367,7 @@ lda_status chunked_iterate(lda_handle *h, int32_t n_iters, lda_iter_stats *stats
         HIP_TRY(h, launch_clear_skips(dc, ci.p, t, h->stream, c == 0));
         if (!p.no_skip) HIP_TRY(h, launch_doc_pass(dc, ci.p, t, h->stream));
         LDA_TRY(run_sampler(h, dc, ci.p, t));
+        HIP_TRY(h, launch_fold_stats(dc, stat_slots(ci.p, t), h->stream));
         DevState dw = dc;
         dw.w_dense = cm.w_next;
         dw.T = cm.t_next;

@@ -149,6 +149,32 @@ inline lda_status sort_pairs(lda_handle *h, const uint32_t *keys_in, uint32_t *k
 }
 
 
+// The sampler's units (sampler_units) and light batches of a region table (on
+// the device as d_region), and the LLPT partials they need.  The tiled sampler
+// takes whole regions (a unit's W^ row costs it three tile fills), and so does
+// everything when the cut would pass the fixed array of lda_loglik_noalloc.
+inline lda_status make_units(lda_handle *h, const std::vector<uint32_t> &region, uint32_t *d_region, Params &p,
+                             uint32_t **unit, uint32_t **light_batch, int64_t *partials) {
+  const std::vector<uint32_t> batches = light_batches(region, p.light_begin, int64_t(p.grid_regions) * 2);
+  p.n_light_batches = int32_t(batches.size() - 1);
+  LDA_TRY(dalloc(h, light_batch, batches.size()));
+  LDA_TRY(upload(h, *light_batch, batches));
+  *unit = d_region;
+  p.n_units = p.light_begin;
+  if (!p.big_k) {
+    const std::vector<uint32_t> units =
+        sampler_units(region, p.light_begin, p.n, p.K, sampler_workgroups(p), p.sampler_block);
+    const int64_t n = int64_t(units.size() / 3);
+    if (n > p.light_begin && n + p.n_light_batches <= int64_t(LDA_NOALLOC_MAX_REGIONS)) {
+      LDA_TRY(dalloc(h, unit, units.size()));
+      LDA_TRY(upload(h, *unit, units));
+      p.n_units = n;
+    }
+  }
+  *partials = p.n_units + p.n_light_batches;
+  return LDA_OK;
+}
+
 // The documents of doc_off (M + 1 offsets) longer than kHeavyDocTokens.
 inline std::vector<uint32_t> heavy_documents(const uint32_t *doc_off, uint32_t M) {
   std::vector<uint32_t> out;

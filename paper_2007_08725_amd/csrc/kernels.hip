@@ -595,7 +595,11 @@ template <bool KeyId>
 __global__ __launch_bounds__(kBlock) void k_doc_pass(DevState d, Params p, uint32_t t,
                                                      unsigned long long *__restrict__ stats) {
   extern __shared__ uint16_t cmap_all[];
-  if (!skip_test_runs(d, p, t)) return;  // uniform over the grid
+  if (!skip_test_runs(d, p, t)) {  // uniform over the grid
+    if (threadIdx.x % kWave == 0)
+      d.wave_stats[size_t(WV_SKIP3) * kWaveSlots + blockIdx.x * uint32_t(p.doc_waves) + threadIdx.x / kWave] = 0ull;
+    return;
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) stats[ST_TEST_RAN] = 1ull;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int K = p.K;
@@ -720,10 +724,8 @@ __global__ __launch_bounds__(kBlock) void k_doc_pass(DevState d, Params p, uint3
     }
   }
   nskip = group_sum_u64<kWave>(nskip);
-  if (lane == 0 && nskip) {
-    atomicAdd(&stats[ST_SKIP3], nskip);
-    atomicAdd(&d.skip_hist[t & 1u], nskip);
-  }
+  if (lane == 0)
+    d.wave_stats[size_t(WV_SKIP3) * kWaveSlots + blockIdx.x * uint32_t(p.doc_waves) + uint32_t(wave)] = nskip;
 }
 
 // Steps 2-3 for the heavy documents (longer than kHeavyDoc), one workgroup
@@ -925,7 +927,7 @@ __device__ __forceinline__ uint32_t pick_segment(uint32_t k, double term, double
 template <bool Sum>
 __device__ void draw_long(unsigned long long mask, unsigned long long foll, unsigned long long starts,
                           const BatchLds &bt, const WordState &w, const uint32_t *__restrict__ d_ent, int grp, int li,
-                          unsigned long long &after_s) {
+                          uint32_t &after_s) {
   constexpr int R = kMaxRun;
   mask &= ~foll;  // the runs' first tokens
   while (mask) {
@@ -1249,7 +1251,7 @@ __device__ __forceinline__ uint32_t finish_draw(int q, const BatchLds &bt, const
 // Sum: no draw; bt.u of the token gets the sum of its row's terms.
 template <int G, int NC, bool Sum>
 __device__ void draw_small(const BatchLds &bt, int slot, int n, const WordState &w,
-                           const uint32_t *__restrict__ d_ent, int li, unsigned long long &after_s) {
+                           const uint32_t *__restrict__ d_ent, int li, uint32_t &after_s) {
   constexpr uint32_t kSpan = uint32_t(G) * kRun;  // entries per chunk
   bool in_m = false;
   if (slot < n) {
@@ -1337,7 +1339,7 @@ __device__ constexpr uint32_t kBucketEnd[8] = {32, 64, 96, 128, 192, 256, 384, 5
 // as many chunks of G*kRun slots as its last (longest) row needs.
 template <int G, int MaxNC, bool Sum>
 __device__ void draw_rounds(int from, int to, const int (&ends)[8], const BatchLds &bt, const WordState &w,
-                            const uint32_t *__restrict__ d_ent, unsigned long long &after_s) {
+                            const uint32_t *__restrict__ d_ent, uint32_t &after_s) {
   constexpr uint32_t kSpan = uint32_t(G) * kRun;
   for (int base = from; base < to; base += kWave / G) {
     const int ln = lane_here(), g = ln / G, li = ln % G;
@@ -1377,7 +1379,7 @@ __device__ void draw_rounds(int from, int to, const int (&ends)[8], const BatchL
 // tokens.
 template <bool Wide, bool Sum = false>
 __device__ void draw_batch_small(bool und, uint32_t nnz, const BatchLds &bt, const WordState &w,
-                                 const uint32_t *__restrict__ d_ent, int lane, unsigned long long &after_s) {
+                                 const uint32_t *__restrict__ d_ent, int lane, uint32_t &after_s) {
   int n = 0, ends[8];
   const uint32_t slots = nnz + 1u;
 #pragma unroll
@@ -1415,7 +1417,7 @@ __device__ void draw_batch_small(bool und, uint32_t nnz, const BatchLds &bt, con
 template <bool Wide, bool Sum = false>
 __device__ __forceinline__ uint32_t draw_tokens(bool und, uint32_t off, uint32_t nnz, int first, int ln,
                                                 const BatchLds &bt, const WordState &w,
-                                                const uint32_t *__restrict__ d_ent, unsigned long long &after_s,
+                                                const uint32_t *__restrict__ d_ent, uint32_t &after_s,
                                                 uint32_t *nnz_read) {
   const unsigned long long lmask = __ballot(und && nnz + 1u > 512u);
   unsigned long long starts = 0ull;
@@ -1434,11 +1436,25 @@ __device__ __forceinline__ uint32_t draw_tokens(bool und, uint32_t off, uint32_t
   return und ? finish_draw(ln, bt, w, d_ent) : 0u;
 }
 
+// One wave's statistics (lane 0 stores them); first: the workgroup's first
+// wave, which also stores the regions' counts.
+__device__ __forceinline__ void store_stats(const DevState &d, uint32_t slot, bool first, uint32_t sampled,
+                                            uint32_t after_s, unsigned long long nnz, uint32_t regions,
+                                            uint32_t dense_regions, unsigned long long row_bytes) {
+  unsigned long long *st = d.wave_stats + slot;
+  st[size_t(WV_SAMPLED) * kWaveSlots] = sampled;
+  st[size_t(WV_AFTER_S) * kWaveSlots] = after_s;
+  st[size_t(WV_NNZ) * kWaveSlots] = nnz;
+  st[size_t(WV_REGIONS) * kWaveSlots] = first ? regions : 0u;
+  st[size_t(WV_DENSE_REGIONS) * kWaveSlots] = first ? dense_regions : 0u;
+  st[size_t(WV_ROW_BYTES) * kWaveSlots] = first ? row_bytes : 0ull;
+}
+
 // The sampler for workgroups of NB threads (NB / 64 waves); every wave works
 // on its own batches, so NB only changes how many waves share a region's W^
 // row in LDS (larger workgroups for large K, where LDS bounds the residency).
-// It takes the regions before p.light_begin; the light ones are
-// k_sampler_light's.
+// It takes the units (sampler_units) of the regions before p.light_begin; the
+// light regions are k_sampler_light's.
 template <int NB>
 __device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, unsigned long long *__restrict__ stats) {
   extern __shared__ double lds[];
@@ -1477,26 +1493,29 @@ __device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, u
   // next sparse word only restores that word's topics and K1 to beta/den[k]
   const uint32_t *held = nullptr;
   uint32_t held_nnz = 0, held_k1 = 0;
-  unsigned long long n_sampled = 0, n_after_s = 0, nnz_sum = 0;
-  unsigned long long n_reg = 0, n_dreg = 0, row_bytes = 0;
+  // (tokens of a corpus, and so these counts, fit 32 bits)
+  uint32_t n_sampled = 0, n_after_s = 0, n_reg = 0, n_dreg = 0;
+  unsigned long long nnz_sum = 0, row_bytes = 0;
 
   for (;;) {
     if (tid == 0) {
       const int64_t r = int64_t(atomicAdd(&d.counters[CNT_SAMPLER], 1u));
-      s_reg[3] = r < p.light_begin ? 1u : 0u;
+      s_reg[3] = r < p.n_units ? 1u : 0u;
       if (s_reg[3]) {
-        s_reg[0] = d.region[3 * size_t(r)];
-        s_reg[1] = d.region[3 * size_t(r) + 1];
-        s_reg[2] = d.region[3 * size_t(r) + 2];
+        s_reg[0] = d.unit[3 * size_t(r)];
+        s_reg[1] = d.unit[3 * size_t(r) + 1];
+        s_reg[2] = d.unit[3 * size_t(r) + 2];
       }
     }
     __syncthreads();
     if (!s_reg[3]) break;
-    const uint32_t v = __builtin_amdgcn_readfirstlane(s_reg[0]);
+    const uint32_t vc = __builtin_amdgcn_readfirstlane(s_reg[0]), v = vc & ~kUnitContinues;
     const uint32_t b = __builtin_amdgcn_readfirstlane(s_reg[1]);
     const uint32_t e = __builtin_amdgcn_readfirstlane(s_reg[2]);
-    n_reg++;
-    if (int32_t(v) < p.n_dense) n_dreg++;
+    if (vc == v) {  // the first unit of its region
+      n_reg++;
+      if (int32_t(v) < p.n_dense) n_dreg++;
+    }
     if (b == d.word_off[v])
       row_bytes += int32_t(v) < p.n_dense ? 4ull * uint64_t(K) : 4ull * d.ws_nnz[int(v) - p.n_dense];
     if (v != cur) {
@@ -1630,18 +1649,10 @@ __device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, u
     }
     __syncthreads();
   }
-  if (lane == 0) {
-    if (n_sampled) atomicAdd(&stats[ST_SAMPLED], n_sampled);
-    if (n_after_s) atomicAdd(&stats[ST_SKIP_AFTER_S], n_after_s);
-    if (nnz_sum) atomicAdd(&stats[ST_NNZ], nnz_sum);
-  }
-  if (tid == 0) {
-    if (n_reg) atomicAdd(&stats[ST_REGIONS], n_reg);
-    if (n_dreg) atomicAdd(&stats[ST_DENSE_REGIONS], n_dreg);
-    if (row_bytes) atomicAdd(&stats[ST_ROW_BYTES], row_bytes);
-  }
+  if (lane == 0)
+    store_stats(d, blockIdx.x * uint32_t(NB / kWave) + uint32_t(wave), wave == 0, n_sampled, n_after_s, nnz_sum, n_reg,
+                n_dreg, row_bytes);
 }
-
 
 __global__ __launch_bounds__(256, 7) void k_sampler(DevState d, Params p, uint32_t t,
                                                  unsigned long long *__restrict__ stats) {
@@ -1695,7 +1706,8 @@ __global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, u
   // fill; held < 0: a dense row or none, so that all of wh is rewritten)
   int held = -1;
   uint32_t held_k = 0, held_k1 = 0;  // lane q: topic of the held row's entry q
-  unsigned long long n_sampled = 0, n_after_s = 0, nnz_sum = 0, n_dreg = 0, row_bytes = 0, n_reg = 0;
+  uint32_t n_sampled = 0, n_after_s = 0, n_reg = 0, n_dreg = 0;
+  unsigned long long nnz_sum = 0, row_bytes = 0;
   // a wave's LDS accesses run in order; the fence keeps the compiler's order
   auto order = [&]() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
 
@@ -1807,14 +1819,9 @@ __global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, u
     if (j < e0) d.z_w[j] = uint16_t(topic);
   }
   row_bytes = group_sum_u64<kWave>(row_bytes);
-  if (lane == 0) {
-    if (n_sampled) atomicAdd(&stats[ST_SAMPLED], n_sampled);
-    if (n_after_s) atomicAdd(&stats[ST_SKIP_AFTER_S], n_after_s);
-    if (nnz_sum) atomicAdd(&stats[ST_NNZ], nnz_sum);
-    if (n_reg) atomicAdd(&stats[ST_REGIONS], n_reg);
-    if (n_dreg) atomicAdd(&stats[ST_DENSE_REGIONS], n_dreg);
-    if (row_bytes) atomicAdd(&stats[ST_ROW_BYTES], row_bytes);
-  }
+  if (lane == 0)
+    store_stats(d, uint32_t(stat_slots(p, t).light0) + blockIdx.x, true, n_sampled, n_after_s, nnz_sum, n_reg, n_dreg,
+                row_bytes);
 }
 
 // ---------------------------------------------------------- large K ----
@@ -2064,7 +2071,8 @@ __global__ __launch_bounds__(kTiledBlock) void k_sampler_tiled(DevState d, Param
   uint32_t *sc_c1 = d.ts_c1 + size_t(blockIdx.x) * size_t(p.max_region);
   uint32_t *sc_code = d.ts_code + size_t(blockIdx.x) * size_t(p.max_region);
   TiledRec *sc_list = d.ts_list + size_t(blockIdx.x) * size_t(p.max_region);
-  unsigned long long n_sampled = 0, n_after_s = 0, nnz_sum = 0, n_reg = 0, n_dreg = 0, row_bytes = 0;
+  uint32_t n_sampled = 0, n_after_s = 0, n_reg = 0, n_dreg = 0;
+  unsigned long long nnz_sum = 0, row_bytes = 0;
   const int waves = kTiledBlock / kWave;
   for (;;) {
     if (tid == 0) {
@@ -2388,23 +2396,49 @@ __global__ __launch_bounds__(kTiledBlock) void k_sampler_tiled(DevState d, Param
     }
   }
   // per-lane counts of group leaders, summed over the wave
-  n_sampled = group_sum_u64<kWave>(n_sampled);
-  n_after_s = group_sum_u64<kWave>(n_after_s);
+  n_sampled = group_sum_u32<kWave>(n_sampled);
+  n_after_s = group_sum_u32<kWave>(n_after_s);
   nnz_sum = group_sum_u64<kWave>(nnz_sum);
-  if (lane == 0) {
-    if (n_sampled) atomicAdd(&stats[ST_SAMPLED], n_sampled);
-    if (n_after_s) atomicAdd(&stats[ST_SKIP_AFTER_S], n_after_s);
-    if (nnz_sum) atomicAdd(&stats[ST_NNZ], nnz_sum);
-  }
-  if (tid == 0) {
-    if (n_reg) atomicAdd(&stats[ST_REGIONS], n_reg);
-    if (n_dreg) atomicAdd(&stats[ST_DENSE_REGIONS], n_dreg);
-    if (row_bytes) atomicAdd(&stats[ST_ROW_BYTES], row_bytes);
-  }
+  if (lane == 0)
+    store_stats(d, blockIdx.x * uint32_t(waves) + uint32_t(wave), wave == 0, n_sampled, n_after_s, nnz_sum, n_reg,
+                n_dreg, row_bytes);
 }
 
+// One statistic (0..kFoldBlocks-1) over the slots of the waves that stored
+// it, by one workgroup of kBlock threads; added, since an out-of-core
+// iteration folds once per chunk.
+__device__ void fold_stat(const DevState &d, const StatSlots &sl, int which) {
+  __shared__ unsigned long long red[kBlock / kWave];
+  const bool skip = which == kFoldBlocks - 1;
+  const unsigned long long *st = d.wave_stats + size_t(which) * kWaveSlots;
+  unsigned long long s = 0;
+  auto add = [&](int slot0, int n) {
+#pragma unroll 4
+    for (int q = int(threadIdx.x); q < n; q += kBlock) s += st[slot0 + q];
+  };
+  if (skip) {
+    add(0, sl.doc);
+  } else {
+    add(0, sl.main);
+    add(sl.light0, sl.light);
+  }
+  s = group_sum_u64<kWave>(s);
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int q = 1; q < kBlock / kWave; ++q) s += red[q];
+    constexpr int to[kFoldBlocks] = {ST_SAMPLED, ST_SKIP_AFTER_S, ST_NNZ, ST_REGIONS, ST_DENSE_REGIONS, ST_ROW_BYTES,
+                                     ST_SKIP3};
+    d.stats[to[which]] += s;
+    if (skip) d.skip_hist[sl.t & 1u] += s;
+  }
+}
+__global__ __launch_bounds__(kBlock) void k_fold_stats(DevState d, StatSlots sl) { fold_stat(d, sl, int(blockIdx.x)); }
+
 // Rows of split dense words are accumulated with atomics; clear them and T.
-__global__ void k_zero_split(DevState d, Params p) {
+// fold: the first kFoldBlocks workgroups also add up the iteration's statistics.
+__global__ __launch_bounds__(kBlock) void k_zero_split(DevState d, Params p, StatSlots sl, int fold) {
+  if (fold && blockIdx.x < kFoldBlocks) fold_stat(d, sl, int(blockIdx.x));
   const int64_t total = int64_t(p.n_dense) * p.K;
   for (int64_t x = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; x < total; x += int64_t(gridDim.x) * blockDim.x) {
     if (d.split[x / p.K]) d.w_dense[x] = 0;
@@ -3018,7 +3052,7 @@ __global__ __launch_bounds__(kBlock) void k_rebuild_d_sort(DevState d, Params p)
 
 // LLPT terms (Sec. 2.2): for every token,
 //   log2( (sum_{k in nz(D[d])} D[d][k] W^[v][k] + alpha * sum_k W^[v][k]) / (len(d) + K alpha) ),
-// summed per region (per batch of light regions) in an order that the layout
+// summed per unit of the sampler (per batch of light regions) in an order that the layout
 // fixes, so that the result does not depend on the schedule.
 //
 // The work is the sampler's S' pass without the draws, and it is organised the
@@ -3056,15 +3090,15 @@ __device__ __forceinline__ void loglik_body(DevState d, Params p) {
     if (tid == 0) {
       const uint32_t r = atomicAdd(&d.counters[CNT_LOGLIK], 1u);
       s_reg[0] = r;
-      if (int64_t(r) < p.light_begin) {
-        s_reg[1] = d.region[3 * size_t(r)];
-        s_reg[2] = d.region[3 * size_t(r) + 1];
-        s_reg[3] = d.region[3 * size_t(r) + 2];
+      if (int64_t(r) < p.n_units) {
+        s_reg[1] = d.unit[3 * size_t(r)] & ~kUnitContinues;
+        s_reg[2] = d.unit[3 * size_t(r) + 1];
+        s_reg[3] = d.unit[3 * size_t(r) + 2];
       }
     }
     __syncthreads();
     const uint32_t r = __builtin_amdgcn_readfirstlane(s_reg[0]);
-    if (int64_t(r) >= p.light_begin) break;
+    if (int64_t(r) >= p.n_units) break;
     const uint32_t v = __builtin_amdgcn_readfirstlane(s_reg[1]);
     const uint32_t b = __builtin_amdgcn_readfirstlane(s_reg[2]), e = __builtin_amdgcn_readfirstlane(s_reg[3]);
     if (v != cur) {
@@ -3110,7 +3144,7 @@ __device__ __forceinline__ void loglik_body(DevState d, Params p) {
         bt.off[ln] = off;
         bt.nnz[ln] = hdr & 0xFFFFu;
       }
-      unsigned long long none = 0;
+      uint32_t none = 0;
       uint32_t nnz_read;
       draw_tokens<(NB >= 1024), true>(in, off, hdr & 0xFFFFu, 0, ln, bt, w, d.d_ent, none, &nnz_read);
       if (in) part += llpt_term(bt.u[ln], asw, hdr >> 16, Kalpha);
@@ -3132,7 +3166,7 @@ __global__ __launch_bounds__(512, 4) void k_loglik_512(DevState d, Params p) { l
 __global__ __launch_bounds__(1024, 4) void k_loglik_1024(DevState d, Params p) { loglik_body<1024>(d, p); }
 
 // The light regions, in the light sampler's batches, one wave each: partial
-// p.light_begin + i is batch i's.
+// p.n_units + i is batch i's.
 __global__ __launch_bounds__(64, 4) void k_loglik_light(DevState d, Params p) {
   extern __shared__ double lds[];
   const int K = p.K;
@@ -3201,14 +3235,14 @@ __global__ __launch_bounds__(64, 4) void k_loglik_light(DevState d, Params p) {
       }
       order();
       const WordState w{wh, nullptr, 0, K, 0, 0u, 0.0, 0.0, p.alpha, nullptr, nullptr};
-      unsigned long long none = 0;
+      uint32_t none = 0;
       uint32_t nnz_read;
       draw_tokens<false, true>(mine, off, hdr & 0xFFFFu, f, ln, bt, w, d.d_ent, none, &nnz_read);
       if (mine) part = llpt_term(bt.u[ln], asw, hdr >> 16, Kalpha);
       order();
     }
     part = group_sum<kWave>(part);
-    if (lane == 0) d.ll_part[p.light_begin + int64_t(bi)] = part;
+    if (lane == 0) d.ll_part[p.n_units + int64_t(bi)] = part;
   }
 }
 
@@ -3465,9 +3499,9 @@ hipError_t launch_sampler(const DevState &d, const Params &p, uint32_t t, hipStr
   }
   const int nb = p.sampler_block;
   const size_t lds = sampler_lds_bytes(p.K, nb, p.q_table != 0);
-  const uint32_t grid = uint32_t(std::max<int64_t>(1, int64_t(p.grid_regions) * kBlock / nb));
+  const uint32_t grid = uint32_t(sampler_grid(p));
   hipError_t err;
-  if (p.light_begin == 0) return hipSuccess;  // every region is light
+  if (p.n_units == 0) return hipSuccess;  // every region is light
   if (nb == 1024) {
     err = allow_lds(k_sampler_1024, lds);
     if (err != hipSuccess) return err;
@@ -3496,22 +3530,27 @@ hipError_t launch_sampler_light(const DevState &d, const Params &p, uint32_t t, 
   const size_t lds = light_lds_bytes(p.K);
   hipError_t err = allow_lds(k_sampler_light, lds);
   if (err != hipSuccess) return err;
-  // at most 16 one-wave workgroups per CU (grid_regions is 8 per CU)
-  const uint32_t grid = uint32_t(std::min<int64_t>(p.n_light_batches, int64_t(p.grid_regions) * 2));
+  const uint32_t grid = uint32_t(light_grid(p));
   hipLaunchKernelGGL(k_sampler_light, dim3(grid), dim3(kWave), lds, s, d, p, t, d.stats);
   return hipGetLastError();
 }
 
-hipError_t launch_rebuild(const DevState &d, const Params &p, hipStream_t s) {
-  hipError_t err = launch_zero_split(d, p, s);
+hipError_t launch_rebuild(const DevState &d, const Params &p, hipStream_t s, const StatSlots *slots) {
+  hipError_t err = launch_zero_split(d, p, s, slots);
   if (err == hipSuccess) err = launch_rebuild_w(d, p, s);
   if (err == hipSuccess) err = launch_rebuild_d(d, p, s);
   return err;
 }
 
-hipError_t launch_zero_split(const DevState &d, const Params &p, hipStream_t s) {
-  const int64_t zb = std::min<int64_t>((int64_t(p.n_dense) * p.K + kBlock - 1) / kBlock + 1, 65536);
-  hipLaunchKernelGGL(k_zero_split, dim3(uint32_t(zb)), dim3(kBlock), 0, s, d, p);
+hipError_t launch_zero_split(const DevState &d, const Params &p, hipStream_t s, const StatSlots *slots) {
+  const int64_t zb = std::min<int64_t>((int64_t(p.n_dense) * p.K + kBlock - 1) / kBlock + kFoldBlocks, 65536);
+  hipLaunchKernelGGL(k_zero_split, dim3(uint32_t(zb)), dim3(kBlock), 0, s, d, p, slots ? *slots : StatSlots{},
+                     slots ? 1 : 0);
+  return hipGetLastError();
+}
+
+hipError_t launch_fold_stats(const DevState &d, const StatSlots &slots, hipStream_t s) {
+  hipLaunchKernelGGL(k_fold_stats, dim3(kFoldBlocks), dim3(kBlock), 0, s, d, slots);
   return hipGetLastError();
 }
 
@@ -3641,11 +3680,11 @@ hipError_t launch_loglik(const DevState &d, const Params &p, hipStream_t s) {
     err = allow_lds(k_loglik_tiled, lds);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(k_loglik_tiled, dim3(uint32_t(tiled_grid(p))), dim3(kTiledBlock), lds, s, d, p);
-  } else if (p.light_begin > 0) {
+  } else if (p.n_units > 0) {
     // the sampler's workgroup size: both hold one W^ row per workgroup
     const int nb = p.sampler_block;
     const size_t lds = loglik_lds_bytes(p.K, nb);
-    const uint32_t grid = uint32_t(std::min<int64_t>(p.light_begin, std::max<int64_t>(1, int64_t(p.grid_regions) * kBlock / nb)));
+    const uint32_t grid = uint32_t(std::min<int64_t>(p.n_units, sampler_workgroups(p)));
     if (nb == 1024) {
       err = allow_lds(k_loglik_1024, lds);
       if (err != hipSuccess) return err;
@@ -3665,13 +3704,12 @@ hipError_t launch_loglik(const DevState &d, const Params &p, hipStream_t s) {
     const size_t lds = loglik_lds_bytes(p.K, kWave);
     err = allow_lds(k_loglik_light, lds);
     if (err != hipSuccess) return err;
-    const uint32_t grid = uint32_t(std::min<int64_t>(p.n_light_batches, int64_t(p.grid_regions) * 2));
+    const uint32_t grid = uint32_t(light_grid(p));
     hipLaunchKernelGGL(k_loglik_light, dim3(grid), dim3(kWave), lds, s, d, p);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
-  // one partial per region, and per batch of light regions
-  hipLaunchKernelGGL(k_loglik_reduce, dim3(1), dim3(kBlock), 0, s, d.ll_part, p.light_begin + p.n_light_batches,
-                     d.ll_out);
+  // one partial per unit and per batch of light regions
+  hipLaunchKernelGGL(k_loglik_reduce, dim3(1), dim3(kBlock), 0, s, d.ll_part, p.n_units + p.n_light_batches, d.ll_out);
   return hipGetLastError();
 }
 

@@ -213,6 +213,23 @@ lda_status build_layout(const int32_t *word, const int32_t *doc, int64_t n, int3
   return LDA_OK;
 }
 
+std::vector<uint32_t> sampler_units(const std::vector<uint32_t> &region, int64_t light_begin, int64_t n, int32_t K,
+                                    int64_t workgroups, int32_t threads) {
+  const uint64_t most = std::max<uint64_t>(uint64_t(n) / (2 * uint64_t(workgroups)),
+                                           std::max<uint64_t>(uint64_t(threads), 2 * uint64_t(K)));
+  std::vector<uint32_t> out;
+  for (size_t r = 0; r < size_t(light_begin); ++r) {
+    const uint32_t v = region[3 * r], b = region[3 * r + 1], c = region[3 * r + 2] - b;
+    const uint64_t k = (uint64_t(c) + most - 1) / most;
+    for (uint64_t q = 0; q < k; ++q) {
+      out.push_back(q ? v | kUnitContinues : v);
+      out.push_back(b + uint32_t(uint64_t(c) * q / k));
+      out.push_back(b + uint32_t(uint64_t(c) * (q + 1) / k));
+    }
+  }
+  return out;
+}
+
 std::vector<uint32_t> light_batches(const std::vector<uint32_t> &region, int64_t light_begin, int64_t waves) {
   const size_t n = region.size() / 3, r0 = size_t(light_begin);
   std::vector<uint32_t> out(1, 0u);

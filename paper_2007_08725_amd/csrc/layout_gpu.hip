@@ -164,11 +164,19 @@ __global__ __launch_bounds__(kThreads) void k_sum_nnz(DevState d, Params p, int 
     if (quads * 4 + i0 < total) nw += d.w_dense[quads * 4 + i0] != 0;
     for (int64_t q = i0; q < p.n_present - p.n_dense; q += step) nw += d.ws_nnz[q];
   }
+  // one atomic per workgroup and sum: a cache line takes 88 million a second
+  __shared__ unsigned long long s_sum[2][kThreads / 64];
   nd = wave_total(nd);
   nw = wave_total(nw);
   if ((threadIdx.x & 63) == 0) {
-    if (nd) atomicAdd(&out[0], nd);
-    if (nw) atomicAdd(&out[1], nw);
+    s_sum[0][threadIdx.x / 64] = nd;
+    s_sum[1][threadIdx.x / 64] = nw;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    unsigned long long v = 0;
+    for (int q = 0; q < kThreads / 64; ++q) v += s_sum[threadIdx.x][q];
+    if (v) atomicAdd(&out[threadIdx.x], v);
   }
 }
 
@@ -256,7 +264,7 @@ hipError_t launch_inflate(const uint32_t *region, int64_t n_regions, const uint3
 
 hipError_t launch_sum_nnz(const DevState &d, const Params &p, bool D, bool W, unsigned long long *out, hipStream_t s) {
   const int64_t work = std::max<int64_t>(D ? p.M : 0, W ? std::max<int64_t>(int64_t(p.n_dense) * p.K / 16, p.n_present) : 0);
-  const uint32_t grid = std::min(grid_for(work), 2048u);
+  const uint32_t grid = std::min(grid_for(work), 1024u);
   hipLaunchKernelGGL(k_sum_nnz, dim3(grid), dim3(kThreads), 0, s, d, p, D ? 1 : 0, W ? 1 : 0, out);
   return hipGetLastError();
 }

@@ -91,6 +91,8 @@ lda_status setup_device(lda_handle *h, const lda_options *o) {
   }
   p.grid_docs = std::max(1, cus * 8);
   set_doc_batches(p);
+  if (!stat_slots_fit(p)) return fail(h, LDA_E_DEVICE, "more compute units than the statistics have slots for");
+  LDA_TRY(dalloc(h, &h->d.wave_stats, size_t(kFoldBlocks) * kWaveSlots));
   return LDA_OK;
 }
 
@@ -199,12 +201,8 @@ lda_status create_device(lda_handle *h, const lda_options *o, const int32_t *wor
     LDA_TRY(dalloc(h, &d.heavy_docs, heavy.size()));
     LDA_TRY(upload(h, d.heavy_docs, heavy));
   }
-  {
-    const std::vector<uint32_t> batches = light_batches(L.region, p.light_begin, int64_t(p.grid_regions) * 2);
-    p.n_light_batches = int32_t(batches.size() - 1);
-    LDA_TRY(dalloc(h, &d.light_batch, batches.size()));
-    LDA_TRY(upload(h, d.light_batch, batches));
-  }
+  int64_t partials = 0;
+  LDA_TRY(make_units(h, L.region, d.region, p, &d.unit, &d.light_batch, &partials));
   LDA_TRY(dalloc(h, &d.split, L.split.size()));
   LDA_TRY(dalloc(h, &d.z_w, n));
   LDA_TRY(dalloc(h, &d.skip_bits, skip_words(int64_t(n))));
@@ -229,7 +227,7 @@ lda_status create_device(lda_handle *h, const lda_options *o, const int32_t *wor
   LDA_TRY(dalloc(h, &d.wskip, size_t(L.n_present)));
   LDA_TRY(dalloc(h, &d.counters, kCounters));
   LDA_TRY(dalloc(h, &h->stats_base, size_t(kStatSlots) * kStatsPerIter));
-  LDA_TRY(dalloc(h, &d.ll_part, size_t(L.n_regions)));
+  LDA_TRY(dalloc(h, &d.ll_part, size_t(partials)));
   // large K: sparse words' per-word records from their rows and a list of
   // the topics with the largest beta/den[k] (sorted each iteration)
   p.sparse_pre = L.K >= 4096 ? 1 : 0;
@@ -461,7 +459,8 @@ lda_status lda_iterate(lda_handle *h, int32_t n_iters, lda_iter_stats *stats) {
       if (ev) HIP_TRY(h, hipEventRecord(ev[2], h->stream));
       LDA_TRY(run_sampler(h, d, h->p, t));
       if (ev) HIP_TRY(h, hipEventRecord(ev[3], h->stream));
-      HIP_TRY(h, launch_rebuild(d, h->p, h->stream));
+      const StatSlots slots = stat_slots(h->p, t);
+      HIP_TRY(h, launch_rebuild(d, h->p, h->stream, &slots));
       if (ev) HIP_TRY(h, hipEventRecord(ev[4], h->stream));
       h->iteration++;
     }

@@ -143,6 +143,7 @@ struct DevState {
   uint32_t *doc_off, *dt_word, *dt_key, *dt_wpos, *word_off;
   uint2 *wt_kr;       // per word-ordered token: (input index = RNG key, D-row offset of its document)
   uint32_t *region;   // 3 per region
+  uint32_t *unit;     // 3 per unit of the sampler (sampler_units); the region table itself when no region is cut
   uint32_t *light_batch; // light regions per batch of the light sampler: [n_light_batches + 1], from p.light_begin
   uint32_t *heavy_docs;  // documents longer than kHeavyDoc tokens (one workgroup each in the doc kernels)
   uint8_t *split;     // per dense word
@@ -163,7 +164,8 @@ struct DevState {
   // scheduler counters and statistics
   uint32_t *counters;           // [kCounters]
   unsigned long long *stats;    // [8]
-  double *ll_part;              // [n_regions]
+  unsigned long long *wave_stats; // [kFoldBlocks][kWaveSlots]: per wave of the samplers and the doc pass (StatSlots)
+  double *ll_part;              // [n_units + n_light_batches] (large K: [n_regions])
   double *ll_out;               // [1]
   // large K only (the tiled sampler): per-workgroup slices of max_region
   // entries carrying a token's S' part, C1 and split chunk between passes,
@@ -206,6 +208,7 @@ struct Params {
   int32_t always_skip_test;  // steps 2-3 every iteration instead of when they pay (lda_options)
   uint32_t key_base;     // out-of-core chunks: input index of the chunk's first doc-ordered token (else 0)
   int32_t n_heavy;       // entries of heavy_docs
+  int64_t n_units;       // units of the sampler and the LLPT kernel: the regions before light_begin, cut
   int64_t light_begin;   // regions [light_begin, n_regions): light words, drawn by single waves
   int32_t n_light_batches;  // entries of light_batch, less one
   int32_t doc_marks_ok;  // the document-ordered bitmap is usable: keys are document positions, regular sampler
@@ -216,12 +219,13 @@ struct Params {
 // Workgroups of the D rebuild by tables of K counts (k_rebuild_d) and of the
 // doc pass: no more waves than documents (a wave without a document still
 // asks every counter), rounded to whole sets of one workgroup per range.
-inline uint32_t doc_grid(int32_t most, int32_t M, int32_t waves) {
-  const int64_t wg = (int64_t(M) + waves - 1) / waves;
-  return uint32_t(std::max<int64_t>(kXcds, std::min<int64_t>(most, (wg + kXcds - 1) / kXcds * kXcds)));
+__host__ __device__ inline uint32_t doc_grid(int32_t most, int32_t M, int32_t waves) {
+  const int32_t wg = (M + waves - 1) / waves, set = (wg + kXcds - 1) / kXcds * kXcds;
+  const int32_t g = set < most ? set : most;
+  return uint32_t(g > kXcds ? g : kXcds);
 }
 inline uint32_t rebuild_grid(const Params &p) { return doc_grid(std::max(1, p.grid_docs / 2), p.M, p.doc_waves); }
-inline uint32_t doc_pass_grid(const Params &p) { return doc_grid(p.grid_docs, p.M, p.doc_waves); }
+__host__ __device__ inline uint32_t doc_pass_grid(const Params &p) { return doc_grid(p.grid_docs, p.M, p.doc_waves); }
 // Documents per counter atomic.  Large corpora: 32 in the doc pass and 24 in
 // the D rebuild (a smaller window of documents in flight keeps more of its
 // topic gathers in the caches).  Small corpora: few enough that every wave of
@@ -246,6 +250,21 @@ constexpr int kDocStripes = kXcds;  // counters of the doc pass
 enum { ST_SKIP3 = 0, ST_SKIP_AFTER_S = 1, ST_SAMPLED = 2, ST_NNZ = 3, ST_REGIONS = 4, ST_DENSE_REGIONS = 5, ST_ERRORS = 6,
        ST_ROW_BYTES = 7, ST_MARKS = 8, ST_TEST_RAN = 9 };
 constexpr int kStatsPerIter = 16;
+
+// The statistics of the samplers and the doc pass: every wave stores its own
+// sums and a later launch adds them up.  Atomics on the statistics' one cache
+// line cost 55,000 of them, 0.6 ms, an iteration at every corpus size.
+enum { WV_SAMPLED, WV_AFTER_S, WV_NNZ, WV_REGIONS, WV_DENSE_REGIONS, WV_ROW_BYTES, WV_SKIP3 };
+constexpr int kFoldBlocks = 7;  // one per statistic
+constexpr size_t kWaveSlots = size_t(1) << 15;
+// Waves that store statistics in iteration t: the main (or tiled) sampler's
+// slots come first, then the light sampler's; the doc pass's have a row of
+// their own.
+struct StatSlots {
+  int32_t main, light, doc;  // waves (0: not launched)
+  int32_t light0;            // the light sampler's first slot
+  uint32_t t;
+};
 
 // Kernel launchers (all asynchronous on `s`); return hipGetLastError().
 hipError_t launch_init_topics(const DevState &d, const Params &p, hipStream_t s);
@@ -279,6 +298,22 @@ inline int64_t light_region_start(const std::vector<uint32_t> &region, int K, bo
   while (r > 0 && region[3 * size_t(r - 1) + 2] - region[3 * size_t(r - 1) + 1] <= kLightTokens) --r;
   return r;
 }
+// The regions before light_begin cut into the units that workgroups of the
+// sampler take, in the regions' order: (word, begin, end), bit 31 of the word
+// set in a unit that continues a region.  A region of up to 10,000 tokens keeps
+// one workgroup busy for a hundred batches, so a small corpus is cut finer:
+// into about two units per resident workgroup, but not below the tokens that
+// give every wave a batch, nor below twice the K topics that a unit's W^ row
+// costs (50,000 tokens at K = 16: sampler 0.146 -> 0.045 ms, 610,000 at K = 101
+// 0.324 -> 0.131; four units instead of two, or a least unit of K / 2, cost 9M
+// tokens at K = 2,000 10%).  Draws do not depend on the cut.
+constexpr uint32_t kUnitContinues = 0x80000000u;
+std::vector<uint32_t> sampler_units(const std::vector<uint32_t> &region, int64_t light_begin, int64_t n, int32_t K,
+                                    int64_t workgroups, int32_t threads);
+__host__ __device__ inline int64_t sampler_workgroups(const Params &p) {
+  const int64_t w = int64_t(p.grid_regions) * kBlock / (p.sampler_block > 0 ? p.sampler_block : kBlock);
+  return w > 0 ? w : 1;
+}
 // The light regions cut into batches of consecutive word-ordered tokens, as
 // offsets from light_begin: at most 64 tokens each, fewer (down to 16) when
 // that would leave the light sampler's waves without a batch.
@@ -289,8 +324,34 @@ size_t tiled_lds_bytes(int K, int kt);
 constexpr int kTiledThreads = 1024;
 // Workgroups of the tiled sampler and LLPT kernel (one per CU: their LDS fills
 // a CU) and of k_topic_hist; the scratch slices are sized for these grids.
-inline int tiled_grid(const Params &p) { return p.grid_regions / 8 > 0 ? p.grid_regions / 8 : 1; }
+__host__ __device__ inline int tiled_grid(const Params &p) { return p.grid_regions / 8 > 0 ? p.grid_regions / 8 : 1; }
 inline int topic_hist_grid(const Params &p) { return tiled_grid(p); }
+// Workgroups of the main (or tiled) and of the light sampler (at most 16
+// one-wave workgroups per CU; grid_regions is 8 per CU), and the statistics
+// slots of an iteration's launches.
+__host__ __device__ inline int32_t sampler_grid(const Params &p) {
+  if (p.big_k) return tiled_grid(p);
+  const int64_t w = sampler_workgroups(p);
+  return int32_t(p.n_units < w ? p.n_units : w);
+}
+__host__ __device__ inline int32_t light_grid(const Params &p) {
+  return p.n_light_batches < 2 * p.grid_regions ? p.n_light_batches : 2 * p.grid_regions;
+}
+__host__ __device__ inline StatSlots stat_slots(const Params &p, uint32_t t) {
+  StatSlots s;
+  s.main = sampler_grid(p) * (p.sampler_block / 64);
+  s.light0 = s.main;
+  s.light = light_grid(p);
+  s.doc = p.no_skip ? 0 : int32_t(doc_pass_grid(p)) * p.doc_waves;
+  s.t = t;
+  return s;
+}
+// Whether every launch's waves have a slot (grids follow the device's CUs).
+inline bool stat_slots_fit(const Params &p) {
+  const int64_t main = p.big_k ? int64_t(tiled_grid(p)) : sampler_workgroups(p);
+  return main * (p.sampler_block / 64) + 2 * int64_t(p.grid_regions) <= int64_t(kWaveSlots) &&
+         int64_t(std::max(p.grid_docs, kXcds)) * p.doc_waves <= int64_t(kWaveSlots);
+}
 // The W rebuild by bitmap, with T from a histogram of the topics (and its
 // scratch rows), from this many topics on: below it a workgroup's tables of K
 // counts are small enough to keep several workgroups on a CU.
@@ -298,8 +359,10 @@ constexpr int kWBitsK = 4096;
 inline bool w_bits(const Params &p) { return p.big_k || p.K >= kWBitsK; }
 // The count rebuild (Sec. 4.3): launch_rebuild = launch_zero_split, then
 // launch_rebuild_w and launch_rebuild_d.
-hipError_t launch_rebuild(const DevState &d, const Params &p, hipStream_t s);
-hipError_t launch_zero_split(const DevState &d, const Params &p, hipStream_t s);
+// slots: also add up the statistics of the samplers and the doc pass that ran.
+hipError_t launch_rebuild(const DevState &d, const Params &p, hipStream_t s, const StatSlots *slots = nullptr);
+hipError_t launch_zero_split(const DevState &d, const Params &p, hipStream_t s, const StatSlots *slots = nullptr);
+hipError_t launch_fold_stats(const DevState &d, const StatSlots &slots, hipStream_t s);
 hipError_t launch_rebuild_w(const DevState &d, const Params &p, hipStream_t s);
 hipError_t launch_rebuild_d(const DevState &d, const Params &p, hipStream_t s);
 hipError_t launch_loglik(const DevState &d, const Params &p, hipStream_t s);
