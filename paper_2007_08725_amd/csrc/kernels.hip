@@ -309,7 +309,7 @@ __device__ void write_word_records(const DevState &d, const Params &p, int r, co
   d.wskip[r] = sr;
 }
 
-// Large K: the sum over all topics of beta/den[k] (one workgroup, a fixed
+// K from 4,096 on: the sum over all topics of beta/den[k] (one workgroup, a fixed
 // order), for the sparse words' sums in k_word_pre_wave.
 __global__ __launch_bounds__(kBlock) void k_beta_sum(DevState d, Params p) {
   __shared__ double red[kBlock / kWave];
@@ -326,14 +326,15 @@ __global__ __launch_bounds__(kBlock) void k_beta_sum(DevState d, Params p) {
 // workgroup, no workgroup barriers.  Lane l takes topics l, l + 64, ...: its top values, then a merge
 // across the wave by exchanges at distances 32 down to 1 (the top set is
 // unique under `better`, so every lane ends with the same list), then Q' and
-// the sum of W^[v] per lane in topic order, summed over the wave.  Below
-// K = 4,096 a sparse row is spread into the wave's table of K counts first.
-// From K = 4,096 on (p.sparse_pre) a sparse word's W^ is beta/den[k] outside
+// the sum of W^[v] per lane in topic order, summed over the wave.  Without
+// p.sparse_pre a sparse row is spread into the wave's table of K counts first.
+// With it (use_topic_list) a sparse word's W^ is beta/den[k] outside
 // its row: its top values come from the row and from the first topics
 // outside the row in the list of all topics by ascending T (descending
 // beta/den[k], lowest id first on ties), 64 candidates of the list at a time;
 // its sums from the sum of beta/den[k] over all topics, corrected on the
-// row.  Should the list run out, every topic is scanned.
+// row.  Should the list run out, every topic is scanned.  The words from
+// p.small_begin on are then k_word_pre_small's.
 __device__ __forceinline__ void wave_top_merge(TopN &t) {
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) {
@@ -360,10 +361,10 @@ __device__ __forceinline__ WordTop word_top_of(const TopN &t) {
   return top;
 }
 __global__ __launch_bounds__(kBlock) void k_word_pre_wave(DevState d, Params p) {
-  extern __shared__ uint16_t wtab[];  // below K = 4,096: [kBlock / kWave][(K + 1) & ~1]
+  extern __shared__ uint16_t wtab[];  // without p.sparse_pre: [kBlock / kWave][(K + 1) & ~1]
   const int K = p.K, lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int r = blockIdx.x * (kBlock / kWave) + wave;
-  if (r >= p.n_present) return;  // a whole wave; nothing below waits on the workgroup
+  if (r >= (p.sparse_pre ? p.small_begin : p.n_present)) return;  // a whole wave; nothing below waits on the workgroup
   const bool dense = r < p.n_dense;
   const int32_t *wrow = dense ? d.w_dense + size_t(r) * size_t(K) : nullptr;
   const uint32_t *ents = nullptr;
@@ -478,6 +479,125 @@ __global__ __launch_bounds__(kBlock) void k_word_pre_wave(DevState d, Params p) 
   q = group_sum<kWave>(q);
   sw = group_sum<kWave>(sw);
   if (lane == 0) write_word_records(d, p, r, top, q, sw);
+}
+
+// The topic list (the p.top_list topics of least T, ascending, lowest id first
+// on ties) and the sum of beta/den[k], for K below 4,096: a topic's place is
+// the number of topics before it, counted by four lanes over T in LDS (6 us
+// at K = 1,000; the radix sort that large K uses takes five launches).  The
+// last workgroup sums beta/den[k].
+constexpr int kListTopics = kBlock / 4;  // topics per workgroup
+__global__ __launch_bounds__(kBlock) void k_topic_list(DevState d, Params p) {
+  extern __shared__ uint32_t ldsu[];  // [K rounded up to 4]
+  __shared__ double red[kBlock / kWave];
+  const int K = p.K, tid = threadIdx.x;
+  if (int(blockIdx.x) * kListTopics >= K) {
+    double s = 0.0;
+    for (int k = tid; k < K; k += kBlock) s += d.bden[k];
+    s = block_sum(s, red);
+    if (tid == 0) d.beta_sum[0] = s;
+    return;
+  }
+  const int K4 = (K + 3) & ~3;
+  for (int k = tid; k < K4; k += kBlock) ldsu[k] = k < K ? d.T[k] : 0xFFFFFFFFu;  // the padding is after every topic
+  __syncthreads();
+  const uint32_t k = blockIdx.x * uint32_t(kListTopics) + uint32_t(tid / 4);
+  if (k >= uint32_t(K)) return;
+  const uint32_t t = ldsu[k];
+  uint32_t before = 0;
+  const uint4 *t4 = reinterpret_cast<const uint4 *>(ldsu);
+  for (uint32_t q = uint32_t(tid & 3); q < uint32_t(K4 / 4); q += 4u) {
+    const uint4 v = t4[q];
+    const uint32_t j = 4u * q;
+    before += uint32_t(v.x < t || (v.x == t && j < k)) + uint32_t(v.y < t || (v.y == t && j + 1u < k)) +
+              uint32_t(v.z < t || (v.z == t && j + 2u < k)) + uint32_t(v.w < t || (v.w == t && j + 3u < k));
+  }
+  before += uint32_t(__shfl_xor(int(before), 1, 4));
+  before += uint32_t(__shfl_xor(int(before), 2, 4));
+  if ((tid & 3) == 0 && before < uint32_t(p.top_list)) d.topic_order[before] = k;
+}
+
+// The per-word records of the small sparse words (at most kSmallWord tokens,
+// the words from p.small_begin on) from their row and the topic list, as
+// k_word_pre_wave makes them, by 16 lanes per word.  A whole wave per word
+// spent most of its instructions on merging 64 lanes' top lists: a million
+// words took 2.1 ms by tables of K = 1,000 counts.  A row has
+// at most 64 entries, so the list (512 topics, or all) holds enough topics
+// outside it.
+__global__ __launch_bounds__(kBlock) void k_word_pre_small(DevState d, Params p) {
+  __shared__ uint16_t s_topic[kBlock / kGroup][kSmallWord];
+  const int K = p.K, li = threadIdx.x % kGroup, g = threadIdx.x / kGroup;
+  const int grp = (threadIdx.x & (kWave - 1)) / kGroup;  // of the wave
+  const int word = p.small_begin + int(blockIdx.x) * (kBlock / kGroup) + g;
+  const int r = min(word, p.n_present - 1), s = r - p.n_dense;
+  const uint32_t nnz = d.ws_nnz[s];
+  const uint32_t *ents = d.ws_ent + d.ws_cap[s];
+  TopN t;
+#pragma unroll
+  for (int q = 0; q < kTop; ++q) {
+    t.v[q] = -1.0;
+    t.k[q] = 0xFFFFFFFFu;
+  }
+  double snz = 0.0, sb = 0.0;
+  uint32_t ent[kSmallWord / kGroup];
+#pragma unroll
+  for (int u = 0; u < int(kSmallWord) / kGroup; ++u) {
+    const uint32_t q = uint32_t(li + u * kGroup);
+    ent[u] = q < nnz ? ents[q] : 0u;
+  }
+#pragma unroll
+  for (int u = 0; u < int(kSmallWord) / kGroup; ++u) {
+    const uint32_t q = uint32_t(li + u * kGroup);
+    if (q < nnz) {
+      const uint32_t k = ent[u] >> 16;
+      const double w = what(ent[u] & 0xFFFFu, p.beta, d.den[k]);
+      top_insert(t, w, k);
+      snz += w;
+      sb += d.bden[k];
+      s_topic[g][q] = uint16_t(k);
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // a wave's LDS accesses run in order
+  const uint32_t want = uint32_t(min(kTop, K - int(nnz)));
+  uint32_t found = 0;
+  for (int i0 = 0; i0 < p.top_list && __ballot(found < want) != 0ull; i0 += kGroup) {
+    const int i = i0 + li;
+    bool cand = false;
+    uint32_t k = 0;
+    if (i < p.top_list && found < want) {
+      k = d.topic_order[i];
+      uint32_t lo = 0, hi = nnz;  // first entry whose topic is >= k
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (s_topic[g][mid] < k) lo = mid + 1;
+        else hi = mid;
+      }
+      cand = !(lo < nnz && s_topic[g][lo] == k);
+    }
+    const uint32_t m = uint32_t(__ballot(cand) >> (grp * kGroup)) & kGroupMask;
+    const uint32_t rank = uint32_t(__popc(m & ((1u << li) - 1u)));
+    if (cand && rank < want - found) top_insert(t, d.bden[k], k);
+    found += min(uint32_t(__popc(m)), want - found);
+  }
+#pragma unroll
+  for (int o = kGroup / 2; o > 0; o >>= 1) {
+    double pv[kTop];
+    uint32_t pk[kTop];
+#pragma unroll
+    for (int q = 0; q < kTop; ++q) {
+      pv[q] = __shfl_xor(t.v[q], o, kWave);
+      pk[q] = uint32_t(__shfl_xor(int(t.k[q]), o, kWave));
+    }
+#pragma unroll
+    for (int q = 0; q < kTop; ++q) top_insert(t, pv[q], pk[q]);
+  }
+  snz = group_sum<kGroup>(snz);
+  sb = group_sum<kGroup>(sb);
+  if (li == 0 && word < p.n_present) {
+    const WordTop top = word_top_of(t);
+    const double sw = (d.beta_sum[0] - sb) + snz;
+    write_word_records(d, p, r, top, p.two_branch ? p.alpha * sw : p.alpha * (sw - top.a1), sw);
+  }
 }
 
 // Steps 2 and 3: per document, C1 = D[d][K1], C2 = D[d][K2], u, M, S_est and
@@ -3401,16 +3521,30 @@ hipError_t launch_beta_sum(const DevState &d, const Params &p, hipStream_t s) {
 hipError_t launch_word_pre(const DevState &d, const Params &p, hipStream_t s) {
   if (p.sparse_pre) {
     // the topic list and the sum of beta/den[k] follow the current T
-    size_t bytes = d.topic_tmp_bytes;
-    hipError_t err = sort_pairs_u32(d.topic_tmp, bytes, d.T, d.topic_keys, d.topic_iota, d.topic_order, p.K, 32, s);
+    hipError_t err;
+    if (p.K < kWBitsK) {
+      const uint32_t grid = uint32_t((p.K + kListTopics - 1) / kListTopics) + 1u;
+      hipLaunchKernelGGL(k_topic_list, dim3(grid), dim3(kBlock), sizeof(uint32_t) * size_t((p.K + 3) & ~3), s, d, p);
+      err = hipGetLastError();
+    } else {
+      size_t bytes = d.topic_tmp_bytes;
+      err = sort_pairs_u32(d.topic_tmp, bytes, d.T, d.topic_keys, d.topic_iota, d.topic_order, p.K, 32, s);
+      if (err == hipSuccess) err = launch_beta_sum(d, p, s);
+    }
     if (err != hipSuccess) return err;
-    err = launch_beta_sum(d, p, s);
-    if (err != hipSuccess) return err;
+    if (p.small_begin < p.n_present) {
+      const int per = kBlock / kGroup;
+      hipLaunchKernelGGL(k_word_pre_small, dim3(uint32_t((p.n_present - p.small_begin + per - 1) / per)), dim3(kBlock),
+                         0, s, d, p);
+      if ((err = hipGetLastError()) != hipSuccess) return err;
+    }
   }
-  // below K = 4,096 a table of K 16-bit counts per wave (at most 32 KB), for
-  // sparse rows only (out of core every word is dense, at every K)
+  // without the topic list a table of K 16-bit counts per wave (K below
+  // 4,096: at most 32 KB), for sparse rows only
   const size_t lds = p.sparse_pre || p.n_dense >= p.n_present ? 0 : sizeof(uint16_t) * size_t((p.K + 1) & ~1) * (kBlock / kWave);
-  const uint32_t grid = uint32_t((p.n_present + kBlock / kWave - 1) / (kBlock / kWave));
+  const int32_t words = p.sparse_pre ? p.small_begin : p.n_present;
+  if (words == 0) return hipSuccess;
+  const uint32_t grid = uint32_t((words + kBlock / kWave - 1) / (kBlock / kWave));
   hipLaunchKernelGGL(k_word_pre_wave, dim3(grid), dim3(kBlock), lds, s, d, p);
   return hipGetLastError();
 }

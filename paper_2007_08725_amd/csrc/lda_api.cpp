@@ -228,15 +228,20 @@ lda_status create_device(lda_handle *h, const lda_options *o, const int32_t *wor
   LDA_TRY(dalloc(h, &d.counters, kCounters));
   LDA_TRY(dalloc(h, &h->stats_base, size_t(kStatSlots) * kStatsPerIter));
   LDA_TRY(dalloc(h, &d.ll_part, size_t(partials)));
-  // large K: sparse words' per-word records from their rows and a list of
-  // the topics with the largest beta/den[k] (sorted each iteration)
-  p.sparse_pre = L.K >= 4096 ? 1 : 0;
+  // sparse words' per-word records from their rows and a list of the topics
+  // with the largest beta/den[k] (made each iteration)
+  p.sparse_pre = use_topic_list(L.K, L.n_present - L.n_dense) ? 1 : 0;
   p.top_list = std::min(L.K, 512);
+  p.small_begin = L.n_dense;  // words are numbered by descending count
+  while (p.small_begin < L.n_present && L.word_off[size_t(p.small_begin) + 1] - L.word_off[size_t(p.small_begin)] > kSmallWord)
+    ++p.small_begin;
   if (p.sparse_pre) {
     LDA_TRY(dalloc(h, &d.topic_order, size_t(L.K)));
+    LDA_TRY(dalloc(h, &d.beta_sum, 1));
+  }
+  if (p.sparse_pre && L.K >= kWBitsK) {
     LDA_TRY(dalloc(h, &d.topic_keys, size_t(L.K)));
     LDA_TRY(dalloc(h, &d.topic_iota, size_t(L.K)));
-    LDA_TRY(dalloc(h, &d.beta_sum, 1));
     std::vector<uint32_t> iota(static_cast<size_t>(L.K));
     std::iota(iota.begin(), iota.end(), 0u);
     LDA_TRY(upload(h, d.topic_iota, iota));

@@ -174,7 +174,7 @@ struct DevState {
   uint32_t *ts_c1, *ts_code;
   TiledRec *ts_list;
   uint32_t *hist_rows;  // large K: the rows of k_topic_hist
-  // large K (p.sparse_pre): topics by ascending T (descending beta/den[k]),
+  // p.sparse_pre: topics by ascending T (descending beta/den[k]),
   // their sort buffers, and the sum of beta/den[k] over all topics
   uint32_t *topic_order, *topic_keys, *topic_iota;
   void *topic_tmp;
@@ -202,7 +202,8 @@ struct Params {
   int32_t max_region;    // tokens of the largest region
   int32_t doc_waves;     // waves per workgroup of the doc pass and the D rebuild (LDS tables of K entries per wave)
   uint32_t doc_batch, rebuild_batch;  // documents a wave takes per counter atomic (doc pass, D rebuild)
-  int32_t sparse_pre;    // per-word precompute of sparse words from their row and a topic list (large K)
+  int32_t sparse_pre;    // per-word precompute of sparse words from their row and a topic list (use_topic_list)
+  int32_t small_begin;   // sparse words [small_begin, n_present) have at most kSmallWord tokens (with sparse_pre)
   int32_t top_list;      // length of that topic list
   int32_t skip_marks;    // 0 auto, 1 word-ordered bitmap, 2 document-ordered bitmap (lda_options)
   int32_t always_skip_test;  // steps 2-3 every iteration instead of when they pay (lda_options)
@@ -356,6 +357,15 @@ inline bool stat_slots_fit(const Params &p) {
 // scratch rows), from this many topics on: below it a workgroup's tables of K
 // counts are small enough to keep several workgroups on a CU.
 constexpr int kWBitsK = 4096;
+// The per-word precompute of sparse words from their rows and a list of the
+// topics with the largest beta/den[k], instead of K topics per word: from
+// K = 4,096 on, where a wave's table of K counts gets large, and below it when
+// the sparse words' tables would be at least 4M topics together (about 40 us;
+// the list is a launch of its own, 6 us at K = 1,000).
+constexpr uint32_t kSmallWord = 64;
+inline bool use_topic_list(int32_t K, int64_t sparse_words) {
+  return K >= kWBitsK || sparse_words * K >= (int64_t(4) << 20);
+}
 inline bool w_bits(const Params &p) { return p.big_k || p.K >= kWBitsK; }
 // The count rebuild (Sec. 4.3): launch_rebuild = launch_zero_split, then
 // launch_rebuild_w and launch_rebuild_d.
