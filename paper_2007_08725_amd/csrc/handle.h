@@ -150,9 +150,9 @@ inline lda_status sort_pairs(lda_handle *h, const uint32_t *keys_in, uint32_t *k
 
 
 // The sampler's units (sampler_units) and light batches of a region table (on
-// the device as d_region), and the LLPT partials they need.  The tiled sampler
-// takes whole regions (a unit's W^ row costs it three tile fills), and so does
-// everything when the cut would pass the fixed array of lda_loglik_noalloc.
+// the device as d_region), and the LLPT partials they need.  Whole
+// regions at large K, whose LLPT kernel walks regions, and when the cut would
+// pass the fixed array of lda_loglik_noalloc.
 inline lda_status make_units(lda_handle *h, const std::vector<uint32_t> &region, uint32_t *d_region, Params &p,
                              uint32_t **unit, uint32_t **light_batch, int64_t *partials) {
   const std::vector<uint32_t> batches = light_batches(region, p.light_begin, int64_t(p.grid_regions) * 2);

@@ -1572,7 +1572,7 @@ __device__ __forceinline__ void store_stats(const DevState &d, uint32_t slot, bo
 
 // The sampler for workgroups of NB threads (NB / 64 waves); every wave works
 // on its own batches, so NB only changes how many waves share a region's W^
-// row in LDS (larger workgroups for large K, where LDS bounds the residency).
+// row in LDS.
 // It takes the units (sampler_units) of the regions before p.light_begin; the
 // light regions are k_sampler_light's.
 template <int NB>
@@ -1778,14 +1778,6 @@ __global__ __launch_bounds__(256, 7) void k_sampler(DevState d, Params p, uint32
                                                  unsigned long long *__restrict__ stats) {
   sampler_body<256>(d, p, t, stats);
 }
-__global__ __launch_bounds__(512, 4) void k_sampler_512(DevState d, Params p, uint32_t t,
-                                                     unsigned long long *__restrict__ stats) {
-  sampler_body<512>(d, p, t, stats);
-}
-__global__ __launch_bounds__(1024, 4) void k_sampler_1024(DevState d, Params p, uint32_t t,
-                                                       unsigned long long *__restrict__ stats) {
-  sampler_body<1024>(d, p, t, stats);
-}
 // The light regions (Sec. 5.1: light units to wavefronts): words of at most
 // kLightTokens tokens, the suffix [p.light_begin, n_regions) of the region
 // table.  A wave takes batches of consecutive light words (d.light_batch: at
@@ -1945,24 +1937,10 @@ __global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, u
 }
 
 // ---------------------------------------------------------- large K ----
-// When the fp64 W^' row does not fit in LDS (K above about 17,000 topics,
-// up to 32,768), the topics are split in two tiles, [0, KT) and [KT, K]
-// (topic K is the padding of D rows), and a region is walked three times:
-//   pass 0, tile 0: per token the S' terms of topics below KT and C1;
-//   pass 1, tile 1: the S' terms of the other topics, then the draw (Eq. 5);
-//                   draws in M, in the tile-1 part of S' or in a tile-1 Q'
-//                   block finish here, the others are recorded;
-//   pass 2, tile 0: the recorded draws finish, over the list of their
-//                   tokens that pass 1 keeps.
-// A row is in ascending topic order, so pass 0 reads its chunks only up to
-// the first one that reaches topic KT (the split chunk, kept per token),
-// pass 1 only from there on, and pass 2's S' walk ends there: every chunk
-// left out holds only terms of the other tile, which add exact zeros.
-// The canonical order [K1 | S' ascending | Q' ascending] is unchanged: the
-// tile-0 part of S' precedes the tile-1 part.  A 16-lane group draws one
-// token at a time and reads its D row in chunks of kChunk slots; entries of
-// the other tile read a zero.  Per-token results between passes live in a
-// per-workgroup slice of global scratch.
+// When the fp64 W^ row does not fit in LDS (K above about 17,000 topics, up to
+// 32,768), the LLPT kernel (k_loglik_tiled) splits the topics in two tiles,
+// [0, KT) and [KT, K] (topic K is the padding of D rows), and walks a region
+// twice.  Entries of the other tile read a zero.
 struct TileState {
   const double *wt;  // the tile: W^' of topics [base, base + KT), zeros past the tile's end
   uint32_t base, kt;
@@ -2002,94 +1980,6 @@ __device__ __forceinline__ double run_sum_tile(const uint32_t (&r)[kMaxRun], con
   for (int i = 0; i < kMaxRun; ++i) s = __builtin_fma(double(r[i] & 0xFFFFu), wt_of(ts, r[i]), s);
   return s;
 }
-
-// The last step of an S' draw in a tile: in the chunk that holds x (this
-// lane's run r, lane sum s, inclusive scan incl, the chunk's terms starting
-// at base), the lane whose run holds x and then the entry in it.
-__device__ uint32_t walk_finish(const uint32_t (&r)[kMaxRun], double s, double incl, const TileState &ts,
-                                double base, double x, int grp, int li, uint32_t *__restrict__ hand) {
-  const int sel = run_lane(s, incl, base, x, grp);
-  const double start = base + __shfl(incl - s, sel, kGroup);
-  if (li == sel) {
-#pragma unroll
-    for (int i = 0; i < kMaxRun; ++i) hand[i] = r[i];
-  }
-  __builtin_amdgcn_wave_barrier();
-  const uint32_t mine = li < kMaxRun ? hand[li] : 0u;
-  const double term = li < kMaxRun ? double(mine & 0xFFFFu) * wt_of(ts, mine) : 0.0;
-  return pick_segment(mine >> 16, term, start, x, grp);
-}
-
-// tile_walk over two chunks already in registers (runs r, lane sums t).
-__device__ uint32_t walk_pair(const uint32_t (&r)[2][kMaxRun], const double (&t)[2], const TileState &ts, double base,
-                              double x, int grp, int li, uint32_t *__restrict__ hand) {
-  double at = base;
-  int pick = -1, last = -1;
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const double total = __shfl(row_incl_scan(t[c]), kGroup - 1, kGroup);
-    if (pick < 0) {
-      if (total > 0.0) {
-        last = c;
-        at = base;
-      }
-      if (x < base + total) pick = c;
-      else base += total;
-    }
-  }
-  if (pick < 0) {
-    pick = last;  // rounding: x at or past the end of the tile's terms
-    base = at;
-  }
-  if (pick < 0) return uint32_t(-1);
-  const uint32_t(&rp)[kMaxRun] = pick == 0 ? r[0] : r[1];
-  const double sp = pick == 0 ? t[0] : t[1];
-  return walk_finish(rp, sp, row_incl_scan(sp), ts, base, x, grp, li, hand);
-}
-
-// The S' draw inside one tile: the entry whose segment holds x, the tile's
-// terms starting at `base`; chunks [ch0, nch) are walked again in order (the
-// others hold no term of the tile).  When
-// rounding leaves x past the tile's terms, the last positive term is taken.
-__device__ uint32_t tile_walk(const uint32_t *__restrict__ row, uint32_t slots, const TileState &ts, double base,
-                              double x, uint32_t pad, int grp, int li, uint32_t *__restrict__ hand, uint32_t ch0,
-                              uint32_t nch) {
-  uint32_t r[kMaxRun];
-  int last_pos = -1;
-  double last_base = base;
-  uint32_t pick = nch;
-  double s = 0.0, incl = 0.0;
-  uint32_t rn[kMaxRun];
-  load_run_masked(row, ch0, slots, li, pad, rn);
-  for (uint32_t ch = ch0; ch < nch; ++ch) {
-#pragma unroll
-    for (int i = 0; i < kMaxRun; ++i) r[i] = rn[i];
-    if (ch + 1 < nch) load_run_masked(row, ch + 1, slots, li, pad, rn);  // the next chunk's loads, in flight meanwhile
-    s = run_sum_tile(r, ts);
-    incl = row_incl_scan(s);
-    const double total = __shfl(incl, kGroup - 1, kGroup);
-    if (total > 0.0) {
-      last_pos = int(ch);
-      last_base = base;
-    }
-    if (x < base + total) {
-      pick = ch;
-      break;
-    }
-    base += total;
-  }
-  if (pick == nch) {
-    // rounding: x at or past the end of the tile's terms
-    if (last_pos < 0) return uint32_t(-1);
-    pick = uint32_t(last_pos);
-    base = last_base;
-    load_run_masked(row, pick, slots, li, pad, r);
-    s = run_sum_tile(r, ts);
-    incl = row_incl_scan(s);
-  }
-  return walk_finish(r, s, incl, ts, base, x, grp, li, hand);
-}
-
 
 // Fills the tile [base, base + len) of the region's word (zeros elsewhere,
 // at K1 and at the padding topic K).  Each thread issues the loads of
@@ -2160,368 +2050,650 @@ __device__ void fill_tile(const DevState &d, const Params &p, uint32_t v, uint32
   __syncthreads();
 }
 
-// A token's records for one pass of the tiled sampler.
-struct TiledTok {
-  uint32_t sk, rec, cn;
-  uint2 kr;
+constexpr int kTiledBlock = 1024;           // threads per workgroup of k_loglik_tiled (16 waves)
+constexpr int kTiledAhead = 2;              // chunks whose loads a group issues together
+
+// ------------------------------------------------- certified draws ----
+// The sampler with the W^' row in single precision.  The row is what limits
+// the residency at large K (80 KB of fp64 at K = 10,000; 256 KB at 32,768,
+// more than a CU has) and its gathers are the sampler's LDS traffic.  Half the
+// size, it fits one workgroup at every K up to 32,768, and three workgroups
+// of 512 threads at K = 10,000.
+//
+// No draw depends on the single precision.  S' and its prefixes are sums of
+// nonnegative terms D[d][k] * W^[v][k]; a lane adds its run of 8 terms in
+// fp32 (W^ rounded once, each fused multiply-add once) and everything else is
+// fp64, so every prefix of S' is off by at most kEps of itself, kEps being a
+// little over 9 * 2^-24.  With x = u*Z the draw is decided only when x is
+// further than the bound on its own error and the edge's from both edges of
+// the chosen segment; otherwise (2e-4 of the tokens at K = 1,000, 2e-3 at
+// 10,000, 6e-3 at 32,768 in a fit's early iterations) a wave redoes the token
+// with all of its arithmetic in fp64 (exact_draw).  Either way the
+// topic is the one the fp64 evaluation gives.
+//   x near M:        x - M is off by at most u * e,            e = kEps * S'
+//   x inside S':     x - (M + prefix): at most 2 * e
+//   x near M + S', and inside Q': x - (M + S'): at most (1 - u) * e
+// tau = 2^-40 Z + 2^-90 on top covers the fp64 roundings (some 2^-50 of Z)
+// and fp32 underflow (terms below 2^-126, fewer than 2^31 of them).
+constexpr double kEps = 9.5 * 0x1p-24;
+constexpr uint16_t kDrawX = 0xFFFD;  // undecided: exact_draw
+constexpr double kWScale = 0x1p24;   // the row holds W^' * 2^24
+// Documents longer than this may hold a count that is not exact as the f16
+// bits of fma_mix (an integer below 2^11 in the low half of an entry reads as
+// that integer times 2^-24, subnormal or not); their tokens take draw_long_f.
+constexpr uint32_t kMixCount = 2047;
+
+struct WordF {
+  const float *wf;
+  const double *qb;
+  int nb, K, qhalf;
+  uint32_t K1;
+  double a1, qp, alpha;
 };
 
-constexpr int kTiledBlock = kTiledThreads;  // threads per workgroup of the tiled sampler (16 waves)
-constexpr int kTiledAhead = 2;              // chunks whose loads a group issues together
-static_assert(kTiledAhead == 2, "pass 1's walk in registers picks one of two chunks");
+typedef const __attribute__((address_space(3))) float lds_f32;
+__device__ __forceinline__ float wf_of(const float *__restrict__ wf, uint32_t e) {
+  uint32_t a;
+  asm("v_mad_u32_u16 %0, %1, 4, %2 op_sel:[1,0,0,0]"
+      : "=v"(a)
+      : "v"(e), "s"(uint32_t(reinterpret_cast<uintptr_t>(wf))));
+  return *(lds_f32 *)(size_t)a;
+}
+// s + count(e) * W^': the count is the entry's low half read as f16, exact
+// times 2^-24 for counts up to kMixCount.
+__device__ __forceinline__ float fma_count(uint32_t e, float w, float s) {
+  asm("v_fma_mix_f32 %0, %1, %2, %0 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "+v"(s) : "v"(e), "v"(w));
+  return s;
+}
+// This lane's S' terms over a run of kRun entries: Mix for counts up to
+// kMixCount, else any count.
+template <bool Mix>
+__device__ __forceinline__ double run_sum_f(const uint32_t (&r)[kRun], const float *__restrict__ wf) {
+  float s = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kRun; ++i) {
+    if (Mix) s = fma_count(r[i], wf_of(wf, r[i]), s);
+    else s = __builtin_fmaf(float(r[i] & 0xFFFFu), wf_of(wf, r[i]), s);
+  }
+  return Mix ? double(s) : double(s) * (1.0 / kWScale);
+}
+__device__ __forceinline__ double tau_of(double Z) { return Z * 0x1p-40 + 0x1p-90; }
 
-__global__ __launch_bounds__(kTiledBlock) void k_sampler_tiled(DevState d, Params p, uint32_t t,
-                                                               unsigned long long *__restrict__ stats) {
+// What a round leaves of a token for finish_f: for an S' draw the run (bt.off)
+// and x inside it (bt.u), for a Q' draw x past M + S'; the bound on the error
+// of x and of the run's start in bt.nnz, as a float rounded up.
+__device__ __forceinline__ uint32_t bound_bits(double e) { return __float_as_uint(float(e) * (1.0f + 0x1p-20f)); }
+
+// x's branch for a token with M, S' (off by at most e) and u: 0 = M, 1 = S',
+// 2 = Q', 3 = too near an edge to tell.
+__device__ __forceinline__ int branch_of(double x, double Mm, double S, double u, double e, double tau) {
+  if (fabs(x - Mm) <= u * e + tau || fabs(x - (Mm + S)) <= (1.0 - u) * e + tau) return 3;
+  return x < Mm ? 0 : x < Mm + S ? 1 : 2;
+}
+
+// One round of small-group draws, as draw_small.
+template <int G, int NC>
+__device__ void draw_small_f(const BatchLds &bt, int slot, int n, const WordF &w, const uint32_t *__restrict__ d_ent,
+                             int li, uint32_t &after_s) {
+  constexpr uint32_t kSpan = uint32_t(G) * kRun;
+  bool in_m = false;
+  if (slot < n) {
+    const int src = bt.list[slot];
+    const uint32_t nc = (bt.nnz[src] + 1u + kSpan - 1) / kSpan;  // slots: header + entries
+    const uint32_t off0 = bt.off[src];
+    const uint32_t *run = d_ent + off0 + uint32_t(li) * kRun;
+    const double u = bt.u[src];
+    uint32_t r[NC][kRun];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if (uint32_t(c) < nc) load_run<kRun>(run + c * kSpan, 0, r[c]);
+    }
+    if (li == 0) r[0][0] = uint32_t(w.K) << 16;  // the row header
+    double s[NC], T[NC];
+    uint32_t c1 = 0xFFFFFFFFu;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      s[c] = 0.0;
+      if (uint32_t(c) < nc) {
+        c1 = run_count_of<kRun>(r[c], w.K1, c1);
+        s[c] = run_sum_f<true>(r[c], w.wf);
+      }
+    }
+    double S = 0.0;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      S += gsum<G>(s[c]);
+      T[c] = S;
+    }
+    c1 = gmin_u32<G>(c1);
+    const double Mm = w.a1 * (double(c1 <= 0xFFFFu ? c1 : 0u) + w.alpha);  // Eq. 7
+    const double Z = (Mm + S) + w.qp, x = u * Z, e = kEps * S, tau = tau_of(Z);
+    const int br = branch_of(x, Mm, S, u, e, tau);
+    in_m = br == 0;
+    if (br == 1) {
+      int cs = 0;
+      double base = Mm, sc = s[0];
+#pragma unroll
+      for (int c = 1; c < NC; ++c) {
+        if (uint32_t(c) < nc && x >= Mm + T[c - 1]) {
+          cs = c;
+          base = Mm + T[c - 1];
+          sc = s[c];
+        }
+      }
+      const double incl = gscan<G>(sc, li);
+      const int sel = pick_lane<G>(sc, incl, base, x, li);
+      if (li == sel) {
+        bt.off[src] = (off0 + uint32_t(cs) * kSpan + uint32_t(li) * kRun) | (cs == 0 && li == 0 ? 1u : 0u);
+        bt.u[src] = x - (base + (incl - sc));
+        bt.nnz[src] = bound_bits(2.0 * e + tau);
+        bt.top[src] = kDrawS;
+      }
+    } else if (li == 0) {
+      if (br == 2) {
+        bt.u[src] = x - (Mm + S);
+        bt.nnz[src] = bound_bits((1.0 - u) * e + tau);
+      }
+      bt.top[src] = br == 0 ? uint16_t(w.K1) : br == 2 ? kDrawQ : kDrawX;
+    }
+  }
+  // outside the divergent part, so the count stays wave-uniform
+  after_s += uint32_t(__popcll(__ballot(in_m && li == 0)));
+}
+
+template <int G, int MaxNC>
+__device__ void draw_rounds_f(int from, int to, const int (&ends)[8], const BatchLds &bt, const WordF &w,
+                              const uint32_t *__restrict__ d_ent, uint32_t &after_s) {
+  constexpr uint32_t kSpan = uint32_t(G) * kRun;
+  for (int base = from; base < to; base += kWave / G) {
+    const int ln = lane_here(), g = ln / G, li = ln % G;
+    const int last = min(base + kWave / G, to) - 1;
+    uint32_t upper = kBucketEnd[7];
+#pragma unroll
+    for (int k = 6; k >= 0; --k) upper = last < ends[k] ? kBucketEnd[k] : upper;
+    const uint32_t nc = (upper + kSpan - 1) / kSpan;
+    const int slot = base + g;
+    if (nc <= 1) {
+      draw_small_f<G, 1>(bt, slot, to, w, d_ent, li, after_s);
+    } else if (nc == 2) {
+      draw_small_f<G, 2>(bt, slot, to, w, d_ent, li, after_s);
+    } else if (nc == 3) {
+      draw_small_f<G, 3>(bt, slot, to, w, d_ent, li, after_s);
+    } else if (MaxNC <= 4 || nc == 4) {
+      draw_small_f<G, 4>(bt, slot, to, w, d_ent, li, after_s);
+    } else {
+      if constexpr (MaxNC > 4) {
+        if (nc <= 6) draw_small_f<G, 6>(bt, slot, to, w, d_ent, li, after_s);
+        else draw_small_f<G, MaxNC>(bt, slot, to, w, d_ent, li, after_s);
+      }
+    }
+  }
+}
+
+// Tokens with rows of more than 512 slots or documents of more than kMixCount
+// tokens, four at a time, one per 16-lane group, as draw_long: the later
+// tokens of a run of one word in one document draw from the first one's sums.
+__device__ void draw_long_f(unsigned long long mask, unsigned long long foll, unsigned long long starts,
+                            const BatchLds &bt, const WordF &w, const uint32_t *__restrict__ d_ent, int grp, int li,
+                            uint32_t &after_s) {
+  mask &= ~foll;  // the runs' first tokens
+  while (mask) {
+    const unsigned long long m1 = mask & (mask - 1ull), m2 = m1 & (m1 - 1ull), m3 = m2 & (m2 - 1ull);
+    const int f0 = __ffsll((long long)mask) - 1, f1 = __ffsll((long long)m1) - 1;
+    const int f2 = __ffsll((long long)m2) - 1, f3 = __ffsll((long long)m3) - 1;
+    mask = m3 & (m3 - 1ull);
+    const int src = grp == 0 ? f0 : grp == 1 ? f1 : grp == 2 ? f2 : f3;
+    uint32_t n_m = 0;  // draws of this group in the max-topic branch
+    if (src >= 0) {
+      const uint32_t off0 = bt.off[src];
+      const uint32_t *row = d_ent + off0;  // slot 0 is the row header
+      const uint32_t pad = uint32_t(w.K) << 16;
+      const uint32_t slots = d_row_slots(bt.nnz[src]), nch = (slots + kChunk - 1) / kChunk;
+      uint32_t r[kRun];
+      double s = 0.0, incl = 0.0, S = 0.0;
+      double tot = 0.0;  // lane c of the group (c < kGroup): the total of chunk c
+      uint32_t c1 = 0xFFFFFFFFu;
+      for (uint32_t ch = 0; ch < nch; ++ch) {
+        load_run_masked(row, ch, slots, li, pad, r);
+        c1 = run_count_of<kRun>(r, w.K1, c1);
+        s = run_sum_f<false>(r, w.wf);
+        incl = row_incl_scan(s);
+        const double tch = __shfl(incl, kGroup - 1, kGroup);
+        S += tch;
+        tot = uint32_t(li) == ch ? tch : tot;
+      }
+      const double Mm = w.a1 * (double(row_sum_u32(c1 <= 0xFFFFu ? c1 : 0u)) + w.alpha);
+      // with the totals kept in the lanes: lane c's chunk base, added left to right
+      const bool kept = nch > 1 && nch <= uint32_t(kGroup);
+      double mine = Mm;
+      if (kept) {
+        double cb = Mm;
+        for (uint32_t c = 0; c < nch; ++c) {
+          mine = uint32_t(li) == c ? cb : mine;
+          cb += __shfl(tot, int(c), kGroup);
+        }
+      }
+      const double Z = (Mm + S) + w.qp, e = kEps * S, tau = tau_of(Z);
+      auto draw = [&](int tok) {
+        const double u = bt.u[tok], x = u * Z;
+        const int br = branch_of(x, Mm, S, u, e, tau);
+        uint16_t code = br == 0 ? uint16_t(w.K1) : br == 2 ? kDrawQ : kDrawX;
+        n_m += br == 0 ? 1u : 0u;
+        if (br == 1) {
+          uint32_t cs = 0;
+          double base = Mm;
+          bool found = nch == 1;
+          if (kept) {
+            const uint32_t hm = uint32_t(__ballot(uint32_t(li) < nch && x < mine + tot) >> (grp * kGroup)) & kGroupMask;
+            found = hm != 0u;
+            if (found) {
+              cs = uint32_t(__ffs(hm) - 1);
+              base = __shfl(mine, int(cs), kGroup);
+              load_run_masked(row, cs, slots, li, pad, r);
+              s = run_sum_f<false>(r, w.wf);
+              incl = row_incl_scan(s);
+            }
+          } else if (nch > 1) {
+            for (uint32_t ch = 0; ch < nch && !found; ++ch) {
+              load_run_masked(row, ch, slots, li, pad, r);
+              s = run_sum_f<false>(r, w.wf);
+              incl = row_incl_scan(s);
+              const double total = __shfl(incl, kGroup - 1, kGroup);
+              found = x < base + total;
+              if (found) cs = ch;
+              else base += total;
+            }
+          }
+          if (found) {
+            const int sel = run_lane(s, incl, base, x, grp);
+            if (li == sel) {
+              bt.off[tok] = (off0 + cs * kChunk + uint32_t(li) * kRun) | (cs == 0u && li == 0 ? 1u : 0u);
+              bt.u[tok] = x - (base + (incl - s));
+            }
+            code = kDrawS;
+          }
+        }
+        if (li == 0) {
+          if (br == 2) bt.u[tok] = x - (Mm + S);
+          bt.nnz[tok] = bound_bits(br == 1 ? 2.0 * e + tau : (1.0 - u) * e + tau);
+          bt.top[tok] = code;
+        }
+      };
+      draw(src);
+      // the run's later tokens: lanes after src up to the next run start
+      const unsigned long long after = ~((2ull << src) - 1ull);  // the lanes above src
+      const unsigned long long nxt = starts & after;
+      unsigned long long fl = foll & after & (nxt ? (nxt & (0ull - nxt)) - 1ull : ~0ull);
+      for (; fl; fl &= fl - 1ull) draw(__ffsll((long long)fl) - 1);
+    }
+    // outside the divergent part, so the count stays wave-uniform
+    after_s += wave_sum_u32(li == 0 ? n_m : 0u);
+  }
+}
+
+// The block of the Q' prefix that holds xq: the largest with qb[block] <= xq,
+// for qb[0] <= xq < qb[nb].
+__device__ __forceinline__ int q_block_f(const WordF &w, double xq) {
+  int lo = 0;
+  for (int step = w.qhalf; step > 0; step >>= 1) {
+    const int at = min(lo + step, w.nb);
+    lo = w.qb[at] <= xq ? at : lo;
+  }
+  return lo;
+}
+
+// The drawn topic of a batch token, one lane per token, or kDrawX where an
+// edge of the segment lies within the bound.
+template <int BS>
+__device__ __forceinline__ uint32_t finish_f(int q, const BatchLds &bt, const WordF &w,
+                                             const uint32_t *__restrict__ d_ent) {
+  const uint32_t code = bt.top[q];
+  if (code != kDrawS && code != kDrawQ) return code;
+  const double xs = bt.u[q];
+  const float e = __uint_as_float(bt.nnz[q]);
+  if (code == kDrawS) {
+    const uint32_t a = bt.off[q];
+    uint32_t r[kRun];
+    load_run<kRun>(d_ent + (a & ~uint32_t(kRun - 1)), 0, r);
+    if (a & 1u) r[0] = uint32_t(w.K) << 16;  // the run starts with the row header
+    double p = 0.0, below = -1.0;
+    uint32_t ent = 0;
+#pragma unroll
+    for (int i = 0; i < kRun; ++i) {
+      const bool open = p <= xs;
+      ent = open ? r[i] : ent;
+      below = open ? p : below;
+      p = __builtin_fma(double(r[i] & 0xFFFFu), double(wf_of(w.wf, r[i])) * (1.0 / kWScale), p);
+    }
+    // the chosen entry's edges
+    const double above = __builtin_fma(double(ent & 0xFFFFu), double(wf_of(w.wf, ent)) * (1.0 / kWScale), below);
+    return xs - below > double(e) && above - xs > double(e) && below >= 0.0 ? ent >> 16 : uint32_t(kDrawX);
+  }
+  if (!(xs < w.qb[w.nb]) || !(xs >= 0.0)) return kDrawX;
+  const int lo = q_block_f(w, xs);
+  // inside the block in fp32, in units of alpha * 2^-24: x rounded once, at
+  // most BS + 1 roundings in a partial sum, two more in the comparison
+  const float inv = float(kWScale / w.alpha);
+  const float xb = float((xs - w.qb[lo]) * (kWScale / w.alpha));
+  const float *wb = w.wf + lo * BS;
+  float p = 0.0f, below = 0.0f;
+  int at = 0;
+#pragma unroll 8
+  for (int i = 0; i < BS; ++i) {
+    const bool open = p <= xb;
+    at = open ? i : at;
+    below = open ? p : below;
+    p += wb[i];
+  }
+  const float above = below + wb[at];
+  const float eq = e * inv * (1.0f + 0x1p-20f) + (p + xb) * (float(BS + 4) * 0x1p-24f);
+  return xb - below > eq && above - xb > eq ? uint32_t(lo * BS + at) : uint32_t(kDrawX);
+}
+
+// One token by a whole wave, all in fp64: W^' of a topic is recomputed from
+// its count (a dense row's own; a sparse row's from the single-precision
+// value, whose rounding, 2^-24 of a count below 2^16 plus beta, leaves the
+// integer, or by a search of the row when beta is large).
+struct ExactRow {
+  const int32_t *dense;   // the word's dense row, or null
+  const uint32_t *ents;   // its sparse row otherwise
+  uint32_t nnz;
+};
+__device__ double exact_w(const DevState &d, const Params &p, const WordF &w, const ExactRow &er, uint32_t k) {
+  if (k >= uint32_t(w.K) || k == w.K1) return 0.0;
+  const double den = d.den[k];
+  if (er.dense) return what(uint32_t(er.dense[k]), p.beta, den);
+  if (p.beta <= 1e6) return (rint(double(w.wf[k]) * (1.0 / kWScale) * den - p.beta) + p.beta) / den;
+  const uint32_t lb = row_lower_bound(er.ents, er.nnz, k);
+  return what(lb < er.nnz && (er.ents[lb] >> 16) == k ? er.ents[lb] & 0xFFFFu : 0u, p.beta, den);
+}
+// Returns the topic, bit 16 set for a draw in the max-topic branch.
+constexpr uint32_t kExactM = 0x10000u;
+template <int BS>
+__device__ uint32_t exact_draw(const DevState &d, const Params &p, const WordF &w, const ExactRow &er, uint32_t off,
+                               double u, int lane) {
+  const uint32_t *row = d.d_ent + off;
+  const uint32_t nnz = __builtin_amdgcn_readfirstlane(row[0]) & 0xFFFFu;
+  double S = 0.0;
+  uint32_t C1 = 0;
+  double term = 0.0;
+  uint32_t k = 0;
+  auto load = [&](uint32_t q0) {
+    const uint32_t q = q0 + uint32_t(lane);
+    const uint32_t ent = q < nnz ? row[1u + q] : uint32_t(w.K) << 16;
+    k = ent >> 16;
+    term = double(ent & 0xFFFFu) * exact_w(d, p, w, er, k);
+    return ent;
+  };
+  for (uint32_t q0 = 0; q0 < nnz; q0 += kWave) {
+    const uint32_t ent = load(q0);
+    S += __shfl(wave_incl_scan(term), kWave - 1);
+    const unsigned long long m = __ballot((ent >> 16) == w.K1);
+    if (m) C1 = max(C1, uint32_t(__shfl(int(ent & 0xFFFFu), __ffsll((long long)m) - 1)));
+  }
+  const double Mm = w.a1 * (double(C1) + w.alpha);
+  const double x = u * ((Mm + S) + w.qp);
+  if (x < Mm) return w.K1 | kExactM;
+  uint32_t last = w.K1;  // the last segment of positive width
+  if (x < Mm + S) {
+    double base = Mm;
+    for (uint32_t q0 = 0; q0 < nnz; q0 += kWave) {
+      load(q0);
+      const double incl = wave_incl_scan(term);
+      const unsigned long long pos = __ballot(term > 0.0), hit = __ballot(term > 0.0 && x < base + incl);
+      if (hit) return uint32_t(__shfl(int(k), __ffsll((long long)hit) - 1));
+      if (pos) last = uint32_t(__shfl(int(k), 63 - __clzll((long long)pos)));
+      base += __shfl(incl, kWave - 1);
+    }
+    return last;
+  }
+  const double xq = x - (Mm + S);
+  if (!(xq < w.qb[w.nb])) return (w.K1 == uint32_t(w.K - 1)) ? uint32_t(w.K - 2) : uint32_t(w.K - 1);
+  const int lo = q_block_f(w, xq);
+  k = uint32_t(lo * BS + lane);
+  term = lane < BS ? w.alpha * exact_w(d, p, w, er, k) : 0.0;
+  const double incl = w.qb[lo] + wave_incl_scan(term);
+  const unsigned long long pos = __ballot(term > 0.0), hit = __ballot(term > 0.0 && xq < incl);
+  if (hit) return uint32_t(__shfl(int(k), __ffsll((long long)hit) - 1));
+  return pos ? uint32_t(__shfl(int(k), 63 - __clzll((long long)pos))) : last;
+}
+
+// Entries of the single-precision row: K + 1 rounded up to whole waves.
+__host__ __device__ inline int wf_entries(int K) { return (K + kWave) / kWave * kWave; }
+
+// Per iteration: qbase[b] = sum of alpha * beta/den[k] over block b of
+// kQBlockF topics, what a sparse word's Q' prefix starts from.
+__global__ __launch_bounds__(kBlock) void k_block_base(DevState d, Params p) {
+  const int k = int(blockIdx.x) * kBlock + int(threadIdx.x);
+  double v = k < p.K ? p.alpha * d.bden[k] : 0.0;
+  v = group_sum<kQBlockF>(v);
+  if (k % kQBlockF == 0 && k < p.K) d.qbase[k / kQBlockF] = v;
+}
+
+// The sampler of the units, NB threads per workgroup: as sampler_body, with
+// the single-precision row.  A unit's setup touches only what changes: after
+// another sparse word the previous word's topics go back to beta/den[k], the
+// new word's entries are written and their excess over beta/den[k] is added
+// to their blocks (LDS atomics in fp64: the sums' last bits depend on their
+// order, which tau covers), then the K / 32 block sums are scanned.  At
+// K = 32,768 the two-tile fp64 sampler filled three tiles of 16,400 topics
+// per region.
+template <int NB>
+__device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
+                                               unsigned long long *__restrict__ stats) {
   extern __shared__ double lds[];
+  constexpr int BS = kQBlockF;
   const int K = p.K;
-  const uint32_t kt = uint32_t(p.tile_topics);  // topics per tile, a multiple of kGroup
-  const int nb = (K + kGroup - 1) / kGroup;
-  double *wt = lds;                                  // [kt + kGroup]
-  double *qb = lds + kt + kGroup;                    // [nb + 1]: prefix of alpha*W^' over blocks of kGroup topics
-  uint32_t *s_hand = reinterpret_cast<uint32_t *>(qb + nb + 1);  // [kTiledBlock / kGroup * kMaxRun]
-  uint32_t *s_reg = s_hand + kTiledBlock / kGroup * kMaxRun;     // [6]: region, flag, list length
-  double *s_u = reinterpret_cast<double *>(s_reg + 6);            // [kTiledBlock]: u of the next 16 steps per wave
+  const int nb = (K + BS - 1) / BS;
+  const int nwf = wf_entries(K);
+  const bool by_doc = doc_marks(d, p, t);
+  float *wf = reinterpret_cast<float *>(lds);                        // [nwf]
+  double *qb = lds + nwf / 2;                                        // [nb + 1]
+  double *s_u = qb + nb + 1;                                        // [NB]
+  uint32_t *s_off = reinterpret_cast<uint32_t *>(s_u + NB);          // [NB]
+  uint32_t *s_nnz = s_off + NB;                                      // [NB]
+  uint32_t *s_reg = s_nnz + NB;                                      // [4]
+  uint16_t *s_top = reinterpret_cast<uint16_t *>(s_reg + 4);         // [NB]
+  uint8_t *s_list = reinterpret_cast<uint8_t *>(s_top + NB);         // [NB]
+  const int qhalf = q_blocks_padded(nb + 1) / 2;  // the first step of a search over qb[0..nb]
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
-  const int wave = tid / kWave, grp = lane / kGroup, li = lane % kGroup;
-  if (blockIdx.x == 0 && tid == 0) stats[ST_MARKS] = 1ull;  // the word-ordered bitmap only
-  uint32_t *hand = s_hand + (tid / kGroup) * kMaxRun;
-  const uint32_t pad = uint32_t(K) << 16;
-  // per-workgroup scratch slices, indexed by the token's place in its region
-  double *sc_s = d.ts_s + size_t(blockIdx.x) * size_t(p.max_region);
-  uint32_t *sc_c1 = d.ts_c1 + size_t(blockIdx.x) * size_t(p.max_region);
-  uint32_t *sc_code = d.ts_code + size_t(blockIdx.x) * size_t(p.max_region);
-  TiledRec *sc_list = d.ts_list + size_t(blockIdx.x) * size_t(p.max_region);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  if (blockIdx.x == 0 && tid == 0) stats[ST_MARKS] = by_doc ? 2ull : 1ull;
+  const BatchLds bt{s_off + wave * kWave, s_nnz + wave * kWave, s_u + wave * kWave, s_top + wave * kWave, nullptr,
+                    s_list + wave * kWave};
+  for (int k = K + tid; k < nwf; k += NB) wf[k] = 0.0f;
+  uint32_t cur = 0xFFFFFFFFu, K1 = 0;
+  double a1 = 0.0, qp = 0.0;
+  const int32_t *wrow = nullptr;   // the word's dense row, or null
+  const uint32_t *held = nullptr;  // the sparse word whose row wf holds
+  uint32_t held_nnz = 0, held_k1 = 0;
+  // (tokens of a corpus, and so these counts, fit 32 bits)
   uint32_t n_sampled = 0, n_after_s = 0, n_reg = 0, n_dreg = 0;
   unsigned long long nnz_sum = 0, row_bytes = 0;
-  const int waves = kTiledBlock / kWave;
+
   for (;;) {
     if (tid == 0) {
-      const uint32_t r = atomicAdd(&d.counters[CNT_SAMPLER], 1u);
-      s_reg[3] = int64_t(r) < p.n_regions ? 1u : 0u;
-      s_reg[4] = 0u;
+      const int64_t r = int64_t(atomicAdd(&d.counters[CNT_SAMPLER], 1u));
+      s_reg[3] = r < p.n_units ? 1u : 0u;
       if (s_reg[3]) {
-        s_reg[0] = d.region[3 * size_t(r)];
-        s_reg[1] = d.region[3 * size_t(r) + 1];
-        s_reg[2] = d.region[3 * size_t(r) + 2];
+        s_reg[0] = d.unit[3 * size_t(r)];
+        s_reg[1] = d.unit[3 * size_t(r) + 1];
+        s_reg[2] = d.unit[3 * size_t(r) + 2];
       }
     }
     __syncthreads();
     if (!s_reg[3]) break;
-    const uint32_t v = __builtin_amdgcn_readfirstlane(s_reg[0]);
+    const uint32_t vc = __builtin_amdgcn_readfirstlane(s_reg[0]), v = vc & ~kUnitContinues;
     const uint32_t b = __builtin_amdgcn_readfirstlane(s_reg[1]);
     const uint32_t e = __builtin_amdgcn_readfirstlane(s_reg[2]);
-    __syncthreads();  // s_reg is rewritten by the next region's fetch
-    n_reg++;
-    if (int32_t(v) < p.n_dense) n_dreg++;
+    if (vc == v) {  // the first unit of its region
+      n_reg++;
+      if (int32_t(v) < p.n_dense) n_dreg++;
+    }
     if (b == d.word_off[v])
       row_bytes += int32_t(v) < p.n_dense ? 4ull * uint64_t(K) : 4ull * d.ws_nnz[int(v) - p.n_dense];
-    const WordRec rec = d.wrec[v];
-    const uint32_t K1 = __builtin_amdgcn_readfirstlane(rec.k1);
-    // C1 = D[d][K1] is sought only in the pass whose tile holds topic K1 (that
-    // pass reads every chunk with topics of its tile); the other reads 0
-    const bool k1_lo = K1 < kt;
-    for (int pass = 0; pass < 3; ++pass) {
-      const uint32_t tbase = pass == 1 ? kt : 0u;
-      const uint32_t tlen = pass == 1 ? uint32_t(K) + 1u - kt : kt;
-      fill_tile(d, p, v, K1, tbase, tlen, kt, wt, tid, kTiledBlock);
-      const TileState ts{wt, tbase, kt, 0u - tbase * 8u};
-      if (pass < 2) {
-        // this tile's blocks of the Q' prefix, continuing the previous tile's.
-        // Thread i sums blocks i and i + kTiledBlock of the tile (a tile has at
-        // most 2 * kTiledBlock blocks), the 16 topics of a block from topic
-        // i % 16 on, wrapping, so that the 16 lanes of a row read 16 different
-        // LDS bank pairs; the prefix is then a scan per wave, in registers,
-        // plus the totals of the waves before, added in wave order
-        const int b0 = int(tbase) / kGroup, b1 = min(nb, int(tbase + tlen + kGroup - 1) / kGroup);
-        const int nblk = b1 - b0;
-        double *s_tot = s_u;  // [2 * waves]; s_u is next written in pass 1's token loop
-        // the rotation's start, opaque to the compiler: otherwise it keeps the
-        // 16 rotated addresses live (spilled) across the region loop
-        uint32_t rot;
-        asm volatile("v_mov_b32 %0, %1" : "=v"(rot) : "v"(uint32_t(li)));
-        auto block_scan = [&](int blk) {
-          double sum = 0.0;
-          if (blk < nblk) {
-            const double *wb = wt + blk * kGroup;
-#pragma unroll
-            for (uint32_t i = 0; i < uint32_t(kGroup); ++i)
-              sum = __builtin_fma(p.alpha, wb[(i + rot) & uint32_t(kGroup - 1)], sum);
-          }
-          return wave_incl_scan(sum);
-        };
-        const double incl0 = block_scan(tid);
-        if (lane == kWave - 1) s_tot[wave] = incl0;
-        double incl1 = 0.0;
-        if (nblk > kTiledBlock) {
-          incl1 = block_scan(kTiledBlock + tid);
-          if (lane == kWave - 1) s_tot[waves + wave] = incl1;
+    if (v != cur) {
+      cur = v;
+      const WordRec rec = d.wrec[v];
+      K1 = rec.k1;
+      a1 = rec.a1;
+      qp = rec.qp;
+      if (int32_t(v) < p.n_dense) {
+        wrow = d.w_dense + size_t(v) * size_t(K);
+        for (int k0 = wave * kWave; k0 < K; k0 += NB) {
+          const int k = k0 + lane;
+          const double w = k < K && uint32_t(k) != K1 ? what(uint32_t(wrow[k]), p.beta, d.den[k]) : 0.0;
+          wf[k] = float(w * kWScale);
+          const double sum = group_sum<BS>(p.alpha * w);
+          if (lane % BS == 0 && k < K) qb[k / BS + 1] = sum;
         }
+        held = nullptr;
         __syncthreads();
-        double acc = pass == 0 ? 0.0 : qb[b0], own = 0.0;
-        for (int w = 0; w < waves; ++w) {
-          if (w == wave) own = acc;
-          acc += s_tot[w];
-        }
-        if (tid < nblk) qb[b0 + tid + 1] = own + incl0;
-        if (nblk > kTiledBlock) {
-          for (int w = 0; w < waves; ++w) {
-            if (w == wave) own = acc;
-            acc += s_tot[waves + w];
+      } else {
+        const int s = int(v) - p.n_dense;
+        const uint32_t *ents = d.ws_ent + d.ws_cap[s];
+        const uint32_t nnz = d.ws_nnz[s];
+        wrow = nullptr;
+        for (int q = tid; q < nb; q += NB) qb[q + 1] = d.qbase[q];
+        if (held) {
+          for (uint32_t q = tid; q < held_nnz; q += NB) {
+            const uint32_t k = held[q] >> 16;
+            wf[k] = float(d.bden[k] * kWScale);
           }
-          if (kTiledBlock + tid < nblk) qb[b0 + kTiledBlock + tid + 1] = own + incl1;
-        }
-        if (pass == 0 && tid == 0) qb[0] = 0.0;
-        __syncthreads();
-      }
-      const uint32_t stride = uint32_t(waves) * 4u;
-      if (pass == 2) {
-        // the draws pass 1 recorded, in the order it listed them, four per
-        // wave at a time; a group's next record is loaded one step ahead
-        const uint32_t nl = __builtin_amdgcn_readfirstlane(s_reg[4]);
-        TiledRec nrec{};
-        if (nl) nrec = sc_list[min(uint32_t(wave) * 4u + uint32_t(grp), nl - 1u)];
-        for (uint32_t i0 = uint32_t(wave) * 4u; i0 < nl; i0 += stride) {
-          const uint32_t i = i0 + uint32_t(grp);
-          const TiledRec tr = nrec;
-          if (i0 + stride < nl) nrec = sc_list[min(i + stride, nl - 1u)];
-          if (i >= nl) continue;
-          const uint32_t j = b + tr.q, code = tr.code, cn = tr.cn;
-          const uint32_t *row = d.d_ent + tr.off;
-          const double x = tr.x;
-          uint32_t topic;
-          if ((code & 3u) == 1u) {
-            const uint32_t slots = d_row_slots(cn >> 16);
-            const double Mm = rec.a1 * (double(cn & 0xFFFFu) + p.alpha);
-            const uint32_t sc = code >> 2;
-            if (sc < uint32_t(kTiledAhead)) {
-              // the tile-0 chunks, 0 to the split chunk, loaded together and
-              // walked in registers (a chunk past the split chunk adds nothing)
-              uint32_t rb[kTiledAhead][kMaxRun];
-              double tb[kTiledAhead];
-#pragma unroll
-              for (int c = 0; c < kTiledAhead; ++c) load_run_masked(row, uint32_t(c), slots, li, pad, rb[c]);
-#pragma unroll
-              for (int c = 0; c < kTiledAhead; ++c) tb[c] = run_sum_tile(rb[c], ts);
-              topic = walk_pair(rb, tb, ts, Mm, x, grp, li, hand);
-            } else {
-              topic = tile_walk(row, slots, ts, Mm, x, pad, grp, li, hand, 0u, sc + 1u);
-            }
-            if (topic == uint32_t(-1)) topic = K1;  // no positive S' term below KT: cannot happen for x in S'
-          } else {
-            const int lo = int(code >> 2);
-            const uint32_t k = uint32_t(lo * kGroup + li);
-            const double term = p.alpha * wt[k];
-            topic = pick_segment(k, term, tr.keep + qb[lo], x, grp);
-          }
-          if (li == 0) d.z_w[j] = uint16_t(topic);
-        }
-        __syncthreads();
-        continue;
-      }
-      // four tokens per wave at a time, one per 16-lane group.  A token's
-      // skip word, key and row offset, and its records of pass 0 are loaded
-      // one step ahead, while the group works on the previous token (the
-      // fp64 record is loaded beside the row's first chunk); pass 0 then
-      // loads the row header and first chunk together (the header is slot 0)
-      auto tok_load = [&](uint32_t jt) {
-        const uint32_t jj = min(jt, e - 1u), qq = jj - b;
-        TiledTok o;
-        o.sk = d.skip_bits[jj >> 5];
-        o.kr = d.wt_kr[jj];
-        o.rec = pass == 0 ? 0u : sc_code[qq];  // pass 1: the split chunk
-        o.cn = pass == 0 ? 0u : sc_c1[qq];     // pass 1: pass 0's C1 and the row length
-        return o;
-      };
-      TiledTok nxt = tok_load(b + uint32_t(wave) * 4u + uint32_t(grp));
-      // pass 1: lane L draws u for the token of group L % 4 at step L / 4 of
-      // each block of 16 steps into the wave's slice of LDS
-      double *s_uw = s_u + wave * kWave;
-      uint32_t step = 0;
-      for (uint32_t j0 = b + uint32_t(wave) * 4u; j0 < e; j0 += stride, ++step) {
-        const uint32_t j = j0 + uint32_t(grp);
-        const uint32_t q = j - b;  // place in the region
-        const TiledTok tk = nxt;
-        if (j0 + stride < e) nxt = tok_load(j + stride);
-        if (pass == 1 && (step & 15u) == 0u) {
-          const uint32_t jl = j0 + uint32_t(lane >> 2) * stride + uint32_t(lane & 3);
-          s_uw[lane] = uniform_draw(p.seed, t, d.wt_kr[min(jl, e - 1u)].x);
-          __builtin_amdgcn_wave_barrier();
-        }
-        const uint32_t sk = tk.sk;
-        const uint2 kr = tk.kr;
-        const uint32_t rec0 = tk.rec, cn0 = tk.cn;
-        const bool skipped = j < e && ((sk >> (j & 31u)) & 1u);
-        if (pass == 0 && skipped && li == 0) d.z_w[j] = uint16_t(K1);  // decided by the step-3 test
-        const bool live = j < e && !skipped;
-        if (!live) continue;
-        const uint32_t *row = d.d_ent + kr.y;
-        if (pass == 0) {
-          // the first two chunks in full (a row start plus 2 * kChunk slots
-          // stays inside the kRowPad slots past the last row), masked below
-          static_assert(kTiledAhead * kChunk <= kRowPad, "the speculative chunks stay inside the D array");
-          uint32_t r0[kTiledAhead][kMaxRun];
-#pragma unroll
-          for (int c = 0; c < kTiledAhead; ++c)
-#pragma unroll
-            for (int i = 0; i < kMaxRun; ++i) r0[c][i] = row[uint32_t(c) * kChunk + uint32_t(li) * kMaxRun + uint32_t(i)];
-          const uint32_t nnz = uint32_t(__shfl(int(r0[0][0]), 0, kGroup)) & 0xFFFFu;
-          const uint32_t slots = d_row_slots(nnz);
-          const uint32_t nch = (slots + kChunk - 1) / kChunk;
-          // a lane's run of kMaxRun slots lies wholly inside or past the row
-          // (slots is a multiple of 32)
-#pragma unroll
-          for (int c = 0; c < kTiledAhead; ++c) {
-            if (uint32_t(c) * kChunk + uint32_t(li) * kMaxRun >= slots) {
-#pragma unroll
-              for (int i = 0; i < kMaxRun; ++i) r0[c][i] = pad;
-            }
-          }
-          if (li == 0) r0[0][0] = pad;  // the row header
-          // S' over the tile-0 topics and C1, chunk by chunk up to the split
-          // chunk; the loads of up to kTiledAhead chunks are issued together
-          double s0 = 0.0;
-          uint32_t c1 = 0xFFFFFFFFu;
-          uint32_t sc = 0;
-          bool open = true;
-#pragma unroll
-          for (int c = 0; c < kTiledAhead; ++c) {
-            if (open) {
-              if (k1_lo) c1 = run_count_of<kMaxRun>(r0[c], K1, c1);
-              sc = uint32_t(c);
-              open = sc + 1u < nch && (uint32_t(__shfl(int(r0[c][kMaxRun - 1]), kGroup - 1, kGroup)) >> 16) < kt;
-              s0 += run_sum_tile(r0[c], ts);
-            }
-          }
-          for (uint32_t c0 = kTiledAhead; open; c0 += kTiledAhead) {
-            uint32_t r[kTiledAhead][kMaxRun];
-#pragma unroll
-            for (int c = 0; c < kTiledAhead; ++c) load_run_masked(row, c0 + uint32_t(c), slots, li, pad, r[c]);
-#pragma unroll
-            for (int c = 0; c < kTiledAhead; ++c) {
-              if (open) {
-                if (k1_lo) c1 = run_count_of<kMaxRun>(r[c], K1, c1);
-                sc = c0 + uint32_t(c);
-                open = sc + 1u < nch && (uint32_t(__shfl(int(r[c][kMaxRun - 1]), kGroup - 1, kGroup)) >> 16) < kt;
-                s0 += run_sum_tile(r[c], ts);
-              }
-            }
-          }
-          const double S0 = gsum<kGroup>(s0);
-          c1 = gsum_u32<kGroup>(c1 <= 0xFFFFu ? c1 : 0u);
-          if (li == 0) {
-            sc_s[q] = S0;
-            sc_c1[q] = c1 | (nnz << 16);
-            sc_code[q] = sc;
-          }
+          if (tid == 0 && held_k1 < uint32_t(K)) wf[held_k1] = float(d.bden[held_k1] * kWScale);  // K1 = K in two-branch mode
         } else {
-          const uint32_t sc = rec0;
-          const uint32_t nnz = cn0 >> 16;
-          const uint32_t slots = d_row_slots(nnz);
-          const uint32_t nch = (slots + kChunk - 1) / kChunk;
-          // S' over the tile-1 topics, and C1 where pass 0 did not read it,
-          // from the split chunk on; the first batch of chunks stays in
-          // registers for the draw
-          double s1 = 0.0;
-          uint32_t c1 = 0xFFFFFFFFu;
-          uint32_t rb[kTiledAhead][kMaxRun];
-          double tb[kTiledAhead];
-#pragma unroll
-          for (int c = 0; c < kTiledAhead; ++c) load_run_masked(row, sc + uint32_t(c), slots, li, pad, rb[c]);
-#pragma unroll
-          for (int c = 0; c < kTiledAhead; ++c) {
-            if (!k1_lo) c1 = run_count_of<kMaxRun>(rb[c], K1, c1);
-            tb[c] = run_sum_tile(rb[c], ts);
-            s1 += tb[c];
-          }
-          for (uint32_t c0 = sc + kTiledAhead; c0 < nch; c0 += kTiledAhead) {
-            uint32_t r[kTiledAhead][kMaxRun];
-#pragma unroll
-            for (int c = 0; c < kTiledAhead; ++c) load_run_masked(row, c0 + uint32_t(c), slots, li, pad, r[c]);
-#pragma unroll
-            for (int c = 0; c < kTiledAhead; ++c) {
-              if (!k1_lo) c1 = run_count_of<kMaxRun>(r[c], K1, c1);
-              s1 += run_sum_tile(r[c], ts);
-            }
-          }
-          const double S1 = gsum<kGroup>(s1);
-          const double S0 = sc_s[q];
-          // topic K1's entry was sought in one of the two passes, the other read 0
-          const uint32_t C1 = max(cn0 & 0xFFFFu, gsum_u32<kGroup>(c1 <= 0xFFFFu ? c1 : 0u));
-          const double Mm = rec.a1 * (double(C1) + p.alpha);  // Eq. 7
-          const double S = S0 + S1;
-          const double x = s_uw[((step & 15u) << 2) | uint32_t(grp)] * ((Mm + S) + rec.qp);
-          uint32_t topic = K1, code = 0u;
-          double keep = 0.0;
-          if (x < Mm) {
-            if (li == 0) n_after_s++;
-          } else if (x < Mm + S) {
-            if (x < Mm + S0) {
-              code = 1u | (sc << 2);  // S' draw in tile 0, whose terms end at the split chunk
-            } else if (nch - sc <= uint32_t(kTiledAhead)) {
-              // every tile-1 chunk is in registers
-              const uint32_t k = walk_pair(rb, tb, ts, Mm + S0, x, grp, li, hand);
-              if (k == uint32_t(-1)) code = 1u | (sc << 2);  // nothing positive in tile 1: rounding at the tile edge
-              else topic = k;
-            } else {
-              const uint32_t k = tile_walk(row, slots, ts, Mm + S0, x, pad, grp, li, hand, sc, nch);
-              if (k == uint32_t(-1)) code = 1u | (sc << 2);  // nothing positive in tile 1: rounding at the tile edge
-              else topic = k;
-            }
-          } else {
-            const double qs = Mm + S;
-            const double xq = x - qs;
-            if (!(xq < qb[nb])) {
-              topic = (K1 == uint32_t(K - 1)) ? uint32_t(K - 2) : uint32_t(K - 1);  // last positive segment
-            } else {
-              // the largest block lo < nb with qb[lo] <= xq, 16 candidates at a time
-              int lo = 0, span = nb;
-              while (span > 1) {
-                const int step = (span + kGroup - 1) / kGroup;
-                const int off = li * step;
-                const bool ok = off < span && qb[lo + off] <= xq;
-                const uint32_t bm = uint32_t(__ballot(ok) >> (grp * kGroup)) & kGroupMask;
-                const int best = bm ? 31 - __clz(bm) : 0;
-                lo += best * step;
-                span = min(step, span - best * step);
-              }
-              const uint32_t k = uint32_t(lo * kGroup + li);
-              if (uint32_t(lo * kGroup) >= kt) {
-                const double term = p.alpha * wt[k - kt];
-                topic = pick_segment(k, term, qs + qb[lo], x, grp);
-              } else {
-                code = 2u | (uint32_t(lo) << 2);  // Q' draw in a tile-0 block
-                keep = qs;
-              }
-            }
-          }
-          if (li == 0) {
-            n_sampled++;
-            nnz_sum += nnz;
-            if (code) {
-              TiledRec tr;
-              tr.q = q;
-              tr.code = code;
-              tr.cn = C1 | (nnz << 16);
-              tr.off = kr.y;
-              tr.x = x;
-              tr.keep = keep;
-              sc_list[atomicAdd(&s_reg[4], 1u)] = tr;
-            } else {
-              d.z_w[j] = uint16_t(topic);
-            }
-          }
+          for (int k = tid; k < K; k += NB) wf[k] = float(d.bden[k] * kWScale);
         }
+        __syncthreads();
+        for (uint32_t q = tid; q < nnz; q += NB) {
+          const uint32_t ent = ents[q], k = ent >> 16;
+          const double w = what(ent & 0xFFFFu, p.beta, d.den[k]);
+          wf[k] = float(w * kWScale);
+          if (k != K1) unsafeAtomicAdd(&qb[k / BS + 1], p.alpha * (w - d.bden[k]));
+        }
+        if (tid == 0 && K1 < uint32_t(K)) unsafeAtomicAdd(&qb[K1 / BS + 1], -(p.alpha * d.bden[K1]));
+        held = ents;
+        held_nnz = nnz;
+        held_k1 = K1;
+        __syncthreads();
+        if (tid == 0) wf[K1] = 0.0f;  // the max topic is its own branch (Eq. 5)
+      }
+      // the prefix over the blocks: a scan per wave, then the totals of the
+      // waves before, in round and wave order
+      double *s_tot = s_u;  // [rounds * waves <= NB]; s_u is next written by the token batches
+      for (int r = 0; r * NB < nb; ++r) {
+        const int blk = r * NB + tid;
+        const double incl = wave_incl_scan(blk < nb ? qb[blk + 1] : 0.0);
+        if (blk < nb) qb[blk + 1] = incl;
+        if (lane == kWave - 1) s_tot[r * (NB / kWave) + wave] = incl;
+      }
+      __syncthreads();
+      {
+        double acc = 0.0;
+        for (int r = 0; r * NB < nb; ++r) {
+          double own = 0.0;
+          for (int w = 0; w < NB / kWave; ++w) {
+            if (w == wave) own = acc;
+            acc += s_tot[r * (NB / kWave) + w];
+          }
+          const int blk = r * NB + tid;
+          if (blk < nb) qb[blk + 1] = own + qb[blk + 1];
+        }
+        if (tid == 0) qb[0] = 0.0;
       }
       __syncthreads();
     }
+
+    const WordF w{wf, qb, nb, K, qhalf, K1, a1, qp, p.alpha};
+    const uint32_t bsz = min(uint32_t(kWave), max(16u, ((e - b + uint32_t(NB / kWave) - 1u) / uint32_t(NB / kWave) + 15u) & ~15u));
+    for (uint32_t base = b + uint32_t(wave) * bsz; base < e; base += uint32_t(NB / kWave) * bsz) {
+      const int ln = lane_here();
+      const uint32_t j = base + uint32_t(ln);
+      const uint32_t be = min(e, base + bsz);
+      uint32_t sk = 0, key = 0, off = 0;
+      if (j < be) {
+        const uint2 kr = d.wt_kr[j];
+        key = kr.x;
+        off = kr.y;
+        sk = by_doc ? d.skip_doc[key >> 5] >> (key & 31u) : d.skip_bits[j >> 5] >> (j & 31u);
+      }
+      const bool und = j < be && !(sk & 1u);
+      uint32_t hdr = 0;
+      if (und) {
+        hdr = d.d_ent[off];
+        bt.off[ln] = off;
+        bt.nnz[ln] = hdr & 0xFFFFu;
+        bt.u[ln] = uniform_draw(p.seed, t, key);
+      }
+      const uint32_t nnz = hdr & 0xFFFFu;
+      // long rows, and documents whose counts may pass fma_mix
+      const bool lng = und && (nnz + 1u > 512u || (hdr >> 16) > kMixCount);
+      const unsigned long long lmask = __ballot(lng);
+      unsigned long long starts = 0ull;
+      bool fol = false;
+      if (lmask) {
+        const uint32_t prev_off = uint32_t(__shfl(int(off), ln - 1));
+        starts = __ballot(ln == 0 || off != prev_off);
+        const unsigned long long below = ln ? ~0ull >> (64 - ln) : 0ull;
+        const int rs = 63 - __clzll((long long)(starts & (below | (1ull << ln))));  // this lane's run start
+        fol = lng && (lmask & below & (~0ull << rs)) != 0ull;
+      }
+      n_sampled += uint32_t(__popcll(__ballot(und)));
+      nnz_sum += wave_sum_u32(fol && nnz + 1u > 512u ? min(nnz, uint32_t(kChunk)) : nnz);
+      // the other rows by length bucket: groups of 4, 8 or 16 lanes
+      const bool sml = und && !lng;
+      int n = 0, ends[8];
+      const uint32_t slots = nnz + 1u;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t lo = k ? kBucketEnd[k - 1] : 0u;
+        const unsigned long long m = __ballot(sml && slots > lo && slots <= kBucketEnd[k]);
+        if ((m >> ln) & 1ull)
+          bt.list[n + int(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)))] =
+              uint8_t(ln);
+        n += __popcll(m);
+        ends[k] = n;
+      }
+      const int left = ends[3] % 16;
+      const int a = left > 0 && left <= 8 && ends[3] - ends[2] >= left ? ends[3] - left : ends[3];
+      draw_rounds_f<4, 4>(0, a, ends, bt, w, d.d_ent, n_after_s);
+      if (NB >= 1024) {
+        draw_rounds_f<8, 8>(a, ends[7], ends, bt, w, d.d_ent, n_after_s);
+      } else {
+        draw_rounds_f<8, 4>(a, ends[5], ends, bt, w, d.d_ent, n_after_s);
+        draw_rounds_f<16, 4>(ends[5], ends[7], ends, bt, w, d.d_ent, n_after_s);
+      }
+      if (lmask) draw_long_f(lmask, __ballot(fol), starts, bt, w, d.d_ent, ln / kGroup, ln % kGroup, n_after_s);
+      uint32_t topic = K1;
+      if (und) topic = finish_f<BS>(ln, bt, w, d.d_ent);
+      // the undecided tokens, by the whole wave in fp64
+      for (unsigned long long m = __ballot(und && topic == uint32_t(kDrawX)); m; m &= m - 1ull) {
+        const int q = __ffsll((long long)m) - 1;
+        const uint32_t q_off = __builtin_amdgcn_readlane(off, q), q_key = __builtin_amdgcn_readlane(key, q);
+        const uint32_t k = __builtin_amdgcn_readfirstlane(
+            exact_draw<BS>(d, p, w, ExactRow{wrow, held, held_nnz}, q_off, uniform_draw(p.seed, t, q_key), ln));
+        n_after_s += k >> 16;
+        if (ln == q) topic = k & 0xFFFFu;
+      }
+      if (j < be) d.z_w[j] = uint16_t(topic);
+    }
+    __syncthreads();
   }
-  // per-lane counts of group leaders, summed over the wave
-  n_sampled = group_sum_u32<kWave>(n_sampled);
-  n_after_s = group_sum_u32<kWave>(n_after_s);
-  nnz_sum = group_sum_u64<kWave>(nnz_sum);
   if (lane == 0)
-    store_stats(d, blockIdx.x * uint32_t(waves) + uint32_t(wave), wave == 0, n_sampled, n_after_s, nnz_sum, n_reg,
+    store_stats(d, blockIdx.x * uint32_t(NB / kWave) + uint32_t(wave), wave == 0, n_sampled, n_after_s, nnz_sum, n_reg,
                 n_dreg, row_bytes);
+}
+__global__ __launch_bounds__(256, 7) void k_sampler_f(DevState d, Params p, uint32_t t,
+                                                      unsigned long long *__restrict__ stats) {
+  sampler_f_body<256>(d, p, t, stats);
+}
+__global__ __launch_bounds__(512, 6) void k_sampler_f_512(DevState d, Params p, uint32_t t,
+                                                          unsigned long long *__restrict__ stats) {
+  sampler_f_body<512>(d, p, t, stats);
+}
+__global__ __launch_bounds__(1024, 4) void k_sampler_f_1024(DevState d, Params p, uint32_t t,
+                                                            unsigned long long *__restrict__ stats) {
+  sampler_f_body<1024>(d, p, t, stats);
 }
 
 // One statistic (0..kFoldBlocks-1) over the slots of the waves that stored
@@ -3519,6 +3691,11 @@ hipError_t launch_beta_sum(const DevState &d, const Params &p, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_word_pre(const DevState &d, const Params &p, hipStream_t s) {
+  if (p.f32) {
+    hipLaunchKernelGGL(k_block_base, dim3(uint32_t((p.K + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, d, p);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
   if (p.sparse_pre) {
     // the topic list and the sum of beta/den[k] follow the current T
     hipError_t err;
@@ -3570,38 +3747,43 @@ size_t sampler_lds_bytes(int K, int nb, bool q_table) {
   return bytes;
 }
 
-// Threads per sampler workgroup for this K: `want` when nonzero, else the
-// size with the most resident waves per CU (ties to the smaller).  LDS holds
-// the W^ row, so a large K leaves room for few workgroups and larger ones
-// keep more waves busy.  0 when the size asked for (or none) fits.
-// *q_table: whether the per-topic partial sums of the Q' blocks are kept in
-// LDS (q_draw's search instead of its walk; the same draws), which they are
-// when they leave the chosen size as many resident waves.
-static int sampler_waves(int K, int nb, bool q_table) {
-  const size_t lds = sampler_lds_bytes(K, nb, q_table);
-  hipError_t err = nb == 256 ? allow_lds(k_sampler, lds) : nb == 512 ? allow_lds(k_sampler_512, lds)
-                                                                      : allow_lds(k_sampler_1024, lds);
+// Resident waves per CU of a kernel with workgroups of nb threads and this
+// dynamic LDS (0 if it does not fit).
+template <typename F>
+static int resident_waves(F *kernel, int nb, size_t lds) {
   int blocks = 0;
-  if (err == hipSuccess)
-    err = nb == 256 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_sampler, nb, lds)
-        : nb == 512 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_sampler_512, nb, lds)
-                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_sampler_1024, nb, lds);
+  hipError_t err = allow_lds(kernel, lds);
+  if (err == hipSuccess) err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, kernel, nb, lds);
   (void)hipGetLastError();
   return err == hipSuccess ? blocks * nb / kWave : 0;
 }
-int sampler_block(int K, int want, bool *q_table) {
+// Whether the fp64 sampler (256 threads) keeps the per-topic partial sums of
+// the Q' blocks in LDS (q_draw's search instead of its walk; the same draws):
+// when they leave it as many resident waves.
+bool sampler_q_table(int K) {
+  return resident_waves(k_sampler, kBlock, sampler_lds_bytes(K, kBlock, true)) >=
+         resident_waves(k_sampler, kBlock, sampler_lds_bytes(K, kBlock, false));
+}
+
+// The single-precision sampler's dynamic LDS, and its workgroup size for K
+// topics: `want` when nonzero, else the size with the most resident waves per
+// CU (ties to the smaller).
+size_t sampler_f_lds_bytes(int K, int nb) {
+  const size_t blocks = size_t((K + kQBlockF - 1) / kQBlockF);
+  return sizeof(float) * size_t(wf_entries(K)) + sizeof(double) * (blocks + 1) +
+         size_t(nb) * (sizeof(double) + 2 * sizeof(uint32_t) + sizeof(uint16_t) + 1) + 4 * sizeof(uint32_t);
+}
+int sampler_f_block(int K, int want) {
   int best = 0, best_waves = 0;
-  const int sizes[3] = {256, 512, 1024};
-  for (int q = 0; q < 3; ++q) {
-    const int nb = sizes[q];
+  for (const int nb : {256, 512, 1024}) {
     if (want && nb != want) continue;
-    const int waves = sampler_waves(K, nb, false);
+    const int waves = resident_waves(nb == 1024 ? k_sampler_f_1024 : nb == 512 ? k_sampler_f_512 : k_sampler_f, nb,
+                                     sampler_f_lds_bytes(K, nb));
     if (waves > best_waves) {
       best = nb;
       best_waves = waves;
     }
   }
-  *q_table = best && sampler_waves(K, best, true) >= best_waves;
   return best;
 }
 
@@ -3613,42 +3795,16 @@ static hipError_t no_static_lds(const void *kernel) {
 }
 
 int tiled_topics(int K) { return ((K + 2) / 2 + kGroup - 1) / kGroup * kGroup; }
-size_t tiled_lds_bytes(int K, int kt) {
-  const size_t nb = size_t((K + kGroup - 1) / kGroup);
-  return sizeof(double) * (size_t(kt) + kGroup + nb + 1 + kTiledBlock) +
-         sizeof(uint32_t) * (kTiledBlock / kGroup * kMaxRun + 6);
-}
 hipError_t launch_sampler(const DevState &d, const Params &p, uint32_t t, hipStream_t s) {
-  if (p.big_k) {
-    // the tile must start at LDS address 0 (wt_of): no static LDS
-    static const hipError_t lds_at_0 = no_static_lds(reinterpret_cast<const void *>(k_sampler_tiled));
-    if (lds_at_0 != hipSuccess) return lds_at_0;
-    // a tile's Q' blocks: at most two per thread
-    if (p.tile_topics / kGroup + 1 > 2 * kTiledBlock) return hipErrorInvalidValue;
-    const size_t lds = tiled_lds_bytes(p.K, p.tile_topics);
-    hipError_t err = allow_lds(k_sampler_tiled, lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k_sampler_tiled, dim3(uint32_t(tiled_grid(p))), dim3(kTiledBlock), lds, s, d, p, t, d.stats);
-    return hipGetLastError();
-  }
-  const int nb = p.sampler_block;
-  const size_t lds = sampler_lds_bytes(p.K, nb, p.q_table != 0);
-  const uint32_t grid = uint32_t(sampler_grid(p));
-  hipError_t err;
   if (p.n_units == 0) return hipSuccess;  // every region is light
-  if (nb == 1024) {
-    err = allow_lds(k_sampler_1024, lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k_sampler_1024, dim3(grid), dim3(1024), lds, s, d, p, t, d.stats);
-  } else if (nb == 512) {
-    err = allow_lds(k_sampler_512, lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k_sampler_512, dim3(grid), dim3(512), lds, s, d, p, t, d.stats);
-  } else {
-    err = allow_lds(k_sampler, lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k_sampler, dim3(grid), dim3(256), lds, s, d, p, t, d.stats);
-  }
+  const size_t lds = p.f32 ? sampler_f_lds_bytes(p.K, p.sampler_block) : sampler_lds_bytes(p.K, p.sampler_block, p.q_table != 0);
+  const auto kernel = !p.f32 ? k_sampler
+                      : p.sampler_block == 1024 ? k_sampler_f_1024
+                      : p.sampler_block == 512  ? k_sampler_f_512
+                                                : k_sampler_f;
+  const hipError_t err = allow_lds(kernel, lds);
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(kernel, dim3(uint32_t(sampler_grid(p))), dim3(uint32_t(p.sampler_block)), lds, s, d, p, t, d.stats);
   return hipGetLastError();
 }
 
@@ -3804,6 +3960,18 @@ static size_t loglik_lds_bytes(int K, int nb) {
          size_t(nb) * (2 * sizeof(uint32_t) + 1) + 4 * sizeof(uint32_t);
 }
 
+int loglik_block(int K) {
+  int best = 0, best_waves = 0;
+  for (const int nb : {256, 512, 1024}) {
+    const int waves = resident_waves(nb == 1024 ? k_loglik_1024 : nb == 512 ? k_loglik_512 : k_loglik, nb, loglik_lds_bytes(K, nb));
+    if (waves > best_waves) {
+      best = nb;
+      best_waves = waves;
+    }
+  }
+  return best;
+}
+
 hipError_t launch_loglik(const DevState &d, const Params &p, hipStream_t s) {
   hipError_t err;
   if (p.big_k) {
@@ -3815,10 +3983,9 @@ hipError_t launch_loglik(const DevState &d, const Params &p, hipStream_t s) {
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(k_loglik_tiled, dim3(uint32_t(tiled_grid(p))), dim3(kTiledBlock), lds, s, d, p);
   } else if (p.n_units > 0) {
-    // the sampler's workgroup size: both hold one W^ row per workgroup
-    const int nb = p.sampler_block;
+    const int nb = p.loglik_block;
     const size_t lds = loglik_lds_bytes(p.K, nb);
-    const uint32_t grid = uint32_t(std::min<int64_t>(p.n_units, sampler_workgroups(p)));
+    const uint32_t grid = uint32_t(std::min<int64_t>(p.n_units, std::max<int64_t>(1, int64_t(p.grid_regions) * kBlock / nb)));
     if (nb == 1024) {
       err = allow_lds(k_loglik_1024, lds);
       if (err != hipSuccess) return err;

@@ -54,23 +54,21 @@ lda_status setup_device(lda_handle *h, const lda_options *o) {
   Params &p = h->p;
   p.grid_regions = std::max(1, cus * 8);
   const int want = o ? o->sampler_block : 0;
-  bool q_table = false;
-  p.sampler_block = sampler_block(p.K, want, &q_table);
-  p.q_table = q_table ? 1 : 0;
-  if (!p.sampler_block && want)
+  // A size asked for has to fit with an fp64 W^' row (what the option promises
+  // for a K does not depend on which sampler draws).
+  auto fits = [&](int nb) { return sampler_lds_bytes(p.K, nb, false) <= size_t(lds_max); };
+  if (want && !fits(want))
     return fail(h, LDA_E_RANGE, "no sampler workgroup of " + std::to_string(want) + " threads fits the LDS of K = " +
                                     std::to_string(L.K));
-  if (!p.sampler_block) {
-    // the W^' row does not fit one workgroup's LDS: the tiled sampler
-    p.big_k = 1;
-    p.tile_topics = tiled_topics(p.K);
-    p.sampler_block = kTiledThreads;
-    if (tiled_lds_bytes(p.K, p.tile_topics) > size_t(lds_max))
-      return fail(h, LDA_E_RANGE, "K = " + std::to_string(L.K) + " needs " +
-                                      std::to_string(tiled_lds_bytes(p.K, p.tile_topics)) +
-                                      " bytes of LDS per workgroup even in tiles; the device allows " +
-                                      std::to_string(lds_max));
-  }
+  p.big_k = fits(kBlock) ? 0 : 1;
+  if (p.big_k) p.tile_topics = tiled_topics(p.K);
+  else p.loglik_block = loglik_block(p.K);
+  p.f32 = use_f32(p.K, want) ? 1 : 0;
+  p.sampler_block = p.f32 ? sampler_f_block(p.K, want) : kBlock;
+  p.q_table = !p.f32 && sampler_q_table(p.K) ? 1 : 0;
+  if (!p.sampler_block || (!p.big_k && !p.loglik_block))
+    return fail(h, LDA_E_RANGE, "K = " + std::to_string(L.K) + " fits no workgroup's LDS on this device");
+  if (p.f32) LDA_TRY(dalloc(h, &h->d.qbase, size_t((p.K + kQBlockF - 1) / kQBlockF)));
   // the doc pass keeps a table of K 16-bit counts per wave; the D rebuild
   // the same table plus a bitmap of the touched topics and a list of them.
   // Waves per workgroup: the count that keeps the most waves running on a CU
@@ -257,9 +255,7 @@ lda_status create_device(lda_handle *h, const lda_options *o, const int32_t *wor
   if (p.big_k) {
     const size_t slots = size_t(tiled_grid(p)) * size_t(max_region);
     LDA_TRY(dalloc(h, &d.ts_s, slots));
-    LDA_TRY(dalloc(h, &d.ts_c1, slots));
     LDA_TRY(dalloc(h, &d.ts_code, slots));
-    LDA_TRY(dalloc(h, &d.ts_list, slots));
   }
   if (w_bits(p)) LDA_TRY(dalloc(h, &d.hist_rows, size_t(topic_hist_grid(p)) * size_t(L.K)));
   LDA_TRY(dalloc(h, &d.ll_out, 1));

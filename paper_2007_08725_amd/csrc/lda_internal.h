@@ -130,14 +130,6 @@ struct SkipRec {
   uint32_t pad;
 };
 
-// A token whose draw the tiled sampler's last pass finishes: its place in
-// the region, the recorded draw, C1 and row length, D-row offset, x and the
-// start of Q'.
-struct TiledRec {
-  uint32_t q, code, cn, off;
-  double x, keep;
-};
-
 struct DevState {
   // layout
   uint32_t *doc_off, *dt_word, *dt_key, *dt_wpos, *word_off;
@@ -167,12 +159,10 @@ struct DevState {
   unsigned long long *wave_stats; // [kFoldBlocks][kWaveSlots]: per wave of the samplers and the doc pass (StatSlots)
   double *ll_part;              // [n_units + n_light_batches] (large K: [n_regions])
   double *ll_out;               // [1]
-  // large K only (the tiled sampler): per-workgroup slices of max_region
-  // entries carrying a token's S' part, C1 and split chunk between passes,
-  // the records of the region's tokens whose draw finishes in the last pass
+  // large K only (k_loglik_tiled): per-workgroup slices of max_region entries
+  // carrying a token's sum and split chunk from the first tile to the second
   double *ts_s;
-  uint32_t *ts_c1, *ts_code;
-  TiledRec *ts_list;
+  uint32_t *ts_code;
   uint32_t *hist_rows;  // large K: the rows of k_topic_hist
   // p.sparse_pre: topics by ascending T (descending beta/den[k]),
   // their sort buffers, and the sum of beta/den[k] over all topics
@@ -180,6 +170,7 @@ struct DevState {
   void *topic_tmp;
   size_t topic_tmp_bytes;
   double *beta_sum;
+  double *qbase;  // p.f32: per block of kQBlockF topics the sum of alpha * beta/den[k]
 };
 
 struct Params {
@@ -197,8 +188,8 @@ struct Params {
   int32_t grid_regions;  // persistent workgroups for region kernels
   int32_t sampler_block; // threads per sampler workgroup: 256, 512 or 1024
   int32_t grid_docs;     // persistent workgroups for doc kernels
-  int32_t big_k;         // the W^' row does not fit LDS: tiled sampler, LDS-light rebuilds (K <= 32768)
-  int32_t tile_topics;   // topics per tile of the tiled sampler (a multiple of 16)
+  int32_t big_k;         // the fp64 W^ row does not fit LDS: tiled LLPT, LDS-light rebuilds (K <= 32768)
+  int32_t tile_topics;   // topics per tile of k_loglik_tiled (a multiple of 16)
   int32_t max_region;    // tokens of the largest region
   int32_t doc_waves;     // waves per workgroup of the doc pass and the D rebuild (LDS tables of K entries per wave)
   uint32_t doc_batch, rebuild_batch;  // documents a wave takes per counter atomic (doc pass, D rebuild)
@@ -213,6 +204,8 @@ struct Params {
   int64_t light_begin;   // regions [light_begin, n_regions): light words, drawn by single waves
   int32_t n_light_batches;  // entries of light_batch, less one
   int32_t doc_marks_ok;  // the document-ordered bitmap is usable: keys are document positions, regular sampler
+  int32_t loglik_block;  // threads per workgroup of the LLPT kernel (its W^ row is fp64)
+  int32_t f32;           // the sampler keeps W^' in single precision (use_f32)
   int32_t q_table;       // the sampler keeps the Q' blocks' partial sums in LDS (search instead of walk)
   uint32_t xcd_doc[kXcds + 1];  // document ranges with equal token counts, one per XCD (D rebuild)
 };
@@ -258,7 +251,7 @@ constexpr int kStatsPerIter = 16;
 enum { WV_SAMPLED, WV_AFTER_S, WV_NNZ, WV_REGIONS, WV_DENSE_REGIONS, WV_ROW_BYTES, WV_SKIP3 };
 constexpr int kFoldBlocks = 7;  // one per statistic
 constexpr size_t kWaveSlots = size_t(1) << 15;
-// Waves that store statistics in iteration t: the main (or tiled) sampler's
+// Waves that store statistics in iteration t: the main sampler's
 // slots come first, then the light sampler's; the doc pass's have a row of
 // their own.
 struct StatSlots {
@@ -277,12 +270,25 @@ hipError_t launch_beta_sum(const DevState &d, const Params &p, hipStream_t s);
 hipError_t launch_clear_skips(const DevState &d, const Params &p, uint32_t t, hipStream_t s, bool reset_count = true);
 hipError_t launch_reset_counters(uint32_t *counters, hipStream_t s);
 hipError_t launch_doc_pass(const DevState &d, const Params &p, uint32_t t, hipStream_t s);
-// The sampler of the regions before p.light_begin (or every region with the
-// tiled sampler), and that of the light regions, by single waves (nothing when
+// The sampler of the regions before p.light_begin, and that of the light regions, by single waves (nothing when
 // there are none); the two touch disjoint topic slots and may run at once.
 hipError_t launch_sampler(const DevState &d, const Params &p, uint32_t t, hipStream_t s);
 hipError_t launch_sampler_light(const DevState &d, const Params &p, uint32_t t, hipStream_t s);
-int sampler_block(int K, int want, bool *q_table);
+bool sampler_q_table(int K);
+// The sampler that keeps W^' in single precision and certifies its draws:
+// topics per block of its Q' prefix, its workgroup size and dynamic LDS, and
+// the K it is used from: where the fp64 row starts to limit the resident
+// waves (22.8 KB a workgroup for 7 workgroups per CU).  Below, the fp64 one is
+// as fast or faster (144M tokens at K = 1,000: 7.66 ms, the other 7.87), above
+// not (33M at K = 10,000: 9.8 against 6.7 ms; 20M at 32,768, where fp64 took
+// the row in two tiles: 15.8 against 8.7).  Workgroups of 512 and 1,024
+// threads (an option) are its own at every K.
+constexpr int kQBlockF = 32;
+constexpr int kF32Topics = 2300;
+inline bool use_f32(int32_t K, int32_t want_block) { return K >= kF32Topics || (want_block != 0 && want_block != kBlock); }
+int sampler_f_block(int K, int want);
+size_t sampler_f_lds_bytes(int K, int nb);
+int loglik_block(int K);  // threads per workgroup of k_loglik (the most resident waves)
 // The sampler's dynamic LDS for K topics and workgroups of nb threads.
 size_t sampler_lds_bytes(int K, int nb, bool q_table);
 // Regions of at most this many tokens (one batch of the sampler) are light:
@@ -319,19 +325,16 @@ __host__ __device__ inline int64_t sampler_workgroups(const Params &p) {
 // offsets from light_begin: at most 64 tokens each, fewer (down to 16) when
 // that would leave the light sampler's waves without a batch.
 std::vector<uint32_t> light_batches(const std::vector<uint32_t> &region, int64_t light_begin, int64_t waves);
-// Large K: topics per tile and the tiled sampler's dynamic LDS.
+// Large K: topics per tile of k_loglik_tiled.
 int tiled_topics(int K);
-size_t tiled_lds_bytes(int K, int kt);
-constexpr int kTiledThreads = 1024;
-// Workgroups of the tiled sampler and LLPT kernel (one per CU: their LDS fills
-// a CU) and of k_topic_hist; the scratch slices are sized for these grids.
+// Workgroups of k_loglik_tiled (one per CU: its LDS fills a CU) and of
+// k_topic_hist; the scratch slices are sized for these grids.
 __host__ __device__ inline int tiled_grid(const Params &p) { return p.grid_regions / 8 > 0 ? p.grid_regions / 8 : 1; }
 inline int topic_hist_grid(const Params &p) { return tiled_grid(p); }
-// Workgroups of the main (or tiled) and of the light sampler (at most 16
+// Workgroups of the main and of the light sampler (at most 16
 // one-wave workgroups per CU; grid_regions is 8 per CU), and the statistics
 // slots of an iteration's launches.
 __host__ __device__ inline int32_t sampler_grid(const Params &p) {
-  if (p.big_k) return tiled_grid(p);
   const int64_t w = sampler_workgroups(p);
   return int32_t(p.n_units < w ? p.n_units : w);
 }
@@ -349,7 +352,7 @@ __host__ __device__ inline StatSlots stat_slots(const Params &p, uint32_t t) {
 }
 // Whether every launch's waves have a slot (grids follow the device's CUs).
 inline bool stat_slots_fit(const Params &p) {
-  const int64_t main = p.big_k ? int64_t(tiled_grid(p)) : sampler_workgroups(p);
+  const int64_t main = sampler_workgroups(p);
   return main * (p.sampler_block / 64) + 2 * int64_t(p.grid_regions) <= int64_t(kWaveSlots) &&
          int64_t(std::max(p.grid_docs, kXcds)) * p.doc_waves <= int64_t(kWaveSlots);
 }
