@@ -2249,26 +2249,45 @@ __device__ void draw_long_f(unsigned long long mask, unsigned long long foll, un
       const uint32_t *row = d_ent + off0;  // slot 0 is the row header
       const uint32_t pad = uint32_t(w.K) << 16;
       const uint32_t slots = d_row_slots(bt.nnz[src]), nch = (slots + kChunk - 1) / kChunk;
-      uint32_t r[kRun];
-      double s = 0.0, incl = 0.0, S = 0.0;
-      double tot = 0.0;  // lane c of the group (c < kGroup): the total of chunk c
-      uint32_t c1 = 0xFFFFFFFFu;
-      for (uint32_t ch = 0; ch < nch; ++ch) {
-        load_run_masked(row, ch, slots, li, pad, r);
-        c1 = run_count_of<kRun>(r, w.K1, c1);
-        s = run_sum_f<false>(r, w.wf);
+      // the row's chunks, two loaded together; lane c of the group keeps the
+      // total of the c-th m chunks, so that a draw walks only those m again
+      const uint32_t m = (nch + uint32_t(kGroup) - 1u) / uint32_t(kGroup);
+      uint32_t r[kRun], r2[kRun];
+      double s = 0.0, incl = 0.0, S = 0.0, tot = 0.0;
+      uint32_t c1 = 0xFFFFFFFFu, sup = 0, in_sup = 0;
+      auto chunk = [&](const uint32_t (&rc)[kRun]) {
+        c1 = run_count_of<kRun>(rc, w.K1, c1);
+        s = run_sum_f<false>(rc, w.wf);
         incl = row_incl_scan(s);
         const double tch = __shfl(incl, kGroup - 1, kGroup);
         S += tch;
-        tot = uint32_t(li) == ch ? tch : tot;
+        tot += uint32_t(li) == sup ? tch : 0.0;
+        if (++in_sup == m) {
+          in_sup = 0;
+          ++sup;
+        }
+      };
+      if (nch == 1) {
+        load_run_masked(row, 0, slots, li, pad, r);
+        chunk(r);
+      } else {
+        // a row of several chunks: its slots are whole chunks, or 64 past one
+        for (uint32_t ch = 0; ch < nch; ch += 2) {
+          load_run_masked(row, ch, slots, li, pad, r);
+          if (ch + 1 < nch) {
+            load_run_masked(row, ch + 1, slots, li, pad, r2);
+            chunk(r);
+            chunk(r2);
+          } else {
+            chunk(r);
+          }
+        }
       }
       const double Mm = w.a1 * (double(row_sum_u32(c1 <= 0xFFFFu ? c1 : 0u)) + w.alpha);
-      // with the totals kept in the lanes: lane c's chunk base, added left to right
-      const bool kept = nch > 1 && nch <= uint32_t(kGroup);
-      double mine = Mm;
-      if (kept) {
+      double mine = Mm;  // lane c's base: M and the totals before it, left to right
+      {
         double cb = Mm;
-        for (uint32_t c = 0; c < nch; ++c) {
+        for (uint32_t c = 0; c * m < nch; ++c) {
           mine = uint32_t(li) == c ? cb : mine;
           cb += __shfl(tot, int(c), kGroup);
         }
@@ -2283,18 +2302,12 @@ __device__ void draw_long_f(unsigned long long mask, unsigned long long foll, un
           uint32_t cs = 0;
           double base = Mm;
           bool found = nch == 1;
-          if (kept) {
-            const uint32_t hm = uint32_t(__ballot(uint32_t(li) < nch && x < mine + tot) >> (grp * kGroup)) & kGroupMask;
-            found = hm != 0u;
-            if (found) {
-              cs = uint32_t(__ffs(hm) - 1);
-              base = __shfl(mine, int(cs), kGroup);
-              load_run_masked(row, cs, slots, li, pad, r);
-              s = run_sum_f<false>(r, w.wf);
-              incl = row_incl_scan(s);
-            }
-          } else if (nch > 1) {
-            for (uint32_t ch = 0; ch < nch && !found; ++ch) {
+          if (nch > 1) {
+            const uint32_t hm = uint32_t(__ballot(uint32_t(li) * m < nch && x < mine + tot) >> (grp * kGroup)) & kGroupMask;
+            const uint32_t sel = hm ? uint32_t(__ffs(hm) - 1) : uint32_t(kGroup);
+            base = __shfl(mine, int(sel & (kGroup - 1)), kGroup);
+            const uint32_t to = hm ? min(nch, (sel + 1u) * m) : 0u;
+            for (uint32_t ch = sel * m; ch < to && !found; ++ch) {
               load_run_masked(row, ch, slots, li, pad, r);
               s = run_sum_f<false>(r, w.wf);
               incl = row_incl_scan(s);

@@ -62,3 +62,20 @@ def test_extreme_priors(K, alpha, beta):
 @pytest.mark.parametrize("K", [2500, 20_000])
 def test_two_branch(K):
     _check(K, 0.05, 0.01, {}, two=True)
+
+
+def test_rows_of_many_chunks():
+    """Rows past 16 chunks of 128 slots (a lane's total covers several), whole and ragged, with runs of one word."""
+    import paper_2007_08725_amd as lda
+    rng = np.random.default_rng(8)
+    K = 20_000
+    lens = [1900, 2040, 2300, 4100, 6200, 9000, 16_500, 30_000]
+    doc = np.repeat(np.arange(len(lens), dtype=np.int32), lens)
+    word = rng.choice(60, doc.size, p=np.r_[0.5, np.full(59, 0.5 / 59)]).astype(np.int32)
+    z = rng.integers(0, K, doc.size).astype(np.int32)
+    kw = dict(M=len(lens), V=60, K=K, alpha=0.05, beta=0.01)
+    with lda.LDA(word, doc, 60, K, 0.05, 0.01, SEED) as m:
+        m.set_assignments(z, 1)
+        want, flags, _ = oracle.iterate(word, doc, z, seed=SEED, t=1, **kw)
+        m.iterate(1)
+        compare_draws(m.counts(D=False, W=False)["z"], want, flags, max(word.size, 10 ** 6))
