@@ -2070,13 +2070,18 @@ constexpr int kTiledAhead = 2;              // chunks whose loads a group issues
 // 10,000, 6e-3 at 32,768 in a fit's early iterations) a wave redoes the token
 // with all of its arithmetic in fp64 (exact_draw).  Either way the
 // topic is the one the fp64 evaluation gives.
-//   x near M:        x - M is off by at most u * e,            e = kEps * S'
-//   x inside S':     x - (M + prefix): at most 2 * e
-//   x near M + S', and inside Q': x - (M + S'): at most (1 - u) * e
+//   x against M and inside S': x - (M + prefix) is off by at most
+//                              2 * e, e = kEps * S'
+//   x inside Q':               x - (M + S') by at most (1 - u) * e, where
+//                              1 - u < Q' / Z <= Q' / (S' + Q')
 // tau = 2^-40 Z + 2^-90 on top covers the fp64 roundings (some 2^-50 of Z)
-// and fp32 underflow (terms below 2^-126, fewer than 2^31 of them).
+// and fp32 underflow (terms below 2^-126, fewer than 2^31 of them).  The
+// rounds only take x and the branch from the sums as they are; the bounds are
+// checked once per token by finish_f.  A wrong branch or run cannot pass: x
+// then lies outside the segment, or within the bound of its edge.
 constexpr double kEps = 9.5 * 0x1p-24;
 constexpr uint16_t kDrawX = 0xFFFD;  // undecided: exact_draw
+constexpr uint16_t kDrawM = 0xFFFC;  // in the max-topic branch, not checked yet
 constexpr double kWScale = 0x1p24;   // the row holds W^' * 2^24
 // Documents longer than this may hold a count that is not exact as the f16
 // bits of fma_mix (an integer below 2^11 in the low half of an entry reads as
@@ -2117,26 +2122,15 @@ __device__ __forceinline__ double run_sum_f(const uint32_t (&r)[kRun], const flo
   }
   return Mix ? double(s) : double(s) * (1.0 / kWScale);
 }
-__device__ __forceinline__ double tau_of(double Z) { return Z * 0x1p-40 + 0x1p-90; }
-
-// What a round leaves of a token for finish_f: for an S' draw the run (bt.off)
-// and x inside it (bt.u), for a Q' draw x past M + S'; the bound on the error
-// of x and of the run's start in bt.nnz, as a float rounded up.
-__device__ __forceinline__ uint32_t bound_bits(double e) { return __float_as_uint(float(e) * (1.0f + 0x1p-20f)); }
-
-// x's branch for a token with M, S' (off by at most e) and u: 0 = M, 1 = S',
-// 2 = Q', 3 = too near an edge to tell.
-__device__ __forceinline__ int branch_of(double x, double Mm, double S, double u, double e, double tau) {
-  if (fabs(x - Mm) <= u * e + tau || fabs(x - (Mm + S)) <= (1.0 - u) * e + tau) return 3;
-  return x < Mm ? 0 : x < Mm + S ? 1 : 2;
-}
+// What a round leaves of a token for finish_f: S' in bt.nnz (as a float) and,
+// in bt.u, M - x for a draw in M, x inside the run for S' (the run in bt.off),
+// x past M + S' for Q'.
 
 // One round of small-group draws, as draw_small.
 template <int G, int NC>
 __device__ void draw_small_f(const BatchLds &bt, int slot, int n, const WordF &w, const uint32_t *__restrict__ d_ent,
-                             int li, uint32_t &after_s) {
+                             int li) {
   constexpr uint32_t kSpan = uint32_t(G) * kRun;
-  bool in_m = false;
   if (slot < n) {
     const int src = bt.list[slot];
     const uint32_t nc = (bt.nnz[src] + 1u + kSpan - 1) / kSpan;  // slots: header + entries
@@ -2167,10 +2161,9 @@ __device__ void draw_small_f(const BatchLds &bt, int slot, int n, const WordF &w
     }
     c1 = gmin_u32<G>(c1);
     const double Mm = w.a1 * (double(c1 <= 0xFFFFu ? c1 : 0u) + w.alpha);  // Eq. 7
-    const double Z = (Mm + S) + w.qp, x = u * Z, e = kEps * S, tau = tau_of(Z);
-    const int br = branch_of(x, Mm, S, u, e, tau);
-    in_m = br == 0;
-    if (br == 1) {
+    const double x = u * ((Mm + S) + w.qp);
+    if (li == 0) bt.nnz[src] = __float_as_uint(float(S));
+    if (x >= Mm && x < Mm + S) {
       int cs = 0;
       double base = Mm, sc = s[0];
 #pragma unroll
@@ -2186,24 +2179,18 @@ __device__ void draw_small_f(const BatchLds &bt, int slot, int n, const WordF &w
       if (li == sel) {
         bt.off[src] = (off0 + uint32_t(cs) * kSpan + uint32_t(li) * kRun) | (cs == 0 && li == 0 ? 1u : 0u);
         bt.u[src] = x - (base + (incl - sc));
-        bt.nnz[src] = bound_bits(2.0 * e + tau);
         bt.top[src] = kDrawS;
       }
     } else if (li == 0) {
-      if (br == 2) {
-        bt.u[src] = x - (Mm + S);
-        bt.nnz[src] = bound_bits((1.0 - u) * e + tau);
-      }
-      bt.top[src] = br == 0 ? uint16_t(w.K1) : br == 2 ? kDrawQ : kDrawX;
+      bt.u[src] = x < Mm ? Mm - x : x - (Mm + S);
+      bt.top[src] = x < Mm ? kDrawM : kDrawQ;
     }
   }
-  // outside the divergent part, so the count stays wave-uniform
-  after_s += uint32_t(__popcll(__ballot(in_m && li == 0)));
 }
 
 template <int G, int MaxNC>
 __device__ void draw_rounds_f(int from, int to, const int (&ends)[8], const BatchLds &bt, const WordF &w,
-                              const uint32_t *__restrict__ d_ent, uint32_t &after_s) {
+                              const uint32_t *__restrict__ d_ent) {
   constexpr uint32_t kSpan = uint32_t(G) * kRun;
   for (int base = from; base < to; base += kWave / G) {
     const int ln = lane_here(), g = ln / G, li = ln % G;
@@ -2214,17 +2201,17 @@ __device__ void draw_rounds_f(int from, int to, const int (&ends)[8], const Batc
     const uint32_t nc = (upper + kSpan - 1) / kSpan;
     const int slot = base + g;
     if (nc <= 1) {
-      draw_small_f<G, 1>(bt, slot, to, w, d_ent, li, after_s);
+      draw_small_f<G, 1>(bt, slot, to, w, d_ent, li);
     } else if (nc == 2) {
-      draw_small_f<G, 2>(bt, slot, to, w, d_ent, li, after_s);
+      draw_small_f<G, 2>(bt, slot, to, w, d_ent, li);
     } else if (nc == 3) {
-      draw_small_f<G, 3>(bt, slot, to, w, d_ent, li, after_s);
+      draw_small_f<G, 3>(bt, slot, to, w, d_ent, li);
     } else if (MaxNC <= 4 || nc == 4) {
-      draw_small_f<G, 4>(bt, slot, to, w, d_ent, li, after_s);
+      draw_small_f<G, 4>(bt, slot, to, w, d_ent, li);
     } else {
       if constexpr (MaxNC > 4) {
-        if (nc <= 6) draw_small_f<G, 6>(bt, slot, to, w, d_ent, li, after_s);
-        else draw_small_f<G, MaxNC>(bt, slot, to, w, d_ent, li, after_s);
+        if (nc <= 6) draw_small_f<G, 6>(bt, slot, to, w, d_ent, li);
+        else draw_small_f<G, MaxNC>(bt, slot, to, w, d_ent, li);
       }
     }
   }
@@ -2234,8 +2221,7 @@ __device__ void draw_rounds_f(int from, int to, const int (&ends)[8], const Batc
 // tokens, four at a time, one per 16-lane group, as draw_long: the later
 // tokens of a run of one word in one document draw from the first one's sums.
 __device__ void draw_long_f(unsigned long long mask, unsigned long long foll, unsigned long long starts,
-                            const BatchLds &bt, const WordF &w, const uint32_t *__restrict__ d_ent, int grp, int li,
-                            uint32_t &after_s) {
+                            const BatchLds &bt, const WordF &w, const uint32_t *__restrict__ d_ent, int grp, int li) {
   mask &= ~foll;  // the runs' first tokens
   while (mask) {
     const unsigned long long m1 = mask & (mask - 1ull), m2 = m1 & (m1 - 1ull), m3 = m2 & (m2 - 1ull);
@@ -2243,7 +2229,6 @@ __device__ void draw_long_f(unsigned long long mask, unsigned long long foll, un
     const int f2 = __ffsll((long long)m2) - 1, f3 = __ffsll((long long)m3) - 1;
     mask = m3 & (m3 - 1ull);
     const int src = grp == 0 ? f0 : grp == 1 ? f1 : grp == 2 ? f2 : f3;
-    uint32_t n_m = 0;  // draws of this group in the max-topic branch
     if (src >= 0) {
       const uint32_t off0 = bt.off[src];
       const uint32_t *row = d_ent + off0;  // slot 0 is the row header
@@ -2292,13 +2277,12 @@ __device__ void draw_long_f(unsigned long long mask, unsigned long long foll, un
           cb += __shfl(tot, int(c), kGroup);
         }
       }
-      const double Z = (Mm + S) + w.qp, e = kEps * S, tau = tau_of(Z);
+      const double Z = (Mm + S) + w.qp;
       auto draw = [&](int tok) {
-        const double u = bt.u[tok], x = u * Z;
-        const int br = branch_of(x, Mm, S, u, e, tau);
-        uint16_t code = br == 0 ? uint16_t(w.K1) : br == 2 ? kDrawQ : kDrawX;
-        n_m += br == 0 ? 1u : 0u;
-        if (br == 1) {
+        const double x = bt.u[tok] * Z;
+        uint16_t code = x < Mm ? kDrawM : kDrawQ;
+        if (x >= Mm && x < Mm + S) {
+          code = kDrawX;
           uint32_t cs = 0;
           double base = Mm;
           bool found = nch == 1;
@@ -2327,8 +2311,8 @@ __device__ void draw_long_f(unsigned long long mask, unsigned long long foll, un
           }
         }
         if (li == 0) {
-          if (br == 2) bt.u[tok] = x - (Mm + S);
-          bt.nnz[tok] = bound_bits(br == 1 ? 2.0 * e + tau : (1.0 - u) * e + tau);
+          if (code == kDrawM || code == kDrawQ) bt.u[tok] = x < Mm ? Mm - x : x - (Mm + S);
+          bt.nnz[tok] = __float_as_uint(float(S));
           bt.top[tok] = code;
         }
       };
@@ -2339,8 +2323,6 @@ __device__ void draw_long_f(unsigned long long mask, unsigned long long foll, un
       unsigned long long fl = foll & after & (nxt ? (nxt & (0ull - nxt)) - 1ull : ~0ull);
       for (; fl; fl &= fl - 1ull) draw(__ffsll((long long)fl) - 1);
     }
-    // outside the divergent part, so the count stays wave-uniform
-    after_s += wave_sum_u32(li == 0 ? n_m : 0u);
   }
 }
 
@@ -2359,11 +2341,14 @@ __device__ __forceinline__ int q_block_f(const WordF &w, double xq) {
 // edge of the segment lies within the bound.
 template <int BS>
 __device__ __forceinline__ uint32_t finish_f(int q, const BatchLds &bt, const WordF &w,
-                                             const uint32_t *__restrict__ d_ent) {
+                                             const uint32_t *__restrict__ d_ent, uint32_t len) {
   const uint32_t code = bt.top[q];
-  if (code != kDrawS && code != kDrawQ) return code;
+  if (code == kDrawX) return kDrawX;
   const double xs = bt.u[q];
-  const float e = __uint_as_float(bt.nnz[q]);
+  const double S = double(__uint_as_float(bt.nnz[q])) * (1.0 + 0x1p-20);  // rounded up
+  const double tau = (w.a1 * (double(len) + w.alpha) + S + w.qp) * 0x1p-40 + 0x1p-90;  // C1 <= len
+  const double e2 = 2.0 * kEps * S + tau;
+  if (code == kDrawM) return xs > e2 ? uint32_t(kDrawM) : uint32_t(kDrawX);
   if (code == kDrawS) {
     const uint32_t a = bt.off[q];
     uint32_t r[kRun];
@@ -2380,9 +2365,10 @@ __device__ __forceinline__ uint32_t finish_f(int q, const BatchLds &bt, const Wo
     }
     // the chosen entry's edges
     const double above = __builtin_fma(double(ent & 0xFFFFu), double(wf_of(w.wf, ent)) * (1.0 / kWScale), below);
-    return xs - below > double(e) && above - xs > double(e) && below >= 0.0 ? ent >> 16 : uint32_t(kDrawX);
+    return xs - below > e2 && above - xs > e2 && below >= 0.0 ? ent >> 16 : uint32_t(kDrawX);
   }
   if (!(xs < w.qb[w.nb]) || !(xs >= 0.0)) return kDrawX;
+  const double eq1 = kEps * S * (w.qp / (S + w.qp)) * (1.0 + 0x1p-20) + tau;
   const int lo = q_block_f(w, xs);
   // inside the block in fp32, in units of alpha * 2^-24: x rounded once, at
   // most BS + 1 roundings in a partial sum, two more in the comparison
@@ -2399,7 +2385,7 @@ __device__ __forceinline__ uint32_t finish_f(int q, const BatchLds &bt, const Wo
     p += wb[i];
   }
   const float above = below + wb[at];
-  const float eq = e * inv * (1.0f + 0x1p-20f) + (p + xb) * (float(BS + 4) * 0x1p-24f);
+  const float eq = float(eq1) * inv * (1.0f + 0x1p-20f) + (p + xb) * (float(BS + 4) * 0x1p-24f);
   return xb - below > eq && above - xb > eq ? uint32_t(lo * BS + at) : uint32_t(kDrawX);
 }
 
@@ -2474,13 +2460,14 @@ __device__ uint32_t exact_draw(const DevState &d, const Params &p, const WordF &
 // Entries of the single-precision row: K + 1 rounded up to whole waves.
 __host__ __device__ inline int wf_entries(int K) { return (K + kWave) / kWave * kWave; }
 
-// Per iteration: qbase[b] = sum of alpha * beta/den[k] over block b of
-// kQBlockF topics, what a sparse word's Q' prefix starts from.
+// Per iteration: qbase[b] = sum of alpha * beta/den[k] over block b of BS
+// topics, what a sparse word's Q' prefix starts from.
+template <int BS>
 __global__ __launch_bounds__(kBlock) void k_block_base(DevState d, Params p) {
   const int k = int(blockIdx.x) * kBlock + int(threadIdx.x);
   double v = k < p.K ? p.alpha * d.bden[k] : 0.0;
-  v = group_sum<kQBlockF>(v);
-  if (k % kQBlockF == 0 && k < p.K) d.qbase[k / kQBlockF] = v;
+  v = group_sum<BS>(v);
+  if (k % BS == 0 && k < p.K) d.qbase[k / BS] = v;
 }
 
 // The sampler of the units, NB threads per workgroup: as sampler_body, with
@@ -2495,7 +2482,7 @@ template <int NB>
 __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
                                                unsigned long long *__restrict__ stats) {
   extern __shared__ double lds[];
-  constexpr int BS = kQBlockF;
+  constexpr int BS = q_block_topics(NB);
   const int K = p.K;
   const int nb = (K + BS - 1) / BS;
   const int nwf = wf_entries(K);
@@ -2669,16 +2656,18 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
       }
       const int left = ends[3] % 16;
       const int a = left > 0 && left <= 8 && ends[3] - ends[2] >= left ? ends[3] - left : ends[3];
-      draw_rounds_f<4, 4>(0, a, ends, bt, w, d.d_ent, n_after_s);
+      draw_rounds_f<4, 4>(0, a, ends, bt, w, d.d_ent);
       if (NB >= 1024) {
-        draw_rounds_f<8, 8>(a, ends[7], ends, bt, w, d.d_ent, n_after_s);
+        draw_rounds_f<8, 8>(a, ends[7], ends, bt, w, d.d_ent);
       } else {
-        draw_rounds_f<8, 4>(a, ends[5], ends, bt, w, d.d_ent, n_after_s);
-        draw_rounds_f<16, 4>(ends[5], ends[7], ends, bt, w, d.d_ent, n_after_s);
+        draw_rounds_f<8, 4>(a, ends[5], ends, bt, w, d.d_ent);
+        draw_rounds_f<16, 4>(ends[5], ends[7], ends, bt, w, d.d_ent);
       }
-      if (lmask) draw_long_f(lmask, __ballot(fol), starts, bt, w, d.d_ent, ln / kGroup, ln % kGroup, n_after_s);
+      if (lmask) draw_long_f(lmask, __ballot(fol), starts, bt, w, d.d_ent, ln / kGroup, ln % kGroup);
       uint32_t topic = K1;
-      if (und) topic = finish_f<BS>(ln, bt, w, d.d_ent);
+      if (und) topic = finish_f<BS>(ln, bt, w, d.d_ent, hdr >> 16);
+      n_after_s += uint32_t(__popcll(__ballot(topic == uint32_t(kDrawM))));
+      topic = topic == uint32_t(kDrawM) ? K1 : topic;
       // the undecided tokens, by the whole wave in fp64
       for (unsigned long long m = __ballot(und && topic == uint32_t(kDrawX)); m; m &= m - 1ull) {
         const int q = __ffsll((long long)m) - 1;
@@ -3705,7 +3694,8 @@ hipError_t launch_beta_sum(const DevState &d, const Params &p, hipStream_t s) {
 }
 hipError_t launch_word_pre(const DevState &d, const Params &p, hipStream_t s) {
   if (p.f32) {
-    hipLaunchKernelGGL(k_block_base, dim3(uint32_t((p.K + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, d, p);
+    const auto base = q_block_topics(p.sampler_block) == 16 ? k_block_base<16> : k_block_base<32>;
+    hipLaunchKernelGGL(base, dim3(uint32_t((p.K + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, d, p);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
@@ -3782,7 +3772,7 @@ bool sampler_q_table(int K) {
 // topics: `want` when nonzero, else the size with the most resident waves per
 // CU (ties to the smaller).
 size_t sampler_f_lds_bytes(int K, int nb) {
-  const size_t blocks = size_t((K + kQBlockF - 1) / kQBlockF);
+  const size_t blocks = size_t((K + q_block_topics(nb) - 1) / q_block_topics(nb));
   return sizeof(float) * size_t(wf_entries(K)) + sizeof(double) * (blocks + 1) +
          size_t(nb) * (sizeof(double) + 2 * sizeof(uint32_t) + sizeof(uint16_t) + 1) + 4 * sizeof(uint32_t);
 }

@@ -68,7 +68,7 @@ lda_status setup_device(lda_handle *h, const lda_options *o) {
   p.q_table = !p.f32 && sampler_q_table(p.K) ? 1 : 0;
   if (!p.sampler_block || (!p.big_k && !p.loglik_block))
     return fail(h, LDA_E_RANGE, "K = " + std::to_string(L.K) + " fits no workgroup's LDS on this device");
-  if (p.f32) LDA_TRY(dalloc(h, &h->d.qbase, size_t((p.K + kQBlockF - 1) / kQBlockF)));
+  if (p.f32) LDA_TRY(dalloc(h, &h->d.qbase, size_t((p.K + q_block_topics(p.sampler_block) - 1) / q_block_topics(p.sampler_block))));
   // the doc pass keeps a table of K 16-bit counts per wave; the D rebuild
   // the same table plus a bitmap of the touched topics and a list of them.
   // Waves per workgroup: the count that keeps the most waves running on a CU

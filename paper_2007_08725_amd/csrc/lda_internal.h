@@ -170,7 +170,7 @@ struct DevState {
   void *topic_tmp;
   size_t topic_tmp_bytes;
   double *beta_sum;
-  double *qbase;  // p.f32: per block of kQBlockF topics the sum of alpha * beta/den[k]
+  double *qbase;  // p.f32: per block of q_block_topics topics the sum of alpha * beta/den[k]
 };
 
 struct Params {
@@ -283,7 +283,8 @@ bool sampler_q_table(int K);
 // not (33M at K = 10,000: 9.8 against 6.7 ms; 20M at 32,768, where fp64 took
 // the row in two tiles: 15.8 against 8.7).  Workgroups of 512 and 1,024
 // threads (an option) are its own at every K.
-constexpr int kQBlockF = 32;
+// (16 with 256 threads, where the LDS has room for K / 16 doubles, else 32)
+__host__ __device__ constexpr int q_block_topics(int threads) { return threads == 256 ? 16 : 32; }
 constexpr int kF32Topics = 2300;
 inline bool use_f32(int32_t K, int32_t want_block) { return K >= kF32Topics || (want_block != 0 && want_block != kBlock); }
 int sampler_f_block(int K, int want);
