@@ -188,14 +188,15 @@ inline std::vector<uint32_t> heavy_documents(const uint32_t *doc_off, uint32_t M
 // whatever is queued next, beside the main sampler.
 inline lda_status run_sampler(lda_handle *h, const DevState &d, const Params &p, uint32_t t) {
   const bool light = p.light_begin < p.n_regions;
+  if (light) HIP_TRY(h, hipEventRecord(h->fork_ev, h->stream));
+  // the main sampler first: the light one's waves then fill the CUs as it drains
+  HIP_TRY(h, launch_sampler(d, p, t, h->stream));
   if (light) {
-    HIP_TRY(h, hipEventRecord(h->fork_ev, h->stream));
     HIP_TRY(h, hipStreamWaitEvent(h->side, h->fork_ev, 0));
     HIP_TRY(h, launch_sampler_light(d, p, t, h->side));
     HIP_TRY(h, hipEventRecord(h->join_ev, h->side));
+    HIP_TRY(h, hipStreamWaitEvent(h->stream, h->join_ev, 0));
   }
-  HIP_TRY(h, launch_sampler(d, p, t, h->stream));
-  if (light) HIP_TRY(h, hipStreamWaitEvent(h->stream, h->join_ev, 0));
   return LDA_OK;
 }
 

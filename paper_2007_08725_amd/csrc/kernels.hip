@@ -131,6 +131,11 @@ __device__ __forceinline__ double wave_incl_scan(double v) {
   return v;
 }
 
+// A double from lane l (uniform) to every lane.
+__device__ __forceinline__ double readlane_f64(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
 constexpr int kTop = 4;  // top values of W^[v] kept per word (a1..a4 of Eq. 9, g <= 3)
 
 struct TopN {
@@ -1778,6 +1783,27 @@ __global__ __launch_bounds__(256, 7) void k_sampler(DevState d, Params p, uint32
                                                  unsigned long long *__restrict__ stats) {
   sampler_body<256>(d, p, t, stats);
 }
+// W^ of a dense row into a wave's LDS row, kLightAhead topics per lane loaded
+// together (one after another each topic waited for memory: out of core, where
+// every light word is a dense row, 1.20 ms a chunk of 123,000 words).
+constexpr int kLightAhead = 8;
+__device__ __forceinline__ void fill_dense_wave(const int32_t *__restrict__ wrow, const double *__restrict__ den,
+                                                double beta, int K, int lane, double *__restrict__ wh) {
+  for (int k0 = lane; k0 < K; k0 += kLightAhead * kWave) {
+    uint32_t c[kLightAhead];
+    double dn[kLightAhead];
+#pragma unroll
+    for (int u = 0; u < kLightAhead; ++u) {
+      const int k = min(k0 + u * kWave, K - 1);
+      c[u] = uint32_t(wrow[k]);
+      dn[u] = den[k];
+    }
+#pragma unroll
+    for (int u = 0; u < kLightAhead; ++u)
+      if (k0 + u * kWave < K) wh[k0 + u * kWave] = what(c[u], beta, dn[u]);
+  }
+}
+
 // The light regions (Sec. 5.1: light units to wavefronts): words of at most
 // kLightTokens tokens, the suffix [p.light_begin, n_regions) of the region
 // table.  A wave takes batches of consecutive light words (d.light_batch: at
@@ -1814,10 +1840,12 @@ __global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, u
   for (int q = nb + 1 + lane; q < nbp; q += kWave) qb[q] = __builtin_inf();
   if (lane == 0) qb[0] = 0.0;
   for (int k = K + lane; k < wh_entries(K); k += kWave) wh[k] = 0.0;
-  // the sparse word whose row wh holds (nnz 0 and K1 = K after the first
-  // fill; held < 0: a dense row or none, so that all of wh is rewritten)
+  // the sparse word whose row wh holds: its entries (held < 0: a dense row or
+  // none, so that all of wh is rewritten), lane q the topic of entry q and its
+  // beta/den, and K1 with what wh had there
   int held = -1;
-  uint32_t held_k = 0, held_k1 = 0;  // lane q: topic of the held row's entry q
+  uint32_t held_k = 0, held_k1 = 0;
+  double held_b = 0.0, held_w1 = 0.0;
   uint32_t n_sampled = 0, n_after_s = 0, n_reg = 0, n_dreg = 0;
   unsigned long long nnz_sum = 0, row_bytes = 0;
   // a wave's LDS accesses run in order; the fence keeps the compiler's order
@@ -1846,6 +1874,7 @@ __global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, u
     const uint32_t nnz_l = dense_l ? 0u : d.ws_nnz[s_l];
     const uint32_t cap_l = dense_l ? 0u : d.ws_cap[s_l];
     const uint32_t k1_l = d.wrec[v_l].k1;
+    const double a1_l = d.wrec[v_l].a1, qp_l = d.wrec[v_l].qp;
     uint32_t nnz = 0;
     if (und) {
       nnz = d.d_ent[off] & 0xFFFFu;
@@ -1862,12 +1891,19 @@ __global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, u
       const uint32_t n = __builtin_amdgcn_readlane(nnz_l, i), c = __builtin_amdgcn_readlane(cap_l, i);
       return uint32_t(lane) < n ? d.ws_ent[c + uint32_t(lane)] : 0u;
     };
-    uint32_t ent_next = entry_of(0);
+    // loaded ahead of their use, so that no word waits for them: the entries
+    // two words ahead, den and beta/den of their topics one word ahead
+    uint32_t ent_1 = entry_of(0), ent_2 = entry_of(min(1, nw - 1));
+    double den_1 = d.den[ent_1 >> 16], bden_1 = d.bden[ent_1 >> 16];
     uint32_t topic = 0;
     for (int i = 0; i < nw; ++i) {
       const uint32_t v = __builtin_amdgcn_readlane(v_l, i);
-      const uint32_t ent = ent_next;
-      if (i + 1 < nw) ent_next = entry_of(i + 1);
+      const uint32_t ent = ent_1;
+      const double den_e = den_1, bden_e = bden_1;
+      ent_1 = ent_2;
+      den_1 = d.den[ent_1 >> 16];
+      bden_1 = d.bden[ent_1 >> 16];
+      ent_2 = entry_of(min(i + 2, nw - 1));
       const int f = int(__builtin_amdgcn_readlane(b_l, i) - b0), l = int(__builtin_amdgcn_readlane(e_l, i) - b0);
       const uint32_t K1 = __builtin_amdgcn_readlane(k1_l, i);
       const bool mine = ln >= f && ln < l;
@@ -1875,18 +1911,19 @@ __global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, u
         if (mine) topic = K1;
         continue;
       }
-      const double a1 = d.wrec[v].a1, qp = d.wrec[v].qp;
+      const double a1 = readlane_f64(a1_l, i), qp = readlane_f64(qp_l, i);
       if (int32_t(v) < p.n_dense) {
         const int32_t *wrow = d.w_dense + size_t(v) * size_t(K);
-        for (int k = lane; k < K; k += kWave) wh[k] = what(uint32_t(wrow[k]), p.beta, d.den[k]);
+        fill_dense_wave(wrow, d.den, p.beta, K, lane, wh);
         held = -1;
       } else {
         const uint32_t n = __builtin_amdgcn_readlane(nnz_l, i);
         const uint32_t ek = ent >> 16;
-        const double we = uint32_t(lane) < n ? what(ent & 0xFFFFu, p.beta, d.den[ek]) : 0.0;
+        const double we = uint32_t(lane) < n ? what(ent & 0xFFFFu, p.beta, den_e) : 0.0;
         if (held >= 0) {
-          if (lane < held) wh[held_k] = d.bden[held_k];
-          if (lane == 0 && held_k1 < uint32_t(K)) wh[held_k1] = d.bden[held_k1];  // K1 = K in two-branch mode
+          if (lane == 0) wh[held_k1] = held_w1;  // before the row: K1 may be in it
+          order();
+          if (lane < held) wh[held_k] = held_b;
         } else {
           for (int k = lane; k < K; k += kWave) wh[k] = d.bden[k];
         }
@@ -1894,10 +1931,12 @@ __global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, u
         if (uint32_t(lane) < n) wh[ek] = we;
         held = int(n);
         held_k = ek;
+        held_b = bden_e;
         held_k1 = K1;
       }
       order();
       if (lane == 0) {
+        held_w1 = wh[K1];
         wh[K1] = 0.0;  // the max topic is its own branch (Eq. 5)
         wh[K] = 0.0;   // topic of the padding entries of D rows
       }
@@ -3473,8 +3512,9 @@ __global__ __launch_bounds__(64, 4) void k_loglik_light(DevState d, Params p) {
   const int lane = threadIdx.x;
   const double Kalpha = double(K) * p.alpha;
   for (int k = K + lane; k < wh_entries(K); k += kWave) wh[k] = 0.0;
-  int held = -1;
+  int held = -1;  // as in k_sampler_light
   uint32_t held_k = 0;
+  double held_b = 0.0;
   auto order = [&]() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
   for (uint32_t bi = blockIdx.x; bi < uint32_t(p.n_light_batches); bi += gridDim.x) {
     const uint32_t r0 = __builtin_amdgcn_readfirstlane(d.light_batch[bi]);
@@ -3500,25 +3540,31 @@ __global__ __launch_bounds__(64, 4) void k_loglik_light(DevState d, Params p) {
       const uint32_t n = __builtin_amdgcn_readlane(nnz_l, i), c = __builtin_amdgcn_readlane(cap_l, i);
       return uint32_t(lane) < n ? d.ws_ent[c + uint32_t(lane)] : 0u;
     };
-    uint32_t ent_next = entry_of(0);
+    const double sumw_l = d.wrec[v_l].sumw;
+    uint32_t ent_1 = entry_of(0), ent_2 = entry_of(min(1, nw - 1));
+    double den_1 = d.den[ent_1 >> 16], bden_1 = d.bden[ent_1 >> 16];
     double part = 0.0;
     for (int i = 0; i < nw; ++i) {
       const uint32_t v = __builtin_amdgcn_readlane(v_l, i);
-      const uint32_t ent = ent_next;
-      if (i + 1 < nw) ent_next = entry_of(i + 1);
+      const uint32_t ent = ent_1;
+      const double den_e = den_1, bden_e = bden_1;
+      ent_1 = ent_2;
+      den_1 = d.den[ent_1 >> 16];
+      bden_1 = d.bden[ent_1 >> 16];
+      ent_2 = entry_of(min(i + 2, nw - 1));
       const int f = int(__builtin_amdgcn_readlane(b_l, i) - b0), l = int(__builtin_amdgcn_readlane(e_l, i) - b0);
       const bool mine = ln >= f && ln < l;
-      const double asw = p.alpha * d.wrec[v].sumw;
+      const double asw = p.alpha * readlane_f64(sumw_l, i);
       if (int32_t(v) < p.n_dense) {
         const int32_t *wrow = d.w_dense + size_t(v) * size_t(K);
-        for (int k = lane; k < K; k += kWave) wh[k] = what(uint32_t(wrow[k]), p.beta, d.den[k]);
+        fill_dense_wave(wrow, d.den, p.beta, K, lane, wh);
         held = -1;
       } else {
         const uint32_t n = __builtin_amdgcn_readlane(nnz_l, i);
         const uint32_t ek = ent >> 16;
-        const double we = uint32_t(lane) < n ? what(ent & 0xFFFFu, p.beta, d.den[ek]) : 0.0;
+        const double we = uint32_t(lane) < n ? what(ent & 0xFFFFu, p.beta, den_e) : 0.0;
         if (held >= 0) {
-          if (lane < held) wh[held_k] = d.bden[held_k];
+          if (lane < held) wh[held_k] = held_b;
         } else {
           for (int k = lane; k < K; k += kWave) wh[k] = d.bden[k];
         }
@@ -3526,6 +3572,7 @@ __global__ __launch_bounds__(64, 4) void k_loglik_light(DevState d, Params p) {
         if (uint32_t(lane) < n) wh[ek] = we;
         held = int(n);
         held_k = ek;
+        held_b = bden_e;
       }
       order();
       const WordState w{wh, nullptr, 0, K, 0, 0u, 0.0, 0.0, p.alpha, nullptr, nullptr};
@@ -3540,7 +3587,7 @@ __global__ __launch_bounds__(64, 4) void k_loglik_light(DevState d, Params p) {
   }
 }
 
-// Large K: the row in two tiles, as in k_sampler_tiled.  Pass 0 keeps each
+// Large K: the row in two tiles.  Pass 0 keeps each
 // token's sum over the topics below KT and the chunk where its row reaches KT
 // (the per-workgroup scratch of the sampler), pass 1 adds the topics from KT
 // on, reading the row from that chunk.
