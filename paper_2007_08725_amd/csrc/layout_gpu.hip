@@ -59,6 +59,13 @@ __global__ void k_word_order(const uint32_t *__restrict__ wkey, const uint32_t *
   }
 }
 
+__global__ void k_check_z(const int32_t *__restrict__ z, int64_t n, int32_t K, unsigned long long *__restrict__ bad) {
+  unsigned long long nbad = 0;
+  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
+    nbad += z[i] < 0 || z[i] >= K ? 1ull : 0ull;
+  if (nbad) atomicAdd(bad, nbad);
+}
+
 __global__ void k_gather_z(const int32_t *__restrict__ z_in, const uint2 *__restrict__ wt_kr, int64_t n,
                            int32_t K, uint16_t *__restrict__ z_w, unsigned long long *__restrict__ bad) {
   unsigned long long nbad = 0;
@@ -334,6 +341,11 @@ hipError_t launch_word_order(const uint32_t *wkey, const uint32_t *wpos, int64_t
                              const uint32_t *d_cap, uint2 *wt_kr, hipStream_t s) {
   hipLaunchKernelGGL(k_word_order, dim3(grid_for(n)), dim3(kThreads), 0, s, wkey, wpos, n, relabel, woff_orig,
                      woff_new, doc_sorted, doc_in, dt_key, dt_word, dt_wpos, d_cap, wt_kr);
+  return hipGetLastError();
+}
+
+hipError_t launch_check_z(const int32_t *z_in, int64_t n, int32_t K, unsigned long long *bad, hipStream_t s) {
+  hipLaunchKernelGGL(k_check_z, dim3(std::min(grid_for(n), 4096u)), dim3(kThreads), 0, s, z_in, n, K, bad);
   return hipGetLastError();
 }
 

@@ -553,11 +553,21 @@ lda_status lda_set_assignments(lda_handle *h, const int32_t *z, int64_t iteratio
   if (h->chunks) return chunked_set_assignments(h, z, iteration);
   const Layout &L = h->L;
   const size_t n = size_t(L.n);
-  for (size_t i = 0; i < n; ++i)
-    if (z[i] < 0 || z[i] >= L.K) return fail(h, LDA_E_ARG, "topic out of range at token " + std::to_string(i));
   int32_t *zin = nullptr;
   LDA_TRY(dalloc(h, &zin, n));
   HIP_TRY(h, hipMemcpyAsync(zin, z, n * 4, hipMemcpyHostToDevice, h->stream));
+  // the topics are checked on the device before anything of the state changes
+  unsigned long long bad = 0;
+  HIP_TRY(h, hipMemsetAsync(h->nnz, 0, sizeof(bad), h->stream));
+  HIP_TRY(h, launch_check_z(zin, L.n, L.K, h->nnz, h->stream));
+  HIP_TRY(h, hipMemcpyAsync(&bad, h->nnz, sizeof(bad), hipMemcpyDeviceToHost, h->stream));
+  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  if (bad) {
+    dfree(h, zin);
+    for (size_t i = 0; i < n; ++i)
+      if (z[i] < 0 || z[i] >= L.K) return fail(h, LDA_E_ARG, "topic out of range at token " + std::to_string(i));
+    return fail(h, LDA_E_ARG, "topic out of range");
+  }
   HIP_TRY(h, hipMemsetAsync(h->stats_base, 0, sizeof(unsigned long long) * kStatsPerIter, h->stream));
   HIP_TRY(h, launch_gather_z(zin, h->d.wt_kr, L.n, L.K, h->d.z_w, h->stats_base + ST_ERRORS, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));

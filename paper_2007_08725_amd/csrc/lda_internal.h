@@ -99,6 +99,8 @@ hipError_t launch_word_order(const uint32_t *wkey, const uint32_t *wpos, int64_t
                              const uint32_t *woff_orig, const uint32_t *woff_new, const uint32_t *doc_sorted,
                              const int32_t *doc_in, const uint32_t *dt_key, uint32_t *dt_word, uint32_t *dt_wpos,
                              const uint32_t *d_cap, uint2 *wt_kr, hipStream_t s);
+// bad += topics outside [0, K).
+hipError_t launch_check_z(const int32_t *z_in, int64_t n, int32_t K, unsigned long long *bad, hipStream_t s);
 hipError_t launch_gather_z(const int32_t *z_in, const uint2 *wt_kr, int64_t n, int32_t K, uint16_t *z_w,
                            unsigned long long *bad, hipStream_t s);
 // Out-of-core chunks: the word-order slot of each doc-order position from the
