@@ -2,13 +2,14 @@
 //
 // One synchronous iteration (Sec. 2.2, 3.2, 4.3):
 //   k_begin      den[k] = T[k] + V*beta; scheduler counters reset
-//   k_word_pre_wave
+//   k_topic_list, k_word_pre_small, k_word_pre_wave
 //                per word: top-3 of W^[v] (K1, K2, a1..a3), Q' and sum W^   (step 1, Sec. 3.2)
 //   k_clear_skips
 //                the skip bitmap (one bit per word-ordered token) cleared
 //   k_doc_pass   per document: C1, C2 by lookup in the D row, u, M, S_est
 //                and the skip test; sets the bit of every skipped token    (steps 2-3, Sec. 3.3)
-//   k_sampler    per region of a word: W^ row and Q' block prefix in LDS,
+//   k_sampler (from K = 2,300 on k_sampler_f...), k_sampler_light
+//                per unit of a word: W^ row and Q' block prefix in LDS,
 //                then for every token whose bit is clear C1 and S' over
 //                nz(D[d]) and the final draw over [K1 | S' | Q']; every
 //                topic slot of the region written (K1 for the skipped)     (steps 4-6, Sec. 4.3)
@@ -17,8 +18,9 @@
 //                histogram (integer atomics for split words), sparse rows of
 //                W and rows of D as packed (topic << 16 | count) entries, T
 //                                                                          (Sec. 4.2-4.3)
-// All floating point is fp64 (IEEE divide for W^), built without
-// contraction so that the values match a plain sequential evaluation.
+// The draws are those of fp64 arithmetic (IEEE divide for W^, built without
+// contraction); k_sampler_f... and the skip test use single precision where a
+// bound proves the fp64 decision.
 #include "lda_internal.h"
 
 #include <mutex>
