@@ -52,7 +52,8 @@ typedef enum {
  * (topic << 16 | count) entries of D and of the sparse rows of W (Sec. 4.2)
  * keep 16 bits per field, and one topic code marks an undrawn token.  Above
  * about 17,000 topics the fp64 word-topic row no longer fits one
- * workgroup's LDS, and the sampler walks it in two tiles. */
+ * workgroup's LDS: the LLPT kernel walks it in two tiles, the sampler keeps
+ * it in single precision and redoes undecided draws in fp64. */
 #define LDA_MAX_TOPICS 32768
 /* Longest document: its per-topic counts must fit 16 bits (Sec. 4.2). */
 #define LDA_MAX_DOC_LEN 65535

@@ -25,12 +25,12 @@ lda_status export_d(lda_handle *h, Crew &crew, const DevState &d, int32_t M, int
     off[0] = at;
     return LDA_OK;
   }
-  uint32_t *num = nullptr, *ent = nullptr;
-  LDA_TRY(dalloc(h, &num, rows));
+  Scratch<uint32_t> num(h), ent(h);
+  LDA_TRY(num.get(rows));
   std::vector<uint32_t> n(docs);
   for (size_t a = 0; a < docs; a += rows) {
     const size_t m = std::min(rows, docs - a);
-    HIP_TRY(h, launch_doc_nnz(d, int64_t(a), int64_t(m), num, h->stream));
+    HIP_TRY(h, launch_doc_nnz(d, int64_t(a), int64_t(m), num.ptr, h->stream));
     LDA_TRY(read_back(h, crew, num, m, [&](const uint32_t *src, size_t first, size_t k) {
       std::memcpy(n.data() + a + first, src, k * sizeof(uint32_t));
     }));
@@ -43,7 +43,7 @@ lda_status export_d(lda_handle *h, Crew &crew, const DevState &d, int32_t M, int
   off[docs] = o;
   *entries = o - at;
   // a row has fewer than 2^16 entries, far below a slab
-  LDA_TRY(dalloc(h, &ent, std::min<size_t>(size_t(o - at), kSlabEntries)));
+  LDA_TRY(ent.get(std::min<size_t>(size_t(o - at), kSlabEntries)));
   std::vector<uint32_t> rel(rows);
   for (size_t a = 0; a < docs;) {
     size_t b = a, total = 0;
@@ -51,8 +51,8 @@ lda_status export_d(lda_handle *h, Crew &crew, const DevState &d, int32_t M, int
       rel[b - a] = uint32_t(total);
       total += n[b];
     }
-    HIP_TRY(h, hipMemcpyAsync(num, rel.data(), (b - a) * sizeof(uint32_t), hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(h, launch_export_d(d, int64_t(a), int64_t(b - a), num, ent, h->stream));
+    LDA_TRY(num.put(rel.data(), b - a));
+    HIP_TRY(h, launch_export_d(d, int64_t(a), int64_t(b - a), num.ptr, ent.ptr, h->stream));
     int32_t *tp = topic + off[a], *ct = count + off[a];
     LDA_TRY(read_back(h, crew, ent, total, [tp, ct](const uint32_t *src, size_t first, size_t m) {
       for (size_t i = 0; i < m; ++i) {
@@ -63,8 +63,6 @@ lda_status export_d(lda_handle *h, Crew &crew, const DevState &d, int32_t M, int
     HIP_TRY(h, hipStreamSynchronize(h->stream));  // rel is rewritten
     a = b;
   }
-  dfree(h, ent);
-  dfree(h, num);
   return LDA_OK;
 }
 
@@ -72,10 +70,10 @@ lda_status export_w(lda_handle *h, Crew &crew, const DevState &d, const Params &
                     int32_t *count) {
   const Layout &L = h->L;
   const size_t np = size_t(p.n_present), V = size_t(L.V), rows = std::min(V, kSlabRows);
-  uint32_t *num = nullptr, *row = nullptr;
-  uint2 *ent = nullptr;
-  LDA_TRY(dalloc(h, &num, std::max(np, rows)));
-  HIP_TRY(h, launch_word_nnz(d, p, num, h->stream));
+  Scratch<uint32_t> num(h), row(h);
+  Scratch<uint2> ent(h);
+  LDA_TRY(num.get(std::max(np, rows)));
+  HIP_TRY(h, launch_word_nnz(d, p, num.ptr, h->stream));
   std::vector<uint32_t> n(np);
   LDA_TRY(read_back(h, crew, num, np, [&](const uint32_t *src, size_t first, size_t k) {
     std::memcpy(n.data() + first, src, k * sizeof(uint32_t));
@@ -88,8 +86,8 @@ lda_status export_w(lda_handle *h, Crew &crew, const DevState &d, const Params &
   }
   off[V] = o;
   // a row has at most K <= 32,768 entries, far below a slab
-  LDA_TRY(dalloc(h, &ent, std::min<size_t>(size_t(o), kSlabEntries)));
-  LDA_TRY(dalloc(h, &row, rows));
+  LDA_TRY(ent.get(std::min<size_t>(size_t(o), kSlabEntries)));
+  LDA_TRY(row.get(rows));
   std::vector<uint32_t> rel(rows), ids(rows);
   for (size_t a = 0; a < V;) {
     size_t b = a, total = 0, m = 0;
@@ -100,9 +98,9 @@ lda_status export_w(lda_handle *h, Crew &crew, const DevState &d, const Params &
       total += words(b);
     }
     if (m) {
-      HIP_TRY(h, hipMemcpyAsync(num, rel.data(), m * sizeof(uint32_t), hipMemcpyHostToDevice, h->stream));
-      HIP_TRY(h, hipMemcpyAsync(row, ids.data(), m * sizeof(uint32_t), hipMemcpyHostToDevice, h->stream));
-      HIP_TRY(h, launch_export_w(d, p, row, num, int64_t(m), ent, h->stream));
+      LDA_TRY(num.put(rel.data(), m));
+      LDA_TRY(row.put(ids.data(), m));
+      HIP_TRY(h, launch_export_w(d, p, row.ptr, num.ptr, int64_t(m), ent.ptr, h->stream));
       int32_t *tp = topic + off[a], *ct = count + off[a];
       LDA_TRY(read_back(h, crew, ent, total, [tp, ct](const uint2 *src, size_t first, size_t k) {
         for (size_t i = 0; i < k; ++i) {
@@ -114,9 +112,6 @@ lda_status export_w(lda_handle *h, Crew &crew, const DevState &d, const Params &
     }
     a = b;
   }
-  dfree(h, row);
-  dfree(h, ent);
-  dfree(h, num);
   return LDA_OK;
 }
 

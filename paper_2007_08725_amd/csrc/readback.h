@@ -8,6 +8,7 @@
 #include <cstring>
 #include <functional>
 #include <mutex>
+#include <string>
 #include <system_error>
 #include <thread>
 #include <vector>
@@ -86,6 +87,50 @@ class Crew {
   bool stop_ = false;
 };
 
+// A device array of one call, given back when the call leaves by any path.
+// Where the device or the caller's allocator has no room it is pinned host
+// memory, which kernels reach over PCIe: an export needs no device memory to
+// succeed, only to be fast.
+template <typename T>
+struct Scratch {
+  lda_handle *h;
+  T *ptr = nullptr;
+  bool on_host = false;
+  explicit Scratch(lda_handle *handle) : h(handle) {}
+  ~Scratch() {
+    if (on_host) (void)hipHostFree(ptr);
+    else dfree(h, ptr);
+  }
+  Scratch(const Scratch &) = delete;
+  Scratch &operator=(const Scratch &) = delete;
+
+  lda_status get(size_t count) {
+    const std::string err = h->err;
+    const lda_status st = dalloc(h, &ptr, count);
+    if (st != LDA_E_NOMEM) return st;
+    (void)hipGetLastError();
+    void *p = nullptr;
+    if (hipHostMalloc(&p, std::max<size_t>(count, 1) * sizeof(T), hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      return st;
+    }
+    h->err = err;
+    ptr = static_cast<T *>(p);
+    on_host = true;
+    return LDA_OK;
+  }
+  // The first n values from src, which the caller keeps until the stream is waited for.
+  lda_status put(const T *src, size_t n) {
+    if (on_host) {
+      HIP_TRY(h, hipStreamSynchronize(h->stream));  // kernels before read what is overwritten
+      std::memcpy(ptr, src, n * sizeof(T));
+    } else {
+      HIP_TRY(h, hipMemcpyAsync(ptr, src, n * sizeof(T), hipMemcpyHostToDevice, h->stream));
+    }
+    return LDA_OK;
+  }
+};
+
 // Below this many bytes a result is copied at once and used by the calling
 // thread (the threads' start costs more than they save).
 constexpr size_t kReadSmall = size_t(1) << 20;
@@ -147,6 +192,19 @@ lda_status read_back(lda_handle *h, Crew &crew, const T *dev, size_t n, const F 
       use(src + f, b + f, std::min(piece, m - f));
     });
   }
+  return LDA_OK;
+}
+
+template <typename T, typename F>
+lda_status read_back(lda_handle *h, Crew &crew, const Scratch<T> &from, size_t n, const F &use) {
+  if (!from.on_host) return read_back(h, crew, static_cast<const T *>(from.ptr), n, use);
+  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  const T *src = from.ptr;
+  const size_t piece = (size_t(64) << 10) / sizeof(T);
+  crew.run((n + piece - 1) / piece, [&](size_t q) {
+    const size_t f = q * piece;
+    use(src + f, f, std::min(piece, n - f));
+  });
   return LDA_OK;
 }
 

@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import lda_synth
-from gpu_common import check_counts_are_histograms, make_lda, say
+from gpu_common import SEED, check_counts_are_histograms, make_lda, say
 
 pytestmark = pytest.mark.gpu
 
@@ -42,3 +42,72 @@ def test_large_exports_are_the_histograms_of_z(n_docs, mean, V, K, opts):
             check_counts_are_histograms(c, cnt, K)
         only = m.counts(D=False, W=False)
         assert np.array_equal(only["z"], cnt["z"]) and only["iteration"] == cnt["iteration"] and only["M"] == n_docs
+
+
+# the tables of a handle whose allocator has nothing left after construction, resident and out of core, over several
+# slabs of rows and with results on either side of the threads' threshold
+@pytest.mark.parametrize("n_docs,mean,V,K,chunks", [
+    (330_000, 30, 60_000, 1000, 0),
+    (40_000, 30, 5_000, 200, 3),
+    (300, 20, 500, 30, 0),
+])
+def test_tables_are_exported_without_device_memory_to_spare(n_docs, mean, V, K, chunks):
+    import ctypes
+
+    import torch
+
+    import paper_2007_08725_amd as lda
+    rng = np.random.default_rng(K)
+    doc = np.repeat(np.arange(n_docs, dtype=np.int32), rng.integers(1, 2 * mean, n_docs))
+    word = rng.integers(0, V, doc.shape[0]).astype(np.int32)
+    n, live, refused = doc.shape[0], {}, []
+
+    def alloc(nbytes, ctx):
+        if alloc.closed:
+            refused.append(int(nbytes))
+            return None
+        t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
+        live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    alloc.closed = False
+
+    def free(ptr, ctx):
+        live.pop(ptr, None)
+
+    fa, ff = lda.ALLOC_FN(alloc), lda.FREE_FN(free)
+    o = lda.Options()
+    o.dev_alloc, o.dev_free = fa, ff
+    if chunks:
+        o.chunks = chunks
+    lib, h = lda.load_library(), ctypes.c_void_p()
+    say("export without device memory N=%d K=%d chunks=%d" % (n, K, chunks))
+
+    def ptr(a):
+        return ctypes.c_void_p(a.ctypes.data)
+
+    assert lib.lda_create(ptr(word), ptr(doc), n, V, K, 50.0 / K, 0.01, SEED, ctypes.byref(o), ctypes.byref(h)) == 0
+    try:
+        assert lib.lda_iterate(h, 1, None) == 0
+
+        def tables():
+            c = lda.Counts()
+            assert lib.lda_get_counts(h, ctypes.byref(c)) == 0
+            a = dict(T=np.empty(K, np.int64), D_off=np.empty(c.M + 1, np.int64), D_topic=np.empty(c.nnz_D, np.int32),
+                     D_count=np.empty(c.nnz_D, np.int32), W_off=np.empty(c.V + 1, np.int64),
+                     W_topic=np.empty(c.nnz_W, np.int32), W_count=np.empty(c.nnz_W, np.int32))
+            for name, arr in a.items():
+                setattr(c, name, arr.ctypes.data)
+            assert lib.lda_get_counts(h, ctypes.byref(c)) == 0, lib.lda_last_error(h)
+            return a
+
+        ref, kept = tables(), len(live)
+        alloc.closed = True
+        got = tables()
+        assert len(refused) == 5 if not chunks else len(refused) >= 5  # every array of the export was refused
+        assert len(live) == kept
+        for name in ref:
+            assert np.array_equal(ref[name], got[name]), name
+    finally:
+        lib.lda_destroy(h)
+    assert not live
