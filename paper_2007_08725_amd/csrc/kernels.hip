@@ -181,6 +181,41 @@ __device__ double block_sum(double v, double *red) {
   return s;
 }
 
+// A sum with the rounding errors of its additions beside it (Knuth's two-sum):
+// h + l is off by about 2^-104 of the largest partial sum.
+struct Sum2 {
+  double h, l;
+};
+__device__ __forceinline__ Sum2 sum2_add(Sum2 a, Sum2 b) {
+  const double s = a.h + b.h, bb = s - a.h;
+  const double e = ((a.h - (s - bb)) + (b.h - bb)) + (a.l + b.l);
+  const double h = s + e;
+  return Sum2{h, e - (h - s)};
+}
+// One more value; h alone is the chain from value to value.
+__device__ __forceinline__ void sum2_push(Sum2 &a, double b) {
+  const double s = a.h + b, bb = s - a.h;
+  a.l += (a.h - (s - bb)) + (b - bb);
+  a.h = s;
+}
+// Over each group of G lanes, in every lane.
+template <int G>
+__device__ __forceinline__ Sum2 group_sum2(Sum2 a) {
+#pragma unroll
+  for (int o = G / 2; o > 0; o >>= 1) a = sum2_add(a, Sum2{__shfl_xor(a.h, o, kWave), __shfl_xor(a.l, o, kWave)});
+  return a;
+}
+// Over the kBlock threads of a workgroup (fixed order), in every thread.
+__device__ Sum2 block_sum2(Sum2 v, Sum2 *red) {
+  v = group_sum2<kWave>(v);
+  __syncthreads();
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
+  __syncthreads();
+  Sum2 s = red[0];
+  for (int q = 1; q < kBlock / kWave; ++q) s = sum2_add(s, red[q]);
+  return s;
+}
+
 // Block-wide exclusive prefix of a uint32 over 256 threads; *total gets the sum.
 __device__ uint32_t block_exclusive_u32(uint32_t v, uint32_t *red, uint32_t *total) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -289,6 +324,18 @@ struct WordTop {
   double a1, a2, a3, a4;
 };
 
+__device__ __forceinline__ WordTop word_top_of(const TopN &t) {
+  WordTop top;
+  top.k1 = t.k[0];
+  top.k2 = t.k[1];
+  top.k3 = t.k[2];
+  top.a1 = t.v[0];
+  top.a2 = t.v[1];
+  top.a3 = t.v[2] > 0.0 ? t.v[2] : 0.0;
+  top.a4 = t.v[3] > 0.0 ? t.v[3] : 0.0;
+  return top;
+}
+
 // The sampler's and the skip test's per-word records.  In two-branch mode
 // (Sec. 2.2) the max-topic branch is empty (a1 = 0, K1 = K, a topic no row
 // holds with a count) and Q' is the full Q.
@@ -316,17 +363,57 @@ __device__ void write_word_records(const DevState &d, const Params &p, int r, co
   d.wskip[r] = sr;
 }
 
-// K from 4,096 on: the sum over all topics of beta/den[k] (one workgroup, a fixed
-// order), for the sparse words' sums in k_word_pre_wave.
-__global__ __launch_bounds__(kBlock) void k_beta_sum(DevState d, Params p) {
-  __shared__ double red[kBlock / kWave];
-  const int K = p.K;
-  const int cs = (K + kBlock - 1) / kBlock;
-  const int c0 = min(K, int(threadIdx.x) * cs), c1 = min(K, c0 + cs);
-  double s = 0.0;
-  for (int k = c0; k < c1; ++k) s += d.bden[k];
-  s = block_sum(s, red);
-  if (threadIdx.x == 0) d.beta_sum[0] = s;
+// The sum over all topics of beta/den[k] (one workgroup, a fixed order) with
+// its rounding error, for the sparse words' sums (RowSums).
+__device__ __forceinline__ void beta_sum_all(const DevState &d, int K) {
+  __shared__ Sum2 red[kBlock / kWave];
+  Sum2 s{0.0, 0.0};
+#pragma unroll 4
+  for (int k = int(threadIdx.x); k < K; k += kBlock) sum2_push(s, d.bden[k]);
+  s = block_sum2(s, red);
+  if (threadIdx.x == 0) {
+    d.beta_sum[0] = s.h;
+    d.beta_sum[1] = s.l;
+  }
+}
+// K from 4,096 on (below, k_topic_list's last workgroup).
+__global__ __launch_bounds__(kBlock) void k_beta_sum(DevState d, Params p) { beta_sum_all(d, p.K); }
+
+// A sparse word's sums from its row, one lane's entries: Q' / alpha is the sum
+// of W^ over every topic but K1, that is beta/den[k] over the topics outside
+// the row and W^ over its other entries.  Both are formed without W^[v][K1]
+// ever being in them: taken off the whole sum, a K1 that holds nearly all of
+// it would leave Q' with the rounding errors of the whole (up to 7e-9 of Q' for
+// words of one topic at beta = 1e-9, K = 1,000; now below 40 * 2^-53).  The topics outside are the
+// sum over all of them less the row's, with the errors of both kept (Sum2),
+// since the row may hold most of it.
+struct RowSums {
+  Sum2 beta{0.0, 0.0};    // beta/den[k] of the entries
+  double rest = 0.0;      // W^ of the entries, but the largest (lowest topic on ties)
+  double best = 0.0;      // W^ of that one
+  uint32_t best_k = 0xFFFFFFFFu;
+  __device__ __forceinline__ void entry(double w, double bden, uint32_t k) {
+    sum2_push(beta, bden);
+    const bool b = better(w, k, best, best_k);
+    rest += b ? best : w;
+    best = b ? w : best;
+    best_k = b ? k : best_k;
+  }
+};
+// The word's records, from the RowSums of its group of G lanes, K1 among them
+// or outside the row; lane `leader` writes.  gmask: the group's lanes.
+template <int G>
+__device__ __forceinline__ void write_sparse_records(const DevState &d, const Params &p, int r, const TopN &t,
+                                                     const RowSums &rs, unsigned long long gmask, bool leader) {
+  const WordTop top = word_top_of(t);
+  const bool mine = rs.best_k == top.k1;
+  const bool in_row = (__ballot(mine) & gmask) != 0ull;
+  const double held = group_sum<G>(rs.rest + (mine ? 0.0 : rs.best));
+  const Sum2 b = group_sum2<G>(rs.beta);
+  Sum2 out = sum2_add(Sum2{d.beta_sum[0], d.beta_sum[1]}, Sum2{-b.h, -b.l});
+  if (!in_row) out = sum2_add(out, Sum2{-top.a1, 0.0});
+  const double q = out.h + held, sw = q + top.a1;
+  if (leader) write_word_records(d, p, r, top, p.alpha * (p.two_branch ? sw : q), sw);
 }
 
 // Step 1 (Sec. 3.2) and Q' (Sec. 2.2), one wave per word, four words per
@@ -339,8 +426,8 @@ __global__ __launch_bounds__(kBlock) void k_beta_sum(DevState d, Params p) {
 // its row: its top values come from the row and from the first topics
 // outside the row in the list of all topics by ascending T (descending
 // beta/den[k], lowest id first on ties), 64 candidates of the list at a time;
-// its sums from the sum of beta/den[k] over all topics, corrected on the
-// row.  Should the list run out, every topic is scanned.  The words from
+// its sums from the sum of beta/den[k] over all topics and the row (RowSums).
+// Should the list run out, every topic is scanned.  The words from
 // p.small_begin on are then k_word_pre_small's.
 __device__ __forceinline__ void wave_top_merge(TopN &t) {
 #pragma unroll
@@ -355,17 +442,6 @@ __device__ __forceinline__ void wave_top_merge(TopN &t) {
 #pragma unroll
     for (int q = 0; q < kTop; ++q) top_insert(t, pv[q], pk[q]);
   }
-}
-__device__ __forceinline__ WordTop word_top_of(const TopN &t) {
-  WordTop top;
-  top.k1 = t.k[0];
-  top.k2 = t.k[1];
-  top.k3 = t.k[2];
-  top.a1 = t.v[0];
-  top.a2 = t.v[1];
-  top.a3 = t.v[2] > 0.0 ? t.v[2] : 0.0;
-  top.a4 = t.v[3] > 0.0 ? t.v[3] : 0.0;
-  return top;
 }
 __global__ __launch_bounds__(kBlock) void k_word_pre_wave(DevState d, Params p) {
   extern __shared__ uint16_t wtab[];  // without p.sparse_pre: [kBlock / kWave][(K + 1) & ~1]
@@ -390,13 +466,12 @@ __global__ __launch_bounds__(kBlock) void k_word_pre_wave(DevState d, Params p) 
   };
   reset();
   if (!dense && p.sparse_pre) {
-    double snz = 0.0, sb = 0.0;
+    RowSums rs;
     for (uint32_t q = uint32_t(lane); q < nnz; q += kWave) {
       const uint32_t ent = ents[q], k = ent >> 16;
       const double w = what(ent & 0xFFFFu, p.beta, d.den[k]);
       top_insert(t, w, k);
-      snz += w;
-      sb += d.bden[k];
+      rs.entry(w, d.bden[k], k);
     }
     const uint32_t want = uint32_t(min(kTop, K - int(nnz)));
     uint32_t found = 0;
@@ -415,14 +490,8 @@ __global__ __launch_bounds__(kBlock) void k_word_pre_wave(DevState d, Params p) 
       found += min(uint32_t(__popcll(m)), want - found);
     }
     wave_top_merge(t);
-    snz = group_sum<kWave>(snz);
-    sb = group_sum<kWave>(sb);
     if (found >= want) {
-      const WordTop top = word_top_of(t);
-      if (lane == 0) {
-        const double sw = (d.beta_sum[0] - sb) + snz;
-        write_word_records(d, p, r, top, p.two_branch ? p.alpha * sw : p.alpha * (sw - top.a1), sw);
-      }
+      write_sparse_records<kWave>(d, p, r, t, rs, ~0ull, lane == 0);
       return;
     }
     reset();  // the list ran out: every topic below
@@ -496,13 +565,9 @@ __global__ __launch_bounds__(kBlock) void k_word_pre_wave(DevState d, Params p) 
 constexpr int kListTopics = kBlock / 4;  // topics per workgroup
 __global__ __launch_bounds__(kBlock) void k_topic_list(DevState d, Params p) {
   extern __shared__ uint32_t ldsu[];  // [K rounded up to 4]
-  __shared__ double red[kBlock / kWave];
   const int K = p.K, tid = threadIdx.x;
   if (int(blockIdx.x) * kListTopics >= K) {
-    double s = 0.0;
-    for (int k = tid; k < K; k += kBlock) s += d.bden[k];
-    s = block_sum(s, red);
-    if (tid == 0) d.beta_sum[0] = s;
+    beta_sum_all(d, K);
     return;
   }
   const int K4 = (K + 3) & ~3;
@@ -545,7 +610,7 @@ __global__ __launch_bounds__(kBlock) void k_word_pre_small(DevState d, Params p)
     t.v[q] = -1.0;
     t.k[q] = 0xFFFFFFFFu;
   }
-  double snz = 0.0, sb = 0.0;
+  RowSums rs;
   uint32_t ent[kSmallWord / kGroup];
 #pragma unroll
   for (int u = 0; u < int(kSmallWord) / kGroup; ++u) {
@@ -559,8 +624,7 @@ __global__ __launch_bounds__(kBlock) void k_word_pre_small(DevState d, Params p)
       const uint32_t k = ent[u] >> 16;
       const double w = what(ent[u] & 0xFFFFu, p.beta, d.den[k]);
       top_insert(t, w, k);
-      snz += w;
-      sb += d.bden[k];
+      rs.entry(w, d.bden[k], k);
       s_topic[g][q] = uint16_t(k);
     }
   }
@@ -598,13 +662,8 @@ __global__ __launch_bounds__(kBlock) void k_word_pre_small(DevState d, Params p)
 #pragma unroll
     for (int q = 0; q < kTop; ++q) top_insert(t, pv[q], pk[q]);
   }
-  snz = group_sum<kGroup>(snz);
-  sb = group_sum<kGroup>(sb);
-  if (li == 0 && word < p.n_present) {
-    const WordTop top = word_top_of(t);
-    const double sw = (d.beta_sum[0] - sb) + snz;
-    write_word_records(d, p, r, top, p.two_branch ? p.alpha * sw : p.alpha * (sw - top.a1), sw);
-  }
+  write_sparse_records<kGroup>(d, p, r, t, rs, (unsigned long long)(kGroupMask) << (grp * kGroup),
+                               li == 0 && word < p.n_present);
 }
 
 // Steps 2 and 3: per document, C1 = D[d][K1], C2 = D[d][K2], u, M, S_est and

@@ -235,7 +235,7 @@ lda_status create_device(lda_handle *h, const lda_options *o, const int32_t *wor
     ++p.small_begin;
   if (p.sparse_pre) {
     LDA_TRY(dalloc(h, &d.topic_order, size_t(L.K)));
-    LDA_TRY(dalloc(h, &d.beta_sum, 1));
+    LDA_TRY(dalloc(h, &d.beta_sum, 2));
   }
   if (p.sparse_pre && L.K >= kWBitsK) {
     LDA_TRY(dalloc(h, &d.topic_keys, size_t(L.K)));

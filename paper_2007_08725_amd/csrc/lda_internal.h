@@ -167,7 +167,7 @@ struct DevState {
   uint32_t *ts_code;
   uint32_t *hist_rows;  // large K: the rows of k_topic_hist
   // p.sparse_pre: topics by ascending T (descending beta/den[k]),
-  // their sort buffers, and the sum of beta/den[k] over all topics
+  // their sort buffers, and [2] the sum of beta/den[k] over all topics with its rounding error
   uint32_t *topic_order, *topic_keys, *topic_iota;
   void *topic_tmp;
   size_t topic_tmp_bytes;
