@@ -228,9 +228,10 @@ lda_status create_device(lda_handle *h, const lda_options *o, const int32_t *wor
   LDA_TRY(dalloc(h, &d.ll_part, size_t(partials)));
   // sparse words' per-word records from their rows and a list of the topics
   // with the largest beta/den[k] (made each iteration)
-  p.sparse_pre = use_topic_list(L.K, L.n_present - L.n_dense) ? 1 : 0;
-  p.top_list = std::min(L.K, 512);
-  p.small_begin = L.n_dense;  // words are numbered by descending count
+  const bool ordered = topic_list_ordered(p.beta, p.vbeta, p.n_all);
+  p.sparse_pre = use_topic_list(L.K, L.n_present - L.n_dense, ordered) ? 1 : 0;
+  p.top_list = ordered ? std::min(L.K, 512) : 0;
+  p.small_begin = ordered ? L.n_dense : L.n_present;  // words are numbered by descending count
   while (p.small_begin < L.n_present && L.word_off[size_t(p.small_begin) + 1] - L.word_off[size_t(p.small_begin)] > kSmallWord)
     ++p.small_begin;
   if (p.sparse_pre) {

@@ -368,9 +368,18 @@ constexpr int kWBitsK = 4096;
 // K = 4,096 on, where a wave's table of K counts gets large, and below it when
 // the sparse words' tables would be at least 4M topics together (about 40 us;
 // the list is a launch of its own, 6 us at K = 1,000).
+// The list is in the order of T; the top topics are by beta/den[k], the lowest
+// id first among equals.  The two orders are the same while beta/den[k] differs
+// wherever T does: den = T + V*beta below 2^50 (neighbours then differ by three
+// units in the last place of the quotient) and no quotient near underflow.
+// With priors beyond, every topic is looked at: by tables of counts below
+// K = 4,096, from there on by searches of the row (a list of no topics).
 constexpr uint32_t kSmallWord = 64;
-inline bool use_topic_list(int32_t K, int64_t sparse_words) {
-  return K >= kWBitsK || sparse_words * K >= (int64_t(4) << 20);
+inline bool topic_list_ordered(double beta, double vbeta, int64_t n) {
+  return vbeta + double(n) < 0x1p50 && beta > 0x1p-960;
+}
+inline bool use_topic_list(int32_t K, int64_t sparse_words, bool ordered) {
+  return K >= kWBitsK || (ordered && sparse_words * K >= (int64_t(4) << 20));
 }
 inline bool w_bits(const Params &p) { return p.big_k || p.K >= kWBitsK; }
 // The count rebuild (Sec. 4.3): launch_rebuild = launch_zero_split, then

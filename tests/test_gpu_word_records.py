@@ -44,6 +44,26 @@ def test_records_by_topic_list_follow_the_oracle(K):
             z = got
 
 
+# beta so large that every W^ is the same number: K1 is topic 0 for every word, whatever T is
+@pytest.mark.parametrize("K", [1000, 4096])
+@pytest.mark.parametrize("beta", [1e18, 1e300])
+def test_equal_w_hat_takes_the_lowest_topic(K, beta):
+    import paper_2007_08725_amd as lda
+    rng = np.random.default_rng(K)
+    V, M, alpha = (5 << 20) // K, 300, 0.05
+    word = np.repeat(np.arange(V, dtype=np.int32), rng.integers(1, 9, V))
+    word = np.r_[word, np.full(K - 10, 7, np.int32)]  # one word past 64 tokens
+    doc = np.sort(rng.integers(0, M, word.size)).astype(np.int32)
+    doc[-1] = M - 1
+    z = rng.integers(0, K, word.size).astype(np.int32)
+    say("equal W^ K=%d beta=%g" % (K, beta))
+    with lda.LDA(word, doc, V, K, alpha, beta, SEED) as m:
+        m.set_assignments(z, 3)
+        want, flags, _ = oracle.iterate(word, doc, z, M=M, V=V, K=K, alpha=alpha, beta=beta, seed=SEED, t=3)
+        m.iterate(1)
+        compare_draws(m.counts(D=False, W=False)["z"], want, flags, max(word.size, 10 ** 6))
+
+
 def _records(word, doc, z, V, K, alpha, beta, two):
     """(a1, Q', sum W^, K1) per word id as the kernels left them in device memory after a scoring call."""
     import ctypes
