@@ -2574,10 +2574,10 @@ __global__ __launch_bounds__(kBlock) void k_block_base(DevState d, Params p) {
 // the single-precision row.  A unit's setup touches only what changes: after
 // another sparse word the previous word's topics go back to beta/den[k], the
 // new word's entries are written and their excess over beta/den[k] is added
-// to their blocks (LDS atomics in fp64: the sums' last bits depend on their
-// order, which tau covers), then the K / 32 block sums are scanned.  At
-// K = 32,768 the two-tile fp64 sampler filled three tiles of 16,400 topics
-// per region.
+// to their blocks (LDS atomics on whole numbers, q_units: exact_draw compares
+// with the block sums, so their bits must not depend on the waves' timing),
+// then the K / BS block sums are scanned.  At K = 32,768 the two-tile fp64
+// sampler filled three tiles of 16,400 topics per region.
 template <int NB>
 __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
                                                unsigned long long *__restrict__ stats) {
@@ -2604,6 +2604,7 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
   for (int k = K + tid; k < nwf; k += NB) wf[k] = 0.0f;
   uint32_t cur = 0xFFFFFFFFu, K1 = 0;
   double a1 = 0.0, qp = 0.0;
+  unsigned long long *qi = reinterpret_cast<unsigned long long *>(qb);  // a sparse word's block sums before the scan
   const int32_t *wrow = nullptr;   // the word's dense row, or null
   const uint32_t *held = nullptr;  // the sparse word whose row wf holds
   uint32_t held_nnz = 0, held_k1 = 0;
@@ -2638,6 +2639,7 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
       K1 = rec.k1;
       a1 = rec.a1;
       qp = rec.qp;
+      const int ex = q_exponent(qp);
       if (int32_t(v) < p.n_dense) {
         wrow = d.w_dense + size_t(v) * size_t(K);
         for (int k0 = wave * kWave; k0 < K; k0 += NB) {
@@ -2654,7 +2656,12 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
         const uint32_t *ents = d.ws_ent + d.ws_cap[s];
         const uint32_t nnz = d.ws_nnz[s];
         wrow = nullptr;
-        for (int q = tid; q < nb; q += NB) qb[q + 1] = d.qbase[q];
+        // K1's block: the sum of its other topics, by the last wave (the one
+        // with the fewest entries), its load ahead of the rest
+        const int b1 = int(K1) / BS, kb = b1 * BS + lane;
+        const bool lw = wave == NB / kWave - 1;
+        double others = lw && lane < BS && kb < K && uint32_t(kb) != K1 ? d.bden[kb] : 0.0;
+        for (int q = tid; q < nb; q += NB) qi[q + 1] = q == b1 ? 0ull : q_units(d.qbase[q], ex);
         if (held) {
           for (uint32_t q = tid; q < held_nnz; q += NB) {
             const uint32_t k = held[q] >> 16;
@@ -2669,9 +2676,12 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
           const uint32_t ent = ents[q], k = ent >> 16;
           const double w = what(ent & 0xFFFFu, p.beta, d.den[k]);
           wf[k] = float(w * kWScale);
-          if (k != K1) unsafeAtomicAdd(&qb[k / BS + 1], p.alpha * (w - d.bden[k]));
+          if (k != K1) atomicAdd(&qi[k / BS + 1], q_units(p.alpha * (w - d.bden[k]), ex));
         }
-        if (tid == 0 && K1 < uint32_t(K)) unsafeAtomicAdd(&qb[K1 / BS + 1], -(p.alpha * d.bden[K1]));
+        if (lw) {
+          others = wave_incl_scan(p.alpha * others);
+          if (lane == BS - 1 && b1 < nb) atomicAdd(&qi[b1 + 1], q_units(others, ex));
+        }
         held = ents;
         held_nnz = nnz;
         held_k1 = K1;
@@ -2683,7 +2693,7 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
       double *s_tot = s_u;  // [rounds * waves <= NB]; s_u is next written by the token batches
       for (int r = 0; r * NB < nb; ++r) {
         const int blk = r * NB + tid;
-        const double incl = wave_incl_scan(blk < nb ? qb[blk + 1] : 0.0);
+        const double incl = wave_incl_scan(blk >= nb ? 0.0 : wrow ? qb[blk + 1] : q_value(qi[blk + 1], ex));
         if (blk < nb) qb[blk + 1] = incl;
         if (lane == kWave - 1) s_tot[r * (NB / kWave) + wave] = incl;
       }

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -289,6 +290,22 @@ bool sampler_q_table(int K);
 __host__ __device__ constexpr int q_block_topics(int threads) { return threads == 256 ? 16 : 32; }
 constexpr int kF32Topics = 2300;
 inline bool use_f32(int32_t K, int32_t want_block) { return K >= kF32Topics || (want_block != 0 && want_block != kBlock); }
+// Its Q' block sums of a sparse word are added up by many lanes in no fixed
+// order, so they are whole numbers of units of 2^(ex - 62), 2^ex being the
+// power of two above the word's Q': any order gives the same bits, no sum
+// passes 2^62, and a term is off by at most 2^-62 of Q' (an fp64 sum by 2^-53
+// of itself at each addition).
+__host__ __device__ inline int q_exponent(double qp) {
+  int ex = 0;
+  (void)frexp(qp, &ex);
+  return ex;
+}
+__host__ __device__ inline unsigned long long q_units(double v, int ex) {
+  return (unsigned long long)rint(ldexp(v, 62 - ex));
+}
+__host__ __device__ inline double q_value(unsigned long long units, int ex) {
+  return ldexp(double(units), ex - 62);
+}
 int sampler_f_block(int K, int want);
 size_t sampler_f_lds_bytes(int K, int nb);
 int loglik_block(int K);  // threads per workgroup of k_loglik (the most resident waves)

@@ -79,3 +79,29 @@ def test_rows_of_many_chunks():
         want, flags, _ = oracle.iterate(word, doc, z, seed=SEED, t=1, **kw)
         m.iterate(1)
         compare_draws(m.counts(D=False, W=False)["z"], want, flags, max(word.size, 10 ** 6))
+
+
+# rows of several hundred entries a word, spread over the blocks of the Q' prefix and over the waves of a workgroup
+@pytest.mark.parametrize("K,alpha", [(2500, 0.05), (2500, 20.0), (20_000, 0.05)])
+def test_determinism_and_resume(K, alpha):
+    """The same topics on every run, from a resumed state, and however the regions are cut and the workgroups sized."""
+    import paper_2007_08725_amd as lda
+    rng = np.random.default_rng(K)
+    doc = np.repeat(np.arange(900, dtype=np.int32), rng.integers(100, 500, 900))
+    word = rng.choice(400, doc.size).astype(np.int32)
+
+    def fit(start=None, t=0, iters=6, **opts):
+        with lda.LDA(word, doc, 400, K, alpha, 0.01, SEED, **opts) as m:
+            if start is not None:
+                m.set_assignments(start, t)
+            m.iterate(iters)
+            return m.counts(D=False, W=False)["z"]
+
+    say("determinism K=%d alpha=%g" % (K, alpha))
+    want, half = fit(), fit(iters=3)
+    assert np.array_equal(fit(), want)
+    assert np.array_equal(fit(start=half, t=3, iters=3), want)
+    assert np.array_equal(fit(region_tokens=150), want)
+    if K <= 4000:
+        for block in (256, 512, 1024):
+            assert np.array_equal(fit(sampler_block=block), want)

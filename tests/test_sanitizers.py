@@ -1,9 +1,11 @@
 """The CPU code under AddressSanitizer and UndefinedBehaviorSanitizer: the
-oracle (oracle/lda_oracle.c) and the host layout planner
-(paper_2007_08725_amd/csrc/layout.cpp) are built with -fsanitize=address,undefined
+oracle (oracle/lda_oracle.c), the host layout planner
+(paper_2007_08725_amd/csrc/layout.cpp) and the whole-number Q' sums shared with
+the device are built with -fsanitize=address,undefined
 (host compilers only; no device code is involved) and driven over seeded
 small corpora by tests/sanitize/*.  Any sanitizer report fails the run."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -40,3 +42,28 @@ def test_layout_planner_under_sanitizers(tmp_path):
           os.path.join(HERE, "sanitize", "layout_checks.cpp"), os.path.join(csrc, "layout.cpp"), "-o", exe])
     r = _run([exe], env=ENV)
     assert "layout checks passed" in r.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
+                    reason="g++ or the HIP headers are not installed")
+def test_q_sums_do_not_depend_on_the_order(tmp_path):
+    exe = str(tmp_path / "q_sum_checks")
+    _run(["g++", "-std=c++17", *SAN, "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I",
+          os.path.join(ROOT, "paper_2007_08725_amd", "csrc"), os.path.join(HERE, "sanitize", "q_sum_checks.cpp"),
+          "-o", exe])
+    r = _run([exe], env=ENV)
+    assert "Q' sum checks passed" in r.stdout
+
+
+def test_kernels_add_no_floating_point_atomics():
+    """Draws and LLPT promise the same bits on every run: an atomic sum of floating-point values has the order of the
+    waves' timing, so the kernels' atomics are whole numbers (their operands' types are declared in the sources)."""
+    csrc = os.path.join(ROOT, "paper_2007_08725_amd", "csrc")
+    for name in sorted(os.listdir(csrc)):
+        if not name.endswith((".hip", ".h", ".cpp")):
+            continue
+        text = open(os.path.join(csrc, name)).read()
+        assert "unsafeAtomicAdd" not in text and "__builtin_amdgcn_ds_atomic_fadd" not in text, name
+        doubles = set(re.findall(r"\b(?:double|float)\s*\*\s*(?:__restrict__\s*)?(\w+)", text))
+        for target in re.findall(r"atomicAdd\(\s*&?\s*(?:\w+(?:\.|->))*(\w+)", text):
+            assert target not in doubles, "%s: atomicAdd on %s" % (name, target)
