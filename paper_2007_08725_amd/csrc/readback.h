@@ -6,10 +6,10 @@
 #include <atomic>
 #include <condition_variable>
 #include <cstring>
+#include <exception>
 #include <functional>
 #include <mutex>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -23,9 +23,10 @@ class Crew {
  public:
   explicit Crew(int threads) {
     try {
+      th_.reserve(size_t(std::max(threads, 1)));  // no growth below: it could fail with threads running
       for (int q = 1; q < threads; ++q) th_.emplace_back([this] { loop(); });
-    } catch (const std::system_error &) {
-      // fewer threads: the pieces are shared among those there are
+    } catch (const std::exception &) {
+      // no thread or no memory for one: the pieces are shared among those there are
     }
   }
   ~Crew() {

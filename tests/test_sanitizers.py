@@ -1,9 +1,9 @@
 """The CPU code under AddressSanitizer and UndefinedBehaviorSanitizer: the
 oracle (oracle/lda_oracle.c), the host layout planner
-(paper_2007_08725_amd/csrc/layout.cpp) and the whole-number Q' sums shared with
-the device are built with -fsanitize=address,undefined
-(host compilers only; no device code is involved) and driven over seeded
-small corpora by tests/sanitize/*.  Any sanitizer report fails the run."""
+(paper_2007_08725_amd/csrc/layout.cpp), the whole-number Q' sums shared with
+the device and the host threads of the exports (csrc/readback.h) are built with
+-fsanitize=address,undefined (host compilers only; no device code is involved)
+and driven by tests/sanitize/*.  Any sanitizer report fails the run."""
 import os
 import re
 import shutil
@@ -67,3 +67,14 @@ def test_kernels_add_no_floating_point_atomics():
         doubles = set(re.findall(r"\b(?:double|float)\s*\*\s*(?:__restrict__\s*)?(\w+)", text))
         for target in re.findall(r"atomicAdd\(\s*&?\s*(?:\w+(?:\.|->))*(\w+)", text):
             assert target not in doubles, "%s: atomicAdd on %s" % (name, target)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
+                    reason="g++ or the HIP headers are not installed")
+def test_read_back_threads_survive_failed_allocations(tmp_path):
+    exe = str(tmp_path / "crew_checks")
+    _run(["g++", "-std=c++17", *SAN, "-pthread", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I",
+          os.path.join(ROOT, "paper_2007_08725_amd", "csrc"), os.path.join(HERE, "sanitize", "crew_checks.cpp"),
+          "-o", exe])
+    r = _run([exe], env=ENV)
+    assert "crew checks passed" in r.stdout
