@@ -150,18 +150,23 @@ lda_status read_back(lda_handle *h, Crew &crew, const T *dev, size_t n, const F 
   const size_t bytes = n * sizeof(T);
   if (n == 0) return LDA_OK;
   if (bytes > kReadSmall && !h->stage[0]) {
-    // both or none: without pinned memory the copies below go straight to host memory
+    // all or none: without pinned memory the copies below go straight to host memory
     void *a = nullptr, *b = nullptr;
+    hipEvent_t ea = nullptr, eb = nullptr;
     if (hipHostMalloc(&a, kStageBytes, hipHostMallocDefault) == hipSuccess &&
         hipHostMalloc(&b, kStageBytes, hipHostMallocDefault) == hipSuccess &&
-        hipEventCreateWithFlags(&h->stage_ev[0], hipEventDisableTiming) == hipSuccess &&
-        hipEventCreateWithFlags(&h->stage_ev[1], hipEventDisableTiming) == hipSuccess) {
+        hipEventCreateWithFlags(&ea, hipEventDisableTiming) == hipSuccess &&
+        hipEventCreateWithFlags(&eb, hipEventDisableTiming) == hipSuccess) {
       h->stage[0] = a;
       h->stage[1] = b;
+      h->stage_ev[0] = ea;
+      h->stage_ev[1] = eb;
     } else {
       (void)hipGetLastError();
       if (a) (void)hipHostFree(a);
       if (b) (void)hipHostFree(b);
+      if (ea) (void)hipEventDestroy(ea);
+      if (eb) (void)hipEventDestroy(eb);
     }
   }
   if (bytes <= kReadSmall || !h->stage[0]) {

@@ -78,3 +78,14 @@ def test_read_back_threads_survive_failed_allocations(tmp_path):
           "-o", exe])
     r = _run([exe], env=ENV)
     assert "crew checks passed" in r.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
+                    reason="g++ or the HIP headers are not installed")
+def test_read_back_leaves_nothing_behind(tmp_path):
+    exe = str(tmp_path / "readback_checks")
+    _run(["g++", "-std=c++17", *SAN, "-pthread", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I",
+          os.path.join(ROOT, "paper_2007_08725_amd", "csrc"), os.path.join(HERE, "sanitize", "readback_checks.cpp"),
+          "-o", exe])
+    r = _run([exe], env=ENV)
+    assert "read-back checks passed" in r.stdout
