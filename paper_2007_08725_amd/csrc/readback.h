@@ -99,6 +99,8 @@ struct Scratch {
   bool on_host = false;
   explicit Scratch(lda_handle *handle) : h(handle) {}
   ~Scratch() {
+    // left by an exception (no host memory), kernels may still be at work on it
+    if (ptr && std::uncaught_exceptions()) (void)hipStreamSynchronize(h->stream);
     if (on_host) (void)hipHostFree(ptr);
     else dfree(h, ptr);
   }

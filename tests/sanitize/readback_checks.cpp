@@ -9,15 +9,31 @@
 #include "readback.h"
 
 static int g_events, g_fail_event = -1, g_pinned, g_pinned_room = 1 << 20;
+static bool g_at_work, g_freed_at_work;  // queued kernels not waited for; memory given back meanwhile
+static long g_countdown = -1;            // the host allocation that fails (negative: none)
+void *operator new(std::size_t n) {
+  if (g_countdown >= 0 && g_countdown-- == 0) throw std::bad_alloc();
+  void *p = std::malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, std::size_t) noexcept { std::free(p); }
 
 extern "C" {
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t) {
   std::memcpy(dst, src, n);
   return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) {
+  g_at_work = false;
+  return hipSuccess;
+}
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) {
+  g_at_work = false;
+  return hipSuccess;
+}
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
   if (g_fail_event >= 0 && g_fail_event-- == 0) return hipErrorOutOfMemory;
   ++g_events;
@@ -57,6 +73,12 @@ void release_chunks(ChunkMode *) {}
       return 1;                                                       \
     }                                                                 \
   } while (0)
+
+static void *dev_alloc(size_t n, void *) { return std::malloc(n); }
+static void dev_free(void *p, void *) {
+  g_freed_at_work = g_freed_at_work || g_at_work;
+  std::free(p);
+}
 
 static void drop_stage(lda_handle &h) {
   for (int q = 0; q < 2; ++q) {
@@ -104,6 +126,32 @@ int main() {
     CHECK(!h.stage[0] && g_events == 0 && g_pinned == 0);
     g_pinned_room = 1 << 20;
     drop_stage(h);
+  }
+  // host memory that runs out between a kernel's launch and the wait for its results: the device array that it
+  // writes is given back to the caller's allocator only when the kernel is done
+  for (long fail = 0; fail < 50; ++fail) {
+    lda_handle h;
+    h.dev_alloc = dev_alloc;
+    h.dev_free = dev_free;
+    bool threw = false;
+    try {
+      lda::Crew crew(1);
+      lda::Scratch<uint32_t> a(&h);
+      CHECK(a.get(1000) == LDA_OK);
+      std::memset(a.ptr, 0, 4000);
+      g_at_work = true;  // a launch
+      g_countdown = fail;
+      CHECK(lda::read_back(&h, crew, a, 1000, [](const uint32_t *, size_t, size_t) {}) == LDA_OK);
+      g_countdown = -1;
+    } catch (const std::bad_alloc &) {
+      threw = true;
+    }
+    g_countdown = -1;
+    CHECK(!g_freed_at_work && h.allocations.empty());
+    if (!threw) {
+      CHECK(fail > 0);  // at least one allocation failed
+      break;
+    }
   }
   std::printf("read-back checks passed\n");
   return 0;
