@@ -319,11 +319,10 @@ lda_status resident_counts(lda_handle *h, lda_counts *out) {
   Crew crew(read_threads(std::max({out->z ? 2 * n : 0, out->D_topic ? size_t(nnz[0]) * 4 : 0,
                                    out->W_topic ? size_t(nnz[1]) * 8 : 0})));
   if (out->z) {
-    uint16_t *zin = nullptr;
-    LDA_TRY(dalloc(h, &zin, n));
-    HIP_TRY(h, launch_gather_z16(h->d.dt_wpos, h->d.dt_key, h->d.z_w, L.n, zin, h->stream));
+    Scratch<uint16_t> zin(h);
+    LDA_TRY(zin.get(n));
+    HIP_TRY(h, launch_gather_z16(h->d.dt_wpos, h->d.dt_key, h->d.z_w, L.n, zin.ptr, h->stream));
     LDA_TRY(read_z(h, crew, zin, n, out->z));
-    dfree(h, zin);
   }
   if (out->T) {
     std::vector<uint32_t> tk(static_cast<size_t>(K));

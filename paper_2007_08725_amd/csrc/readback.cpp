@@ -10,11 +10,20 @@ constexpr size_t kSlabEntries = size_t(1) << 23;  // entries of a slab (32 MB of
 constexpr size_t kSlabRows = size_t(1) << 21;     // rows of a slab
 }  // namespace
 
-lda_status read_z(lda_handle *h, Crew &crew, const uint16_t *z, size_t n, int32_t *out) {
-  return read_back(h, crew, z, n, [out](const uint16_t *src, size_t first, size_t m) {
+namespace {
+auto widen_to(int32_t *out) {
+  return [out](const uint16_t *src, size_t first, size_t m) {
     int32_t *dst = out + first;
     for (size_t i = 0; i < m; ++i) dst[i] = int32_t(src[i]);
-  });
+  };
+}
+}  // namespace
+
+lda_status read_z(lda_handle *h, Crew &crew, const uint16_t *z, size_t n, int32_t *out) {
+  return read_back(h, crew, z, n, widen_to(out));
+}
+lda_status read_z(lda_handle *h, Crew &crew, const Scratch<uint16_t> &z, size_t n, int32_t *out) {
+  return read_back(h, crew, z, n, widen_to(out));
 }
 
 lda_status export_d(lda_handle *h, Crew &crew, const DevState &d, int32_t M, int64_t at, int64_t *off, int32_t *topic,

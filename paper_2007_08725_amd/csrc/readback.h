@@ -218,6 +218,7 @@ lda_status read_back(lda_handle *h, Crew &crew, const Scratch<T> &from, size_t n
 
 // Caller arrays of one export.
 lda_status read_z(lda_handle *h, Crew &crew, const uint16_t *z, size_t n, int32_t *out);
+lda_status read_z(lda_handle *h, Crew &crew, const Scratch<uint16_t> &z, size_t n, int32_t *out);
 // D rows of documents [0, M) of d (offsets d_cap) as CSR, appended at entry
 // `at` of the topic and count arrays: off[q] = entry of document q's first
 // (M + 1 written); returns the entries written in *entries.
