@@ -553,8 +553,18 @@ lda_status lda_set_assignments(lda_handle *h, const int32_t *z, int64_t iteratio
   if (h->chunks) return chunked_set_assignments(h, z, iteration);
   const Layout &L = h->L;
   const size_t n = size_t(L.n);
+  auto out_of_range = [&]() -> lda_status {  // LDA_E_ARG for the first topic outside [0, K), else LDA_OK
+    for (size_t i = 0; i < n; ++i)
+      if (z[i] < 0 || z[i] >= L.K) return fail(h, LDA_E_ARG, "topic out of range at token " + std::to_string(i));
+    return LDA_OK;
+  };
   int32_t *zin = nullptr;
-  LDA_TRY(dalloc(h, &zin, n));
+  const lda_status room = dalloc(h, &zin, n);
+  if (room != LDA_OK) {
+    const std::string msg = h->err;
+    LDA_TRY(out_of_range());
+    return fail(h, room, msg);
+  }
   HIP_TRY(h, hipMemcpyAsync(zin, z, n * 4, hipMemcpyHostToDevice, h->stream));
   // the topics are checked on the device before anything of the state changes
   unsigned long long bad = 0;
@@ -564,8 +574,7 @@ lda_status lda_set_assignments(lda_handle *h, const int32_t *z, int64_t iteratio
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   if (bad) {
     dfree(h, zin);
-    for (size_t i = 0; i < n; ++i)
-      if (z[i] < 0 || z[i] >= L.K) return fail(h, LDA_E_ARG, "topic out of range at token " + std::to_string(i));
+    LDA_TRY(out_of_range());
     return fail(h, LDA_E_ARG, "topic out of range");
   }
   HIP_TRY(h, hipMemsetAsync(h->stats_base, 0, sizeof(unsigned long long) * kStatsPerIter, h->stream));

@@ -108,6 +108,14 @@ def test_tables_are_exported_without_device_memory_to_spare(n_docs, mean, V, K, 
         assert len(live) == kept
         for name in ref:
             assert np.array_equal(ref[name], got[name]), name
+        # topics out of range are LDA_E_ARG with their place, topics in range LDA_E_NOMEM; both leave the state alone
+        if not chunks:
+            z = ref["z"].copy()
+            assert lib.lda_set_assignments(h, ptr(z), 5) == lda.LDA_E_NOMEM
+            z[n // 2] = K
+            assert lib.lda_set_assignments(h, ptr(z), 5) == lda.LDA_E_ARG
+            assert b"topic out of range at token %d" % (n // 2) in lib.lda_last_error(h)
+            assert np.array_equal(tables()["z"], ref["z"])
     finally:
         lib.lda_destroy(h)
     assert not live
