@@ -1559,13 +1559,14 @@ __device__ void draw_rounds(int from, int to, const int (&ends)[8], const BatchL
 // 97-128 slots (two whole 64-slot chunks), those rows join the 8-lane
 // rounds instead: they fill free places there, or make a round that reads
 // half as many entries per lane as the partial 4-lane round would.
-// Wide (the 1024-thread workgroups, whose waves have registers to spare):
-// rows of up to 512 slots by 8 lanes as well, 8 tokens a round, so that a
-// round's per-token work (sums, scans, the split of x) serves twice the
+// Wide (sums only: the LLPT kernel's 1,024-thread workgroups, whose waves have
+// registers to spare): rows of up to 512 slots by 8 lanes as well, 8 tokens a
+// round, so that a round's per-token work (sums, scans) serves twice the
 // tokens.
-template <bool Wide, bool Sum = false>
+template <bool Wide, bool Sum>
 __device__ void draw_batch_small(bool und, uint32_t nnz, const BatchLds &bt, const WordState &w,
                                  const uint32_t *__restrict__ d_ent, int lane, uint32_t &after_s) {
+  static_assert(Sum || !Wide, "no workgroup of 1,024 threads draws in fp64");
   int n = 0, ends[8];
   const uint32_t slots = nnz + 1u;
 #pragma unroll
@@ -1600,7 +1601,7 @@ __device__ void draw_batch_small(bool und, uint32_t nnz, const BatchLds &bt, con
 // S' walks and Q' searches, one lane per token.
 // Sum: no draws; bt.u of every such lane gets the sum of its row's terms
 // D[d][k] * W^[v][k] instead (w.wh with all of W^[v]).
-template <bool Wide, bool Sum = false>
+template <bool Wide = false, bool Sum = false>
 __device__ __forceinline__ uint32_t draw_tokens(bool und, uint32_t off, uint32_t nnz, int first, int ln,
                                                 const BatchLds &bt, const WordState &w,
                                                 const uint32_t *__restrict__ d_ent, uint32_t &after_s,
@@ -1636,14 +1637,14 @@ __device__ __forceinline__ void store_stats(const DevState &d, uint32_t slot, bo
   st[size_t(WV_ROW_BYTES) * kWaveSlots] = first ? row_bytes : 0ull;
 }
 
-// The sampler for workgroups of NB threads (NB / 64 waves); every wave works
-// on its own batches, so NB only changes how many waves share a region's W^
-// row in LDS.
-// It takes the units (sampler_units) of the regions before p.light_begin; the
+// The sampler with the W^' row in fp64 (K below kF32Topics): workgroups of four
+// waves that share a word's row in LDS, every wave on its own batches.  It
+// takes the units (sampler_units) of the regions before p.light_begin; the
 // light regions are k_sampler_light's.
-template <int NB>
-__device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, unsigned long long *__restrict__ stats) {
+__global__ __launch_bounds__(kBlock, 7) void k_sampler(DevState d, Params p, uint32_t t,
+                                                       unsigned long long *__restrict__ stats) {
   extern __shared__ double lds[];
+  constexpr int NB = kBlock;
   const int K = p.K;
   const int nb = (K + kGroup - 1) / kGroup;
   const int nbp = q_blocks_padded(nb);
@@ -1827,7 +1828,7 @@ __device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, u
       }
       n_sampled += uint32_t(__popcll(__ballot(und)));
       uint32_t nnz_read;
-      const uint32_t drawn = draw_tokens<(NB >= 1024)>(und, off, nnz, 0, ln, bt, w, d.d_ent, n_after_s, &nnz_read);
+      const uint32_t drawn = draw_tokens(und, off, nnz, 0, ln, bt, w, d.d_ent, n_after_s, &nnz_read);
       nnz_sum += wave_sum_u32(nnz_read);
       // the batch's topics (K1 for the tokens the step-3 test decided) leave in one coalesced store
       const uint32_t topic = und ? drawn : K1;
@@ -1840,10 +1841,6 @@ __device__ __forceinline__ void sampler_body(DevState d, Params p, uint32_t t, u
                 n_dreg, row_bytes);
 }
 
-__global__ __launch_bounds__(256, 7) void k_sampler(DevState d, Params p, uint32_t t,
-                                                 unsigned long long *__restrict__ stats) {
-  sampler_body<256>(d, p, t, stats);
-}
 // W^ of a dense row into a wave's LDS row, kLightAhead topics per lane loaded
 // together (one after another each topic waited for memory: out of core, where
 // every light word is a dense row, 1.20 ms a chunk of 123,000 words).
@@ -2023,7 +2020,7 @@ __global__ __launch_bounds__(64, 4) void k_sampler_light(DevState d, Params p, u
       order();
       const WordState w{wh, qb, nb, K, nbp / 2, K1, a1, qp, p.alpha, nullptr, nullptr};
       uint32_t nnz_read;
-      const uint32_t drawn = draw_tokens<false>(mine && und, off, nnz, f, ln, bt, w, d.d_ent, n_after_s, &nnz_read);
+      const uint32_t drawn = draw_tokens(mine && und, off, nnz, f, ln, bt, w, d.d_ent, n_after_s, &nnz_read);
       nnz_sum += wave_sum_u32(nnz_read);
       if (mine) topic = und ? drawn : K1;
       order();  // wh and qb are rewritten for the next word
@@ -2049,7 +2046,7 @@ struct TileState {
 
 // W^' of a packed D entry's topic if it lies in the tile, else 0 (wt[kt] is
 // 0).  The tile starts at LDS address 0 (the kernel's LDS is all dynamic,
-// which launch_sampler checks), so the address (topic - base) * 8 is one
+// which launch_loglik checks), so the address (topic - base) * 8 is one
 // v_mad_u32_u16 on the entry's high half; topics below the tile wrap to
 // addresses near 2^32, and one unsigned min sends every topic outside the
 // tile to wt[kt].
@@ -2570,7 +2567,7 @@ __global__ __launch_bounds__(kBlock) void k_block_base(DevState d, Params p) {
   if (k % BS == 0 && k < p.K) d.qbase[k / BS] = v;
 }
 
-// The sampler of the units, NB threads per workgroup: as sampler_body, with
+// The sampler of the units, NB threads per workgroup: as k_sampler, with
 // the single-precision row.  A unit's setup touches only what changes: after
 // another sparse word the previous word's topics go back to beta/den[k], the
 // new word's entries are written and their excess over beta/den[k] is added
@@ -3456,8 +3453,8 @@ __global__ __launch_bounds__(kBlock) void k_rebuild_d_sort(DevState d, Params p)
 
 // LLPT terms (Sec. 2.2): for every token,
 //   log2( (sum_{k in nz(D[d])} D[d][k] W^[v][k] + alpha * sum_k W^[v][k]) / (len(d) + K alpha) ),
-// summed per unit of the sampler (per batch of light regions) in an order that the layout
-// fixes, so that the result does not depend on the schedule.
+// summed per unit of the sampler (per batch of light regions) in an order that
+// the layout fixes, so that the result does not depend on the schedule.
 //
 // The work is the sampler's S' pass without the draws, and it is organised the
 // same way: batches of 64 tokens per wave, rows in registers by groups of 4, 8
@@ -3658,10 +3655,10 @@ __global__ __launch_bounds__(64, 4) void k_loglik_light(DevState d, Params p) {
   }
 }
 
-// Large K: the row in two tiles.  Pass 0 keeps each
-// token's sum over the topics below KT and the chunk where its row reaches KT
-// (the per-workgroup scratch of the sampler), pass 1 adds the topics from KT
-// on, reading the row from that chunk.
+// Large K: the row in two tiles.  Pass 0 keeps each token's sum over the topics
+// below KT and the chunk where its row reaches KT (in the workgroup's slice of
+// ts_s and ts_code), pass 1 adds the topics from KT on, reading the row from
+// that chunk.
 __global__ __launch_bounds__(kTiledBlock) void k_loglik_tiled(DevState d, Params p) {
   extern __shared__ double lds[];
   const int K = p.K;

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kThreads) void k_sum_nnz(DevState d, Params p, int 
   if (D)
     for (int64_t q = i0; q < p.M; q += step) nd += d.d_ent[d.d_cap[q]] & 0xFFFFu;
   if (W) {
-    // the dense table by 16 bytes (its base is 256-byte aligned), then its last values
+    // the dense table by 16 bytes (global loads of 16 bytes need 4-byte alignment only), then its last values
     const int64_t total = int64_t(p.n_dense) * p.K, quads = total / 4;
     const int4 *w4 = reinterpret_cast<const int4 *>(d.w_dense);
     for (int64_t q = i0; q < quads; q += step) {
