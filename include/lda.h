@@ -86,9 +86,14 @@ typedef struct {
    * canonical order, so different draws for the same u. */
   int32_t two_branch;
   /* Threads per sampler workgroup: 256, 512 or 1024 (0 = the size with the
-   * most resident waves per CU for this K; the W^ row of K fp64 values in LDS
-   * limits how many workgroups a CU holds).  LDA_E_RANGE if the size asked
-   * for does not fit.  Performance switch; the draws are unchanged. */
+   * most resident waves per CU for this K; a word's row of K values in LDS,
+   * fp64 below K = 2,300 with 256 threads and single precision otherwise,
+   * limits how many workgroups a CU holds).  A size asked for is accepted
+   * while the CU's LDS would hold a workgroup of that size with an fp64 row,
+   * whichever row the sampler keeps: up to K = 17,743 (256), 17,071 (512) and
+   * 16,384 (1,024), LDA_E_RANGE above.  0 works at every K and may choose a
+   * size that cannot be asked for.  Performance switch; the draws are
+   * unchanged. */
   int32_t sampler_block;
   /* How the step-3 skip decisions reach the sampler (Sec. 3.3): 0 = chosen
    * per iteration from the previous iteration's skip rate (default); 1 =

@@ -54,12 +54,13 @@ lda_status setup_device(lda_handle *h, const lda_options *o) {
   Params &p = h->p;
   p.grid_regions = std::max(1, cus * 8);
   const int want = o ? o->sampler_block : 0;
-  // A size asked for has to fit with an fp64 W^' row (what the option promises
-  // for a K does not depend on which sampler draws).
+  // A size asked for has to fit with an fp64 W^' row, whichever sampler draws:
+  // the sizes that the option takes at a K are those of the fp64 sampler.
   auto fits = [&](int nb) { return sampler_lds_bytes(p.K, nb, false) <= size_t(lds_max); };
   if (want && !fits(want))
-    return fail(h, LDA_E_RANGE, "no sampler workgroup of " + std::to_string(want) + " threads fits the LDS of K = " +
-                                    std::to_string(L.K));
+    return fail(h, LDA_E_RANGE, "a sampler workgroup of " + std::to_string(want) +
+                                    " threads cannot be asked for at K = " + std::to_string(L.K) +
+                                    " (its LDS with an fp64 row)");
   p.big_k = fits(kBlock) ? 0 : 1;
   if (p.big_k) p.tile_topics = tiled_topics(p.K);
   else p.loglik_block = loglik_block(p.K);
