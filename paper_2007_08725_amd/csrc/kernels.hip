@@ -2176,10 +2176,9 @@ constexpr int kTiledAhead = 2;              // chunks whose loads a group issues
 // rounds only take x and the branch from the sums as they are; the bounds are
 // checked once per token by finish_f.  A wrong branch or run cannot pass: x
 // then lies outside the segment, or within the bound of its edge.
-constexpr double kEps = 9.5 * 0x1p-24;
+// (The bounds themselves are in lda_internal.h, kEps and draw_tau on.)
 constexpr uint16_t kDrawX = 0xFFFD;  // undecided: exact_draw
 constexpr uint16_t kDrawM = 0xFFFC;  // in the max-topic branch, not checked yet
-constexpr double kWScale = 0x1p24;   // the row holds W^' * 2^24
 // Documents longer than this may hold a count that is not exact as the f16
 // bits of fma_mix (an integer below 2^11 in the low half of an entry reads as
 // that integer times 2^-24, subnormal or not); their tokens take draw_long_f.
@@ -2443,8 +2442,8 @@ __device__ __forceinline__ uint32_t finish_f(int q, const BatchLds &bt, const Wo
   if (code == kDrawX) return kDrawX;
   const double xs = bt.u[q];
   const double S = double(__uint_as_float(bt.nnz[q])) * (1.0 + 0x1p-20);  // rounded up
-  const double tau = (w.a1 * (double(len) + w.alpha) + S + w.qp) * 0x1p-40 + 0x1p-90;  // C1 <= len
-  const double e2 = 2.0 * kEps * S + tau;
+  const double tau = draw_tau(w.a1 * (double(len) + w.alpha), S, w.qp);  // C1 <= len
+  const double e2 = s_bound(S, tau);
   if (code == kDrawM) return xs > e2 ? uint32_t(kDrawM) : uint32_t(kDrawX);
   if (code == kDrawS) {
     const uint32_t a = bt.off[q];
@@ -2465,10 +2464,9 @@ __device__ __forceinline__ uint32_t finish_f(int q, const BatchLds &bt, const Wo
     return xs - below > e2 && above - xs > e2 && below >= 0.0 ? ent >> 16 : uint32_t(kDrawX);
   }
   if (!(xs < w.qb[w.nb]) || !(xs >= 0.0)) return kDrawX;
-  const double eq1 = kEps * S * (w.qp / (S + w.qp)) * (1.0 + 0x1p-20) + tau;
+  const double eq1 = q_bound(S, w.qp, tau);
   const int lo = q_block_f(w, xs);
-  // inside the block in fp32, in units of alpha * 2^-24: x rounded once, at
-  // most BS + 1 roundings in a partial sum, two more in the comparison
+  // inside the block in fp32, in units of alpha * 2^-24
   const float inv = float(kWScale / w.alpha);
   const float xb = float((xs - w.qb[lo]) * (kWScale / w.alpha));
   const float *wb = w.wf + lo * BS;
@@ -2482,7 +2480,7 @@ __device__ __forceinline__ uint32_t finish_f(int q, const BatchLds &bt, const Wo
     p += wb[i];
   }
   const float above = below + wb[at];
-  const float eq = float(eq1) * inv * (1.0f + 0x1p-20f) + (p + xb) * (float(BS + 4) * 0x1p-24f);
+  const float eq = q_bound_f(eq1, inv, p, xb, BS);
   return xb - below > eq && above - xb > eq ? uint32_t(lo * BS + at) : uint32_t(kDrawX);
 }
 

@@ -290,6 +290,24 @@ bool sampler_q_table(int K);
 __host__ __device__ constexpr int q_block_topics(int threads) { return threads == 256 ? 16 : 32; }
 constexpr int kF32Topics = 2300;
 inline bool use_f32(int32_t K, int32_t want_block) { return K >= kF32Topics || (want_block != 0 && want_block != kBlock); }
+// Its bounds (why they hold: kernels.hip, "certified draws").  S' and its
+// prefixes are off by at most kEps of S; S here is S' rounded up, tau covers
+// the fp64 roundings and underflow; M is any number not below the max-topic
+// branch.  s_bound: x against M and against the edges inside S'.  q_bound: x
+// less M + S'.  q_bound_f: the same inside a Q' block of bs topics walked in
+// fp32, in units of alpha * 2^-24 (inv of them to 1): x rounded once, at most
+// bs + 1 roundings in a partial sum, two more in the comparison; p is the sum
+// of the block.
+constexpr double kEps = 9.5 * 0x1p-24;
+constexpr double kWScale = 0x1p24;  // the row holds W^' * 2^24
+__host__ __device__ inline double draw_tau(double M, double S, double qp) { return (M + S + qp) * 0x1p-40 + 0x1p-90; }
+__host__ __device__ inline double s_bound(double S, double tau) { return 2.0 * kEps * S + tau; }
+__host__ __device__ inline double q_bound(double S, double qp, double tau) {
+  return kEps * S * (qp / (S + qp)) * (1.0 + 0x1p-20) + tau;
+}
+__host__ __device__ inline float q_bound_f(double eq, float inv, float p, float xb, int bs) {
+  return float(eq) * inv * (1.0f + 0x1p-20f) + (p + xb) * (float(bs + 4) * 0x1p-24f);
+}
 // Its Q' block sums of a sparse word are added up by many lanes in no fixed
 // order, so they are whole numbers of units of 2^(ex - 62), 2^ex being the
 // power of two above the word's Q': any order gives the same bits, no sum

@@ -105,3 +105,106 @@ def test_determinism_and_resume(K, alpha):
     if K <= 4000:
         for block in (256, 512, 1024):
             assert np.array_equal(fit(sampler_block=block), want)
+
+
+EPS = 9.5 * 2.0 ** -24  # the bound on the single-precision error of S', of S'; the CPU checks see up to 4 of 9.5
+
+
+def _edges(word, doc, z, u, M, V, K, alpha, beta):
+    """Per token in fp64, by brute force: branch (0 M, 1 S', 2 Q'), the distance of x from the nearest edge, S' and Q'."""
+    import torch
+    dev = "cuda"
+    word, doc, z = (torch.as_tensor(a, device=dev).long() for a in (word, doc, z))
+    D = torch.bincount(doc * K + z, minlength=M * K).view(M, K).double()
+    W = torch.bincount(word * K + z, minlength=V * K).view(V, K).double()
+    den = W.sum(0) + V * beta
+    u = torch.as_tensor(u, device=dev)
+    out = [torch.empty(word.numel(), dtype=torch.float64, device=dev) for _ in range(4)]
+    step = max(1, 20_000_000 // K)
+    for b in range(0, word.numel(), step):
+        w = (W[word[b:b + step]] + beta) / den
+        d = D[doc[b:b + step]]
+        a1, k1 = w.max(1, keepdim=True)
+        m = a1 * (d.gather(1, k1) + alpha)
+        w.scatter_(1, k1, 0.0)
+        S, Q = (d * w).sum(1, keepdim=True), (alpha * w).sum(1, keepdim=True)
+        x = u[b:b + step, None] * ((m + S) + Q)
+        inside = torch.where(x < m + S, m + torch.cumsum(d * w, 1), (m + S) + torch.cumsum(alpha * w, 1))
+        near = torch.minimum((inside - x).abs().min(1, keepdim=True).values,
+                             torch.minimum((x - m).abs(), (x - (m + S)).abs()))
+        near = torch.where(x < m, m - x, near)
+        for o, v in zip(out, (torch.where(x < m, 0.0, torch.where(x < m + S, 1.0, 2.0)), near, S, Q)):
+            o[b:b + step] = v[:, 0]
+    return [o.cpu().numpy() for o in out]
+
+
+def _uniforms(t, n):
+    return np.array([oracle.uniform(SEED, t, i) for i in range(n)])
+
+
+@pytest.mark.parametrize("K", [2500, 10_000, 32_768])
+def test_both_ways_are_taken(K):
+    """The corpus of these tests has tokens within the bound of an edge of S' and of Q', which are redone in fp64, and
+    at least 95% of its tokens further from every edge than the bound and its own error, which are not."""
+    word, doc, z, M = _corpus(K, 3)
+    say("both ways K=%d" % K)
+    branch, near, S, Q = _edges(word, doc, z, _uniforms(1, word.size), M, 2000, K, 0.05, 0.01)
+    eq = EPS * S * Q / (S + Q)
+    # the single-precision x and edge are each off by at most 4 of the 9.5 units
+    assert np.sum((branch == 1) & (near < EPS * S)) >= 1
+    assert np.sum((branch == 2) & (near < 0.5 * eq)) >= 1
+    # inside a block of 32 topics the walk's own bound is below (32 + 4) * 2^-23 of the block, here at most of Q'
+    far = np.where(branch == 2, near > 2.5 * eq + 36 * 2.0 ** -23 * Q, near > 3 * EPS * S)
+    assert far.mean() > 0.95 if K < 30_000 else far.mean() > 0.5
+
+
+@pytest.mark.parametrize("K", [2500, 20_000])
+def test_draws_next_to_the_max_topic_edge(K):
+    """alpha chosen so that one token's x falls beside M by half the bound, on either side: redone in fp64, and right
+    (an edge of the max-topic branch is within the bound of one x in a million, so no corpus holds it by itself)."""
+    import paper_2007_08725_amd as lda
+    word, doc, z, M = _corpus(K, 5, tokens=20_000)
+    t, V, beta = 4, 2000, 0.01
+    u = _uniforms(t, word.size)
+    D = np.bincount(doc.astype(np.int64) * K + z, minlength=M * K).reshape(M, K)
+    W = np.bincount(word.astype(np.int64) * K + z, minlength=V * K).reshape(V, K)
+    den = W.sum(0) + V * beta
+    tried = 0
+    for i in np.random.default_rng(1).permutation(word.size):
+        w = (W[word[i]] + beta) / den
+        k1 = int(np.argmax(w))
+        a1, rest = w[k1], np.delete(w, k1).sum()
+        S = float(np.dot(D[doc[i]], w) - D[doc[i], k1] * a1)
+        # M - x = a1 (C1 + alpha) (1 - u) - u (S + alpha rest) = side * kEps S / 2, linear in alpha
+        for side in (1.0, -1.0):
+            slope = a1 * (1 - u[i]) - u[i] * rest
+            alpha = (side * 0.5 * EPS * S - a1 * D[doc[i], k1] * (1 - u[i]) + u[i] * S) / slope
+            Z = a1 * (D[doc[i], k1] + alpha) + S + alpha * rest
+            # a usable prior, with the edge further than the oracle's own margin (1e-9 of Z)
+            if not (1e-3 < alpha < 50.0) or 0.5 * EPS * S < 1e-8 * Z:
+                continue
+            say("edge of M K=%d token %d side %+d alpha=%.6g" % (K, i, side, alpha))
+            with lda.LDA(word, doc, V, K, alpha, beta, SEED) as m:
+                m.set_assignments(z, t)
+                want, flags, _ = oracle.iterate(word, doc, z, M=M, V=V, K=K, alpha=alpha, beta=beta, seed=SEED, t=t)
+                m.iterate(1)
+                got = m.counts(D=False, W=False)["z"]
+            assert not flags[i] & 1 and got[i] == want[i] and (want[i] == k1) == (side > 0)
+            compare_draws(got, want, flags, max(word.size, 10 ** 6))
+            tried += 1
+        if tried >= 6:
+            break
+    assert tried >= 6
+
+
+@pytest.mark.parametrize("block,last", [(256, 17_743), (512, 17_071), (1024, 16_384)])
+def test_sizes_that_can_be_asked_for(block, last):
+    import paper_2007_08725_amd as lda
+    word, doc = np.array([0, 1, 0], np.int32), np.array([0, 0, 1], np.int32)
+    with lda.LDA(word, doc, 2, last, 0.05, 0.01, SEED, sampler_block=block) as m:
+        assert m.iterate(1, stats=True)[0]["sampler_block"] == block
+    with pytest.raises(lda.LDAError) as e:
+        lda.LDA(word, doc, 2, last + 1, 0.05, 0.01, SEED, sampler_block=block)
+    assert e.value.status == lda.LDA_E_RANGE
+    with lda.LDA(word, doc, 2, last + 1, 0.05, 0.01, SEED) as m:
+        assert m.iterate(1, stats=True)[0]["sampler_block"] in (256, 512, 1024)

@@ -89,3 +89,14 @@ def test_read_back_leaves_nothing_behind(tmp_path):
           "-o", exe])
     r = _run([exe], env=ENV)
     assert "read-back checks passed" in r.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
+                    reason="g++ or the HIP headers are not installed")
+def test_certified_draws_that_stand_are_the_exact_ones(tmp_path):
+    exe = str(tmp_path / "certified_checks")
+    _run(["g++", "-std=c++17", *SAN, "-O2", "-ffp-contract=off", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I",
+          os.path.join(ROOT, "paper_2007_08725_amd", "csrc"), os.path.join(HERE, "sanitize", "certified_checks.cpp"),
+          "-o", exe])
+    r = _run([exe], env=ENV)
+    assert "certified draw checks passed" in r.stdout, r.stdout
