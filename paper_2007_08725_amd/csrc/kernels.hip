@@ -133,6 +133,21 @@ __device__ __forceinline__ double wave_incl_scan(double v) {
   return v;
 }
 
+// Inclusive prefix sum of whole numbers over each row of 16 lanes.
+template <int S>
+__device__ __forceinline__ unsigned long long row_shr_u64(unsigned long long v) {
+  const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(v)), 0x110 + S, 0xF, 0xF, true));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(v >> 32)), 0x110 + S, 0xF, 0xF, true));
+  return (unsigned long long)hi << 32 | lo;
+}
+__device__ __forceinline__ unsigned long long row_incl_scan_u64(unsigned long long v) {
+  v += row_shr_u64<1>(v);
+  v += row_shr_u64<2>(v);
+  v += row_shr_u64<4>(v);
+  v += row_shr_u64<8>(v);
+  return v;
+}
+
 // A double from lane l (uniform) to every lane.
 __device__ __forceinline__ double readlane_f64(double v, int l) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
@@ -379,25 +394,34 @@ __device__ __forceinline__ void beta_sum_all(const DevState &d, int K) {
 // K from 4,096 on (below, k_topic_list's last workgroup).
 __global__ __launch_bounds__(kBlock) void k_beta_sum(DevState d, Params p) { beta_sum_all(d, p.K); }
 
-// A sparse word's sums from its row, one lane's entries: Q' / alpha is the sum
-// of W^ over every topic but K1, that is beta/den[k] over the topics outside
-// the row and W^ over its other entries.  Both are formed without W^[v][K1]
-// ever being in them: taken off the whole sum, a K1 that holds nearly all of
-// it would leave Q' with the rounding errors of the whole (up to 7e-9 of Q' for
-// words of one topic at beta = 1e-9, K = 1,000; now below 40 * 2^-53).  The topics outside are the
-// sum over all of them less the row's, with the errors of both kept (Sum2),
-// since the row may hold most of it.
+// Q' and the sum of W^[v] from `others`, the sum of W^[v] over every topic but
+// K1.  It comes with its rounding errors (Sum2), so that the numbers are the
+// exact sums rounded once: the same bits from a dense row, topic by topic, and
+// from a sparse one (RowSums), and so the same draws.
+__device__ __forceinline__ void write_word_sums(const DevState &d, const Params &p, int r, const WordTop &top, Sum2 others) {
+  const double sw = sum2_add(others, Sum2{top.a1, 0.0}).h;
+  write_word_records(d, p, r, top, p.alpha * (p.two_branch ? sw : others.h), sw);
+}
+
+// A sparse word's sums from its row, one lane's entries: the sum of W^ over
+// every topic but K1 is the sum of beta/den[k] over all topics, less
+// beta/den[k] of the row's topics, plus W^ of its entries other than K1.
+// W^[v][K1] is never in it: taken off a plain sum, a K1 that holds nearly all
+// of it would leave Q' with the rounding errors of the whole (up to 7e-9 of Q'
+// for words of one topic at beta = 1e-9, K = 1,000).
 struct RowSums {
-  Sum2 beta{0.0, 0.0};    // beta/den[k] of the entries
-  double rest = 0.0;      // W^ of the entries, but the largest (lowest topic on ties)
-  double best = 0.0;      // W^ of that one
+  Sum2 rest{0.0, 0.0};    // W^ of the entries but the largest (lowest topic on ties), less their beta/den[k]
+  double best = 0.0;      // W^ of the largest
   uint32_t best_k = 0xFFFFFFFFu;
-  __device__ __forceinline__ void entry(double w, double bden, uint32_t k) {
-    sum2_push(beta, bden);
+  __device__ __forceinline__ void topic(double w, uint32_t k) {
     const bool b = better(w, k, best, best_k);
-    rest += b ? best : w;
+    sum2_push(rest, b ? best : w);
     best = b ? w : best;
     best_k = b ? k : best_k;
+  }
+  __device__ __forceinline__ void entry(double w, double bden, uint32_t k) {
+    topic(w, k);
+    sum2_push(rest, -bden);
   }
 };
 // The word's records, from the RowSums of its group of G lanes, K1 among them
@@ -408,19 +432,18 @@ __device__ __forceinline__ void write_sparse_records(const DevState &d, const Pa
   const WordTop top = word_top_of(t);
   const bool mine = rs.best_k == top.k1;
   const bool in_row = (__ballot(mine) & gmask) != 0ull;
-  const double held = group_sum<G>(rs.rest + (mine ? 0.0 : rs.best));
-  const Sum2 b = group_sum2<G>(rs.beta);
-  Sum2 out = sum2_add(Sum2{d.beta_sum[0], d.beta_sum[1]}, Sum2{-b.h, -b.l});
-  if (!in_row) out = sum2_add(out, Sum2{-top.a1, 0.0});
-  const double q = out.h + held, sw = q + top.a1;
-  if (leader) write_word_records(d, p, r, top, p.alpha * (p.two_branch ? sw : q), sw);
+  Sum2 s = rs.rest;
+  sum2_push(s, mine ? 0.0 : rs.best);
+  s = sum2_add(group_sum2<G>(s), Sum2{d.beta_sum[0], d.beta_sum[1]});
+  s = sum2_add(s, Sum2{in_row ? 0.0 : -top.a1, 0.0});
+  if (leader) write_word_sums(d, p, r, top, s);
 }
 
 // Step 1 (Sec. 3.2) and Q' (Sec. 2.2), one wave per word, four words per
 // workgroup, no workgroup barriers.  Lane l takes topics l, l + 64, ...: its top values, then a merge
 // across the wave by exchanges at distances 32 down to 1 (the top set is
-// unique under `better`, so every lane ends with the same list), then Q' and
-// the sum of W^[v] per lane in topic order, summed over the wave.  Without
+// unique under `better`, so every lane ends with the same list), then the sum
+// of W^[v] over the other topics (write_word_sums).  Without
 // p.sparse_pre a sparse row is spread into the wave's table of K counts first.
 // With it (use_topic_list) a sparse word's W^ is beta/den[k] outside
 // its row: its top values come from the row and from the first topics
@@ -530,31 +553,25 @@ __global__ __launch_bounds__(kBlock) void k_word_pre_wave(DevState d, Params p) 
 #pragma unroll
     for (int u = 0; u < kPreAhead; ++u) w[u] = what(c[u], p.beta, dn[u]);
   };
-  for (int k0 = lane; k0 < K; k0 += kPreAhead * kWave) {
-    double w[kPreAhead];
-    batch(k0, w);
-#pragma unroll
-    for (int u = 0; u < kPreAhead; ++u)
-      if (k0 + u * kWave < K) top_insert(t, w[u], uint32_t(k0 + u * kWave));
-  }
-  wave_top_merge(t);
-  const WordTop top = word_top_of(t);
-  double q = 0.0, sw = 0.0;
+  // one pass: the sum of all but the lane's largest W^, which is K1's or belongs to the sum as well
+  RowSums rs;
   for (int k0 = lane; k0 < K; k0 += kPreAhead * kWave) {
     double w[kPreAhead];
     batch(k0, w);
 #pragma unroll
     for (int u = 0; u < kPreAhead; ++u) {
-      const int k = k0 + u * kWave;
-      if (k < K) {
-        sw += w[u];
-        if (p.two_branch || uint32_t(k) != top.k1) q += p.alpha * w[u];
+      const uint32_t k = uint32_t(k0 + u * kWave);
+      if (k < uint32_t(K)) {
+        top_insert(t, w[u], k);
+        rs.topic(w[u], k);
       }
     }
   }
-  q = group_sum<kWave>(q);
-  sw = group_sum<kWave>(sw);
-  if (lane == 0) write_word_records(d, p, r, top, q, sw);
+  wave_top_merge(t);
+  const WordTop top = word_top_of(t);
+  sum2_push(rs.rest, rs.best_k == top.k1 ? 0.0 : rs.best);
+  const Sum2 others = group_sum2<kWave>(rs.rest);
+  if (lane == 0) write_word_sums(d, p, r, top, others);
 }
 
 // The topic list (the p.top_list topics of least T, ascending, lowest id first
@@ -2163,10 +2180,10 @@ constexpr int kTiledAhead = 2;              // chunks whose loads a group issues
 // fp64, so every prefix of S' is off by at most kEps of itself, kEps being a
 // little over 9 * 2^-24.  With x = u*Z the draw is decided only when x is
 // further than the bound on its own error and the edge's from both edges of
-// the chosen segment; otherwise (2e-4 of the tokens at K = 1,000, 2e-3 at
-// 10,000, 6e-3 at 32,768 in a fit's early iterations) a wave redoes the token
-// with all of its arithmetic in fp64 (exact_draw).  Either way the
-// topic is the one the fp64 evaluation gives.
+// the chosen segment; otherwise (2.4e-3 of the tokens at K = 10,000 and 5.7e-3
+// at 32,768 in a fit's first iterations, 1.7e-3 and 3.6e-3 after 50, counted in
+// a copy) a wave redoes the token with all of its arithmetic in fp64
+// (exact_draw).  Either way the topic is the one the fp64 evaluation gives.
 //   x against M and inside S': x - (M + prefix) is off by at most
 //                              2 * e, e = kEps * S'
 //   x inside Q':               x - (M + S') by at most (1 - u) * e, where
@@ -2556,7 +2573,7 @@ __device__ uint32_t exact_draw(const DevState &d, const Params &p, const WordF &
 __host__ __device__ inline int wf_entries(int K) { return (K + kWave) / kWave * kWave; }
 
 // Per iteration: qbase[b] = sum of alpha * beta/den[k] over block b of BS
-// topics, what a sparse word's Q' prefix starts from.
+// topics, what a word's Q' prefix starts from.
 template <int BS>
 __global__ __launch_bounds__(kBlock) void k_block_base(DevState d, Params p) {
   const int k = int(blockIdx.x) * kBlock + int(threadIdx.x);
@@ -2569,10 +2586,11 @@ __global__ __launch_bounds__(kBlock) void k_block_base(DevState d, Params p) {
 // the single-precision row.  A unit's setup touches only what changes: after
 // another sparse word the previous word's topics go back to beta/den[k], the
 // new word's entries are written and their excess over beta/den[k] is added
-// to their blocks (LDS atomics on whole numbers, q_units: exact_draw compares
-// with the block sums, so their bits must not depend on the waves' timing),
-// then the K / BS block sums are scanned.  At K = 32,768 the two-tile fp64
-// sampler filled three tiles of 16,400 topics per region.
+// to their blocks, then the K / BS block sums are scanned.  exact_draw compares
+// with these sums, so they are whole numbers (q_units): their bits depend on
+// the counts alone, not on the waves' timing, the cut or whether the row is
+// dense.  At K = 32,768 the two-tile fp64 sampler filled
+// three tiles of 16,400 topics per region.
 template <int NB>
 __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
                                                unsigned long long *__restrict__ stats) {
@@ -2599,7 +2617,7 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
   for (int k = K + tid; k < nwf; k += NB) wf[k] = 0.0f;
   uint32_t cur = 0xFFFFFFFFu, K1 = 0;
   double a1 = 0.0, qp = 0.0;
-  unsigned long long *qi = reinterpret_cast<unsigned long long *>(qb);  // a sparse word's block sums before the scan
+  unsigned long long *qi = reinterpret_cast<unsigned long long *>(qb);  // the block sums before the prefix is taken
   const int32_t *wrow = nullptr;   // the word's dense row, or null
   const uint32_t *held = nullptr;  // the sparse word whose row wf holds
   uint32_t held_nnz = 0, held_k1 = 0;
@@ -2635,15 +2653,32 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
       a1 = rec.a1;
       qp = rec.qp;
       const int ex = q_exponent(qp);
+      // every block starts from the topics that the word does not hold; K1's
+      // from its other topics, by the last wave (the one with the fewest
+      // entries), the load ahead of the rest
+      const int b1 = int(K1) / BS, kb = b1 * BS + lane;
+      const bool lw = wave == NB / kWave - 1;
+      double others = lw && lane < BS && kb < K && uint32_t(kb) != K1 ? d.bden[kb] : 0.0;
+      for (int q = tid; q < nb; q += NB) qi[q + 1] = q == b1 ? 0ull : q_units(d.qbase[q], ex);
+      auto add_others = [&]() {
+        if (lw) {
+          others = wave_incl_scan(p.alpha * others);
+          if (lane == BS - 1 && b1 < nb) atomicAdd(&qi[b1 + 1], q_units(others, ex));
+        }
+      };
       if (int32_t(v) < p.n_dense) {
         wrow = d.w_dense + size_t(v) * size_t(K);
+        __syncthreads();
         for (int k0 = wave * kWave; k0 < K; k0 += NB) {
           const int k = k0 + lane;
-          const double w = k < K && uint32_t(k) != K1 ? what(uint32_t(wrow[k]), p.beta, d.den[k]) : 0.0;
+          const bool in = k < K && uint32_t(k) != K1;
+          const double w = in ? what(uint32_t(wrow[k]), p.beta, d.den[k]) : 0.0;
           wf[k] = float(w * kWScale);
-          const double sum = group_sum<BS>(p.alpha * w);
-          if (lane % BS == 0 && k < K) qb[k / BS + 1] = sum;
+          // (a topic that the word does not hold adds nothing)
+          const unsigned long long sum = row_incl_scan_u64(in ? q_units(p.alpha * (w - d.bden[k]), ex) : 0ull);
+          if (lane % kGroup == kGroup - 1 && sum) atomicAdd(&qi[k / BS + 1], sum);
         }
+        add_others();
         held = nullptr;
         __syncthreads();
       } else {
@@ -2651,12 +2686,6 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
         const uint32_t *ents = d.ws_ent + d.ws_cap[s];
         const uint32_t nnz = d.ws_nnz[s];
         wrow = nullptr;
-        // K1's block: the sum of its other topics, by the last wave (the one
-        // with the fewest entries), its load ahead of the rest
-        const int b1 = int(K1) / BS, kb = b1 * BS + lane;
-        const bool lw = wave == NB / kWave - 1;
-        double others = lw && lane < BS && kb < K && uint32_t(kb) != K1 ? d.bden[kb] : 0.0;
-        for (int q = tid; q < nb; q += NB) qi[q + 1] = q == b1 ? 0ull : q_units(d.qbase[q], ex);
         if (held) {
           for (uint32_t q = tid; q < held_nnz; q += NB) {
             const uint32_t k = held[q] >> 16;
@@ -2673,10 +2702,7 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
           wf[k] = float(w * kWScale);
           if (k != K1) atomicAdd(&qi[k / BS + 1], q_units(p.alpha * (w - d.bden[k]), ex));
         }
-        if (lw) {
-          others = wave_incl_scan(p.alpha * others);
-          if (lane == BS - 1 && b1 < nb) atomicAdd(&qi[b1 + 1], q_units(others, ex));
-        }
+        add_others();
         held = ents;
         held_nnz = nnz;
         held_k1 = K1;
@@ -2688,7 +2714,7 @@ __device__ __forceinline__ void sampler_f_body(DevState d, Params p, uint32_t t,
       double *s_tot = s_u;  // [rounds * waves <= NB]; s_u is next written by the token batches
       for (int r = 0; r * NB < nb; ++r) {
         const int blk = r * NB + tid;
-        const double incl = wave_incl_scan(blk >= nb ? 0.0 : wrow ? qb[blk + 1] : q_value(qi[blk + 1], ex));
+        const double incl = wave_incl_scan(blk < nb ? q_value(qi[blk + 1], ex) : 0.0);
         if (blk < nb) qb[blk + 1] = incl;
         if (lane == kWave - 1) s_tot[r * (NB / kWave) + wave] = incl;
       }

@@ -308,11 +308,13 @@ __host__ __device__ inline double q_bound(double S, double qp, double tau) {
 __host__ __device__ inline float q_bound_f(double eq, float inv, float p, float xb, int bs) {
   return float(eq) * inv * (1.0f + 0x1p-20f) + (p + xb) * (float(bs + 4) * 0x1p-24f);
 }
-// Its Q' block sums of a sparse word are added up by many lanes in no fixed
-// order, so they are whole numbers of units of 2^(ex - 62), 2^ex being the
-// power of two above the word's Q': any order gives the same bits, no sum
-// passes 2^62, and a term is off by at most 2^-62 of Q' (an fp64 sum by 2^-53
-// of itself at each addition).
+// Its Q' block sums are added up by many lanes in no fixed order, so they are
+// whole numbers of units of 2^(ex - 62), 2^ex being the power of two above the
+// word's Q': any order gives the same bits, no sum passes 2^62 by more than
+// the terms' roundings, and a term is off by at most 2^-62 of Q' (an fp64 sum
+// by 2^-53 of itself at each addition).  The terms are the block's sum of
+// alpha * beta/den[k] (K1's block: of the other topics) and
+// alpha * (W^[v][k] - beta/den[k]) of every topic that the word holds.
 __host__ __device__ inline int q_exponent(double qp) {
   int ex = 0;
   (void)frexp(qp, &ex);

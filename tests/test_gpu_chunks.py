@@ -107,3 +107,23 @@ def test_chunked_edge_shapes():
             m.set_assignments(z, 3)
             m.iterate(1)
             compare_draws(m.counts(D=False, W=False)["z"], zo, flags, c.N)
+
+
+# K = 1,000 with enough sparse words for the topic list, and the certified sampler's K: the resident path's sparse rows
+# against the out-of-core path's dense ones, and the hybrid cutoff's extremes
+@pytest.mark.parametrize("K,V,n_docs", [(1000, 9000, 4000), (2500, 2000, 3000), (10_000, 400, 1500)])
+def test_dense_and_sparse_rows_draw_the_same(K, V, n_docs):
+    rng = np.random.default_rng(K)
+    doc = np.repeat(np.arange(n_docs, dtype=np.int32), rng.integers(1, 120, n_docs))
+    word = (rng.zipf(1.3, doc.shape[0]) % V).astype(np.int32)
+    spec = lda_synth.CorpusSpec("rows", n_docs, ("poisson", 1.0), V, 0.0, K, K, 0.05)
+    c = lda_synth.Corpus(spec, word, doc, V, int(doc.max()) + 1)
+    say("dense and sparse rows K=%d N=%d" % (K, c.N))
+    outs = []
+    for opts in ({}, {"chunks": 3}, {"dense_cutoff": -1}, {"dense_cutoff": 1 << 30}):
+        with make_lda(c, **opts) as m:
+            m.iterate(5)
+            outs.append((m.counts(D=False, W=False)["z"], m.loglik()))
+    for z, ll in outs[1:]:
+        assert np.array_equal(z, outs[0][0])
+        assert ll == pytest.approx(outs[0][1], rel=1e-13)

@@ -64,7 +64,7 @@ def test_equal_w_hat_takes_the_lowest_topic(K, beta):
         compare_draws(m.counts(D=False, W=False)["z"], want, flags, max(word.size, 10 ** 6))
 
 
-def _records(word, doc, z, V, K, alpha, beta, two):
+def _records(word, doc, z, V, K, alpha, beta, two, dense_cutoff=0):
     """(a1, Q', sum W^, K1) per word id as the kernels left them in device memory after a scoring call."""
     import ctypes
 
@@ -83,7 +83,7 @@ def _records(word, doc, z, V, K, alpha, beta, two):
 
     fa, ff = lda.ALLOC_FN(alloc), lda.FREE_FN(free)
     o = lda.Options()
-    o.dev_alloc, o.dev_free, o.two_branch = fa, ff, int(two)
+    o.dev_alloc, o.dev_free, o.two_branch, o.dense_cutoff = fa, ff, int(two), dense_cutoff
     lib, h, ll = lda.load_library(), ctypes.c_void_p(), ctypes.c_double()
     w, d, z = (np.ascontiguousarray(x, np.int32) for x in (word, doc, z))
     ptr = lambda a: ctypes.c_void_p(a.ctypes.data)  # noqa: E731
@@ -130,10 +130,13 @@ def test_q_prime_of_a_word_held_by_one_topic(K, beta, two):
     top = wh[np.arange(V), k1].copy()
     wh[np.arange(V), k1] = 0
     q = wh.sum(1)
-    # sums of at most 200 / 64 + 16 + 6 terms of one sign per strand, each added and rounded once, in 53 bits
-    bound = 40 * 2.0 ** -53
+    # the exact sums rounded once, times alpha
+    bound = 2.5 * 2.0 ** -53
     if not two:
         assert np.array_equal(got[:, 3], k1) and np.array_equal(got[:, 0], top.astype(np.float64))
     want = np.longdouble(alpha) * (total if two else q)
     assert np.max(np.abs(got[:, 1] - want) / want) < bound
     assert np.max(np.abs(got[:, 2] - total) / total) < bound
+    # the same bits from dense rows (of which out-of-core handles are made), and without a list of few topics
+    for cutoff in (-1, 1 << 30):
+        assert np.array_equal(_records(word, doc, z, V, K, alpha, beta, two, cutoff), got)
