@@ -76,7 +76,7 @@ def test_chunked_snapshot_follows_the_oracle(c3r):
 
 def test_chunked_edge_shapes():
     """Empty documents at and between chunk edges, more chunks than non-empty documents would
-    give equal shares, a word split into many regions, and the tiled sampler (K = 20,000)."""
+    give equal shares, a word split into many regions, and a K above the fp64 row's (20,000)."""
     rng = np.random.default_rng(41)
     lens = rng.integers(0, 120, 400)
     lens[::7] = 0

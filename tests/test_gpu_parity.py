@@ -436,7 +436,7 @@ def test_topic_list_running_out_follows_the_oracle():
 def test_heavy_documents_follow_the_oracle(K, marks, shuffle):
     """Documents longer than 4,096 tokens get a whole workgroup in the doc pass and the D rebuild
     (the others one wave): with heavy documents of 4,097 to 30,000 tokens among light ones, both
-    skip bitmaps, shuffled input and the tiled sampler, the draws are the oracle's and the counts
+    skip bitmaps, shuffled input and the single-precision sampler, the draws are the oracle's and the counts
     the histograms of z.  The first snapshot gives every word one topic, so many tokens skip."""
     rng = np.random.default_rng(99)
     lens = np.concatenate([rng.integers(1, 300, 200), [4097, 8000, 30000, 4096, 12345]])
@@ -466,9 +466,9 @@ def test_heavy_documents_follow_the_oracle(K, marks, shuffle):
 @pytest.mark.parametrize("K", [16384, 5000])
 @pytest.mark.parametrize("block", [0, 256, 512, 1024])
 def test_sampler_block_sizes_at_large_K(K, block):
-    """Every sampler workgroup size the LDS allows draws what the oracle draws at a
-    large K (the W^ row of K fp64 values fills most of the LDS); the default picks
-    one of them."""
+    """Every sampler workgroup size that can be asked for draws what the oracle draws
+    at a large K (the W^ row of K values fills half of the LDS or more); the default
+    picks one of them."""
     rng = np.random.default_rng(5)
     c = _Tiny(rng.integers(0, 60, 6000), np.sort(rng.integers(0, 40, 6000)), 60, K, 0.01)
     say("sampler block %d K=%d" % (block, K))
@@ -497,9 +497,9 @@ def _large_k_corpus(K):
 
 @pytest.mark.parametrize("K", [32768, 20000])
 def test_large_k_tiled_sampler_follows_the_oracle(K):
-    """K above what one workgroup's LDS holds as an fp64 row: the tiled sampler
-    (two topic tiles, three passes per region) draws what the oracle draws, over
-    three snapshots, with dense split words and sparse words; counts and LLPT too."""
+    """K above what one workgroup's LDS holds as an fp64 row: the sampler with the
+    single-precision row draws what the oracle draws, over three snapshots, with
+    dense split words and sparse words; counts and LLPT (in two topic tiles) too."""
     c = _large_k_corpus(K)
     cnt_w = np.bincount(c.word, minlength=c.V)
     assert (cnt_w > K).sum() >= 1  # a dense word, split into regions of 10,000
@@ -521,7 +521,7 @@ def test_large_k_tiled_sampler_follows_the_oracle(K):
 
 
 def test_large_k_schedule_invariance():
-    """The tiled sampler's draws do not depend on the region size."""
+    """The draws at the largest K do not depend on the region size."""
     c = _large_k_corpus(32768)
     with lda_make(c) as a:
         a.iterate(2)
@@ -533,7 +533,7 @@ def test_large_k_schedule_invariance():
 
 
 def test_large_k_two_branch_follows_the_oracle():
-    """The two-branch ablation through the tiled sampler and the large-K precompute
+    """The two-branch ablation through the largest row and the large-K precompute
     (K = 32,768) against the oracle's two-branch form."""
     c = _large_k_corpus(32768)
     kw = dict(M=c.n_docs, V=c.V, K=c.K, alpha=c.alpha, beta=c.beta)
@@ -550,7 +550,7 @@ def test_large_k_two_branch_follows_the_oracle():
 @pytest.mark.parametrize("opts", [dict(g=1), dict(g=3), dict(no_skip=True), dict(dense_cutoff=-1),
                                   dict(dense_cutoff=1 << 30)])
 def test_large_k_options_leave_the_draws_unchanged(opts):
-    """S_est depth, the skip test and the hybrid-W cutoff at K = 32,768 (tiled sampler,
+    """S_est depth, the skip test and the hybrid-W cutoff at K = 32,768 (certified draws,
     bitmap rebuilds, sparse-word precompute or its dense fallback)."""
     c = _large_k_corpus(32768)
     say("large K options %s" % opts)
